@@ -215,7 +215,7 @@ dwg_status mc_prepare(const float* P, const float* N, const float* area, const f
   int64_t m = 0;
   DWG_PROPAGATE(mc_corners(mp, *w, &m, st));
   if (mp.iso_points) DWG_PROPAGATE(mc_append_points(P, n, *w, st));
-  DWG_PROPAGATE(knn_grid(P, n, w->knn, st));
+  DWG_PROPAGATE(knn_grid(P, n, mp.k, w->knn, st));
   DWG_PROPAGATE(mc_clear(*w, st));
   return eval_prepare(P, N, area, delta, n, w->pos, w->ld, kp, false, static_cast<char*>(ws) + c.used, st, es);
 }
@@ -630,7 +630,7 @@ dwg_status dwg_init_normals(dwg_init_kind kind, uint64_t seed, const float* P, i
   Carver c(ws);
   AnchorCtx x;
   carve_anchor(c, n, feat_chunk(n), DWG_FEAT_ANCHORS, &x);
-  DWG_PROPAGATE(anchor_build(P, n, x, st));
+  DWG_PROPAGATE(anchor_build(P, n, DWG_FEAT_K, x, st));
   for (int64_t q0 = 0; q0 < n; q0 += x.chunk) {
     const int64_t cnt = std::min<int64_t>(x.chunk, n - q0);
     DWG_PROPAGATE(anchor_features(P, n, q0, cnt, x, x.feat, st));
@@ -654,8 +654,7 @@ dwg_status dwg_knn(const float* R, int64_t nr, const float* Q, int64_t m, int se
     return DWG_E_WORKSPACE;
   }
   DWG_PROPAGATE(check_device());
-  return knn_run(R, nr, Q, m, self_skip, nullptr, k, idx, dist, ws, ws_bytes,
-                 static_cast<hipStream_t>(stream));
+  return knn_run(R, nr, Q, m, self_skip, k, idx, dist, ws, static_cast<hipStream_t>(stream));
 }
 
 dwg_status dwg_delta_knn_mean(const float* P, int64_t n, int k, float scale, float* delta,
@@ -664,10 +663,6 @@ dwg_status dwg_delta_knn_mean(const float* P, int64_t n, int k, float scale, flo
   DWG_CHECK(k >= 1 && k <= kMaxK, "k must be in [1, %d]", kMaxK);
   DWG_CHECK(n > k && n < (int64_t(1) << 31), "need k < n < 2^31");
   DWG_CHECK(std::isfinite(scale) && scale > 0.0f, "scale must be finite and > 0");
-  Carver c(nullptr);
-  c.take<int32_t>((size_t)n * k);
-  c.take<float>((size_t)n * k);
-  const size_t head = c.used;
   const size_t need = aux_bytes(n);
   DWG_CHECK(ws || ws_bytes == 0, "ws is NULL but ws_bytes > 0");
   if (!ws || ws_bytes < need) {
@@ -675,13 +670,7 @@ dwg_status dwg_delta_knn_mean(const float* P, int64_t n, int k, float scale, flo
     return DWG_E_WORKSPACE;
   }
   DWG_PROPAGATE(check_device());
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  Carver w(ws);
-  int32_t* idx = w.take<int32_t>((size_t)n * k);
-  float* dist = w.take<float>((size_t)n * k);
-  DWG_PROPAGATE(knn_run(P, n, P, n, 1, nullptr, k, idx, dist, static_cast<char*>(ws) + head,
-                        ws_bytes - head, st));
-  return delta_from_knn(dist, n, k, scale, delta, st);
+  return delta_mean(P, n, k, scale, delta, ws, static_cast<hipStream_t>(stream));
 }
 
 dwg_status dwg_delta_knn_window(const float* P, int64_t n, int k, float vmin, float vmax, float* delta,
@@ -736,7 +725,7 @@ dwg_status dwg_delta_anchor_mean(const float* P, int64_t n, int k, int64_t n_anc
   AnchorCtx x;
   carve_anchor(c, n, feat_chunk(n), n_anchor, &x);
   DWG_CHECK(x.na > k, "too few anchors (%lld) for k = %d", (long long)x.na, k);
-  DWG_PROPAGATE(anchor_build(P, n, x, st));
+  DWG_PROPAGATE(anchor_build(P, n, k, x, st));
   return anchor_delta(P, n, x, k, scale, delta, st);
 }
 

@@ -67,16 +67,14 @@ struct GridParams {
   int64_t ncells;
 };
 struct KnnWork {
-  float* bbox_part;  // [256 * 6] per-block bbox partials
-  double* range;     // [6] trimmed box per axis (lo, hi)
-  int64_t* below;    // [3] reference points under each axis' lo
-  int32_t* hist;     // [3 * 1024] axis histograms of the trimming passes
   GridParams* gp;
   int32_t* key;      // [nr] cell of each reference point
+  int32_t* rank;     // [nr] rank of each reference point in its cell
   int32_t* start;    // [max_cells + 1] first sorted slot of each cell
-  int32_t* cursor;   // [max_cells] scatter cursors
-  int32_t* sums;     // scan tile totals
+  unsigned long long* state;  // scan ticket and tile states
   float4* sorted;    // [nr] (x, y, z, index bits) in cell order
+  int32_t* total;    // [4096 + 1] query buckets
+  float4* items;     // [mq] queries (x, y, z, number) in cell order
   int32_t* defer;    // [1 + mq] count and list of the queries left to the second search pass
   int64_t mq;        // most queries of one search call
 };
@@ -94,7 +92,7 @@ struct AnchorCtx {
 };
 size_t carve_anchor(Carver& c, int64_t n, int64_t chunk, int64_t n_anchor, AnchorCtx* out);
 size_t anchor_ws_bytes(int64_t n, int64_t chunk, int64_t n_anchor);
-dwg_status anchor_build(const float* P, int64_t n, const AnchorCtx& x, hipStream_t stream);
+dwg_status anchor_build(const float* P, int64_t n, int k, const AnchorCtx& x, hipStream_t stream);
 dwg_status anchor_features(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, float* feat,
                            hipStream_t stream);
 dwg_status anchor_delta(const float* P, int64_t n, const AnchorCtx& x, int k, float scale, float* delta,
@@ -209,7 +207,7 @@ dwg_status morton_frame(const float* P, int64_t n, float* bpart, float* box, dou
 // query array with leading dimension qld (no skipping; m <= the capacity carved for the grid).
 // One thread searches each query to the end, in the given order: meant for query sets that
 // are already in spatial order.
-dwg_status knn_grid(const float* R, int64_t nr, const KnnWork& w, hipStream_t st);
+dwg_status knn_grid(const float* R, int64_t nr, int k, const KnnWork& w, hipStream_t st);
 dwg_status knn_search(const float* Q, int64_t qld, int64_t q0, int64_t m, const KnnWork& w, int k, int32_t* idx,
                       float* dist, hipStream_t st);
 
@@ -292,11 +290,9 @@ dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const
 dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, hipStream_t stream);
 dwg_status launch_random_normals(uint64_t seed, int64_t n, float* N, hipStream_t stream);
 
-dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip,
-                   const int64_t* skip_stride, int k, int32_t* idx, float* dist, void* ws,
-                   size_t ws_bytes, hipStream_t stream);
-dwg_status delta_from_knn(const float* dist, int64_t n, int k, float scale, float* delta,
-                          hipStream_t stream);
+dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k, int32_t* idx,
+                   float* dist, void* ws, hipStream_t stream);
+dwg_status delta_mean(const float* P, int64_t n, int k, float scale, float* delta, void* ws, hipStream_t stream);
 dwg_status pca_normals(const float* P, int64_t n, int k, float* N, void* ws, hipStream_t stream);
 dwg_status gauss_normals(const float* P, int64_t n, float* N, hipStream_t stream);
 dwg_status voronoi_area(const float* P, int64_t n, int m, float* area, void* ws, hipStream_t stream);

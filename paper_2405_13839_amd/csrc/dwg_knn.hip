@@ -2,20 +2,20 @@
 // "Poisson Kernels": mean distance to the k nearest neighbours) and the k = 16 anchor
 // features of the learned initial normals.
 //
-// Grid build: bounding box (deterministic two-stage min/max), trimmed per axis to the
-// quantiles 1/1024 and 1 - 1/1024 of the reference points (three passes of a 1024-bin
-// histogram, each refining the range the last one found), cell size from the trimmed box's
-// volume with at most ~8 cells per reference point, counting sort of the reference points
-// by cell (atomic cursors; the order inside a cell is arbitrary, which is harmless because
+// Grid build: the box is the range of a stratified sample of at most 4096 points (all of them
+// below that), trimmed per axis to the sample's quantiles 1/1024 and 1 - 1/1024; the cell size
+// is the one at which a point is expected to share its cell with kCellShare * k others, from
+// the sample's pair counts on two coarse grids (k_grid_setup); counting sort of the reference
+// points by cell (atomic ranks; the order inside a cell is arbitrary, which is harmless because
 // candidates are ranked by the pair (squared distance, index)). Points outside the trimmed
-// box sit in its border cells: a few points far from the rest then no longer stretch the
+// box sit in its border cells: a few points far from the rest then do not stretch the
 // cells until the whole cloud shares one, and the search stays exact because projecting
-// onto a box shortens no distance (see k_knn). Query: Chebyshev rings of
-// cells around the query's own cell, a row of cells (one contiguous range of the sorted
+// onto a box shortens no distance (see k_knn). Query: the 27 cells around the query's own, then
+// Chebyshev rings of cells, a row of cells (one contiguous range of the sorted
 // points) at a time, keeping the k best candidates in registers, until the k-th best
-// distance is below the distance to the next ring. One thread per query takes rings 0..3;
-// the few queries still unfinished (isolated points) are then searched by a wavefront each
-// (k_knn, k_knn_wave).
+// distance is below the distance to the faces of the searched cube. One thread per query takes
+// rings up to kFirstPassRings; the few queries still unfinished (isolated points) are then
+// searched by a wavefront each (k_knn, k_knn_wave).
 #include <cfloat>
 #include <climits>
 #include <cmath>
@@ -26,9 +26,10 @@ namespace dwg {
 namespace {
 
 constexpr int kScanBlock = 256;
-constexpr int kScanItems = 4;  // elements per thread in the block scan
+constexpr int kScanItems = 8;  // elements per thread of the tiled scan
 constexpr int kScanTile = kScanBlock * kScanItems;
-
+constexpr int kScanOneBlock = 1024;   // threads of the one-block scan
+constexpr int64_t kScanOneMax = 8192; // longest array of the one-block scan (two of its rounds)
 
 __global__ __launch_bounds__(256) void k_bbox_partial(const float* __restrict__ R, int64_t n,
                                                       float* __restrict__ part) {
@@ -89,106 +90,54 @@ __global__ __launch_bounds__(256) void k_bbox_final(const float* __restrict__ pa
   if (threadIdx.x < 6) out6[threadIdx.x] = v6[threadIdx.x];
 }
 
-// Grid box trimming. range[2d], range[2d + 1] = the current [lo, hi] of axis d (FP64) and
-// below[d] = the number of reference points under lo; kTrimLevels passes of k_axis_hist /
-// k_trim_refine narrow each axis to the bins that hold the ranks floor(n / 1024) and
-// n - 1 - floor(n / 1024) of its coordinates.
+// ---- Grid setup ----
+constexpr int kSetupBlock = 1024;
+constexpr int kSample = 4096;                       // points the grid is laid out from
+constexpr int kSamplePer = kSample / kSetupBlock;   // of them per thread
 constexpr int kTrimBins = 1024;
 constexpr int kTrimLevels = 3;
+constexpr int kCoarse = 32;                         // cells per axis of the finer counting grid
+constexpr int kSetupTable = kCoarse * kCoarse * kCoarse;
+// Other reference points that a reference point is expected to share its cell with, per
+// neighbour searched for. The thread-per-query pass takes the 27 cells around the query, which
+// reach 1 to 1.5 cells from it: on a surface 0.6 k points per cell put about 3 k of them there, and
+// it finishes nearly every query that is not isolated. Both passes for 0.4 / 0.5 / 0.65 / 0.8 in
+// place of 0.6 (whole calls, us): radius of 1M points by 10 of 4,096 anchors 570 / 373 / 341 / 320,
+// 10 and 15 nearest of 131,071 points with their areas 626 / 565 / 560 / 591, 10 nearest of 50,001
+// points 124 / 132 / 141 / 149. (8 cells per reference point, whatever the cloud, give 0.1 k on a
+// sampled surface of 4,096 points: rings 2 and 3, 84 rows of cells instead of 9.)
+constexpr float kCellShare = 0.6f;
 
-// range = the bounding box (from the per-block partials, reduced by one block of 256
-// threads), below = 0, histograms cleared.
-__global__ __launch_bounds__(256) void k_trim_init(const float* __restrict__ part, int nblocks,
-                                                   double* __restrict__ range, int64_t* __restrict__ below,
-                                                   int32_t* __restrict__ hist) {
-  __shared__ float lds[6][256];
-  for (int i = threadIdx.x; i < 3 * kTrimBins; i += blockDim.x) hist[i] = 0;
-  float v6[6];
-  reduce_bbox_parts(part, nblocks, lds, v6);
-  if (threadIdx.x < 3) {
-    range[2 * threadIdx.x] = v6[threadIdx.x];
-    range[2 * threadIdx.x + 1] = v6[3 + threadIdx.x];
-    below[threadIdx.x] = 0;
-  }
+struct SetupLds {
+  int hist[3 * kTrimBins];
+  int wtot[kSetupBlock / 64];
+  int found[3][2];
+  int64_t below_lo[3], below[3];
+  double range[6];
+  float red[6][kSetupBlock / 64];
+  unsigned pairs[2];
+  GridParams gp;
+};
+
+__device__ __forceinline__ uint32_t hash32(uint32_t x) {  // a 32-bit integer mixer
+  x ^= x >> 16;
+  x *= 0x7feb352du;
+  x ^= x >> 15;
+  x *= 0x846ca68bu;
+  return x ^ (x >> 16);
 }
 
-// Per axis, the histogram of the coordinates inside [lo, hi] over kTrimBins equal bins
-// (LDS counts per block, then added to `hist`); NaN coordinates fall in no bin.
-__global__ __launch_bounds__(256) void k_axis_hist(const float* __restrict__ R, int64_t n,
-                                                   const double* __restrict__ range, int32_t* __restrict__ hist) {
-  __shared__ int32_t h[3 * kTrimBins];
-  for (int i = threadIdx.x; i < 3 * kTrimBins; i += blockDim.x) h[i] = 0;
-  double lo[3], hi[3], sc[3];
-  for (int d = 0; d < 3; ++d) {
-    lo[d] = range[2 * d];
-    hi[d] = range[2 * d + 1];
-    sc[d] = hi[d] > lo[d] ? kTrimBins / (hi[d] - lo[d]) : 0.0;
-  }
-  __syncthreads();
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    for (int d = 0; d < 3; ++d) {
-      const double x = R[d * n + i];
-      if (x >= lo[d] && x <= hi[d]) {
-        int b = (int)((x - lo[d]) * sc[d]);
-        b = b < kTrimBins - 1 ? b : kTrimBins - 1;
-        atomicAdd(&h[d * kTrimBins + b], 1);
-      }
-    }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 3 * kTrimBins; i += blockDim.x)
-    if (h[i]) atomicAdd(&hist[i], h[i]);
+// Index of sample s of S out of n points: all of them when n == S, else a pseudo-random point of
+// the s-th of S equal strata (a fixed step would sample a raster of points in columns).
+__device__ __forceinline__ int64_t sample_index(int s, int S, int64_t n) {
+  if (n == S) return s;
+  const double u = (double)hash32((uint32_t)s) * 0x1p-32;
+  const int64_t i = (int64_t)(((double)s + u) * ((double)n / (double)S));
+  return i < n ? i : n - 1;
 }
 
-// One block of 256 threads per axis (blockIdx.x): the bins holding ranks rlo and rhi
-// (counting the points below lo) become the new range, found from an exclusive scan of the
-// histogram in LDS; the histogram is cleared for the next pass. A range whose ranks are not
-// found (NaN coordinates among the points) is kept.
-__global__ __launch_bounds__(256) void k_trim_refine(int32_t* __restrict__ hist, double* __restrict__ range,
-                                                     int64_t* __restrict__ below, int64_t rlo, int64_t rhi) {
-  constexpr int kPer = kTrimBins / 256;
-  __shared__ int64_t scan[256];
-  __shared__ int found[2];
-  __shared__ int64_t below_lo;
-  const int d = blockIdx.x, t = threadIdx.x;
-  int32_t* hd = hist + d * kTrimBins;
-  int64_t c[kPer], sum = 0;
-  for (int k = 0; k < kPer; ++k) {
-    c[k] = hd[t * kPer + k];
-    hd[t * kPer + k] = 0;
-    sum += c[k];
-  }
-  scan[t] = sum;
-  if (t < 2) found[t] = -1;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {  // inclusive scan of the per-thread sums
-    const int64_t x = t >= off ? scan[t - off] : 0;
-    __syncthreads();
-    scan[t] += x;
-    __syncthreads();
-  }
-  int64_t cum = below[d] + scan[t] - sum;  // points below this thread's first bin
-  for (int k = 0; k < kPer; ++k) {
-    if (cum <= rlo && cum + c[k] > rlo) {
-      found[0] = t * kPer + k;
-      below_lo = cum;
-    }
-    if (cum <= rhi && cum + c[k] > rhi) found[1] = t * kPer + k;
-    cum += c[k];
-  }
-  __syncthreads();
-  if (t != 0) return;
-  const double lo = range[2 * d], hi = range[2 * d + 1];
-  const int blo = found[0], bhi = found[1];
-  if (blo < 0 || bhi < 0 || !(hi > lo)) return;
-  const double w = (hi - lo) / kTrimBins;
-  range[2 * d] = lo + blo * w;
-  range[2 * d + 1] = bhi == kTrimBins - 1 ? hi : lo + (bhi + 1) * w;
-  below[d] = below_lo;
-}
-
-// Grid parameters over the trimmed box (single thread).
-__global__ void k_grid_params(const double* __restrict__ range, int64_t max_cells, GridParams* __restrict__ gp) {
-  if (threadIdx.x != 0) return;
+// Grid parameters for the cell edge h (grown until the grid has at most max_cells cells).
+__device__ void grid_dims(const double* range, double h, int64_t max_cells, GridParams* gp) {
   float mn[3], mx[3];
   for (int d = 0; d < 3; ++d) {  // the FP64 range rounded outwards to FP32
     mn[d] = (float)range[2 * d];
@@ -207,7 +156,9 @@ __global__ void k_grid_params(const double* __restrict__ range, int64_t max_cell
   // slabs thinner than 1e-3 of the largest extent count as that thickness for the volume
   double vol = 1.0;
   for (int d = 0; d < 3; ++d) vol *= fmax(ext[d], 1e-3 * emax);
-  double h = cbrt(vol / (double)max_cells);
+  const double hmin = cbrt(vol / (double)max_cells);
+  if (!(h >= hmin)) h = hmin;
+  if (!(h <= emax)) h = emax;
   // every point of the box must fall inside the grid: grow h until the uncapped cell counts
   // multiply to at most max_cells (at most a few steps; the cap only bounds the loop)
   double dd[3] = {1.0, 1.0, 1.0};
@@ -224,18 +175,173 @@ __global__ void k_grid_params(const double* __restrict__ range, int64_t max_cell
     dd[0] = dd[1] = dd[2] = 1.0;
     h = emax;
   }
-  int dims[3] = {(int)dd[0], (int)dd[1], (int)dd[2]};
   GridParams g;
   g.ox = mn[0];
   g.oy = mn[1];
   g.oz = mn[2];
   g.h = (float)h;
   g.ih = (float)(1.0 / h);
-  g.nx = dims[0];
-  g.ny = dims[1];
-  g.nz = dims[2];
-  g.ncells = (int64_t)dims[0] * dims[1] * dims[2];
+  g.nx = (int)dd[0];
+  g.ny = (int)dd[1];
+  g.nz = (int)dd[2];
+  g.ncells = (int64_t)g.nx * g.ny * g.nz;
   *gp = g;
+}
+
+// Sum of v over the block into *out (LDS, zero before; integer atomics).
+__device__ __forceinline__ void block_add(unsigned v, unsigned* out) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if ((threadIdx.x & 63) == 0 && v) atomicAdd(out, v);
+}
+
+// Lays out the grid of the references R for searches of k neighbours, by one block of
+// kSetupBlock threads; s.gp holds it when this returns (after a barrier). tab: kSetupTable LDS
+// counters. What the sample says sets the cost of the search only, never its result.
+__device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_cells, int k, SetupLds& s, int* tab) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int S = (int)(n < kSample ? n : kSample);
+  float x[kSamplePer][3];
+  float mn[3] = {FLT_MAX, FLT_MAX, FLT_MAX}, mx[3] = {-FLT_MAX, -FLT_MAX, -FLT_MAX};
+#pragma unroll
+  for (int j = 0; j < kSamplePer; ++j) {
+    const int i = t + j * kSetupBlock;
+    const int64_t o = sample_index(i < S ? i : 0, S, n);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      x[j][d] = R[d * n + o];
+      mn[d] = fminf(mn[d], x[j][d]);
+      mx[d] = fmaxf(mx[d], x[j][d]);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    for (int o = 32; o > 0; o >>= 1) {
+      mn[d] = fminf(mn[d], __shfl_xor(mn[d], o, 64));
+      mx[d] = fmaxf(mx[d], __shfl_xor(mx[d], o, 64));
+    }
+  if (lane == 0)
+    for (int d = 0; d < 3; ++d) {
+      s.red[d][wv] = mn[d];
+      s.red[3 + d][wv] = mx[d];
+    }
+  for (int i = t; i < 3 * kTrimBins; i += kSetupBlock) s.hist[i] = 0;
+  for (int i = t; i < kSetupTable; i += kSetupBlock) tab[i] = 0;
+  if (t < 2) s.pairs[t] = 0;
+  __syncthreads();
+  if (t < 3) {
+    float lo = s.red[t][0], hi = s.red[3 + t][0];
+    for (int w = 1; w < kSetupBlock / 64; ++w) {
+      lo = fminf(lo, s.red[t][w]);
+      hi = fmaxf(hi, s.red[3 + t][w]);
+    }
+    s.range[2 * t] = lo;
+    s.range[2 * t + 1] = hi;
+    s.below[t] = 0;
+  }
+  // Trimming: each level narrows an axis to the bins that hold the ranks floor(S / 1024) and
+  // S - 1 - floor(S / 1024) of the sample's coordinates. A range whose ranks are not found
+  // (NaN coordinates) is kept.
+  const int64_t rlo = S / kTrimBins, rhi = S - 1 - S / kTrimBins;
+  for (int level = 0; level < kTrimLevels && rlo > 0; ++level) {
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const double lo = s.range[2 * d], hi = s.range[2 * d + 1];
+      const double sc = hi > lo ? kTrimBins / (hi - lo) : 0.0;
+#pragma unroll
+      for (int j = 0; j < kSamplePer; ++j) {
+        const double v = x[j][d];
+        if (t + j * kSetupBlock < S && v >= lo && v <= hi) {
+          const double f = (v - lo) * sc;
+          const int b = f > 0.0 ? (f < kTrimBins - 1 ? (int)f : kTrimBins - 1) : 0;
+          atomicAdd(&s.hist[d * kTrimBins + b], 1);
+        }
+      }
+    }
+    if (t < 6) s.found[t >> 1][t & 1] = -1;
+    __syncthreads();
+    // threads 256 d .. 256 d + 255 scan the bins of axis d, four each
+    const int d = t >> 8, b0 = (t & 255) * 4;
+    int c[4] = {0, 0, 0, 0}, sum = 0, inc = 0;
+    if (d < 3) {
+      for (int q = 0; q < 4; ++q) {
+        c[q] = s.hist[d * kTrimBins + b0 + q];
+        s.hist[d * kTrimBins + b0 + q] = 0;
+        sum += c[q];
+      }
+      inc = sum;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+      }
+      if (lane == 63) s.wtot[wv] = inc;
+    }
+    __syncthreads();
+    if (d < 3) {
+      int64_t cum = s.below[d] + inc - sum;
+      for (int w = 4 * d; w < wv; ++w) cum += s.wtot[w];
+      for (int q = 0; q < 4; ++q) {
+        if (cum <= rlo && cum + c[q] > rlo) {
+          s.found[d][0] = b0 + q;
+          s.below_lo[d] = cum;
+        }
+        if (cum <= rhi && cum + c[q] > rhi) s.found[d][1] = b0 + q;
+        cum += c[q];
+      }
+    }
+    __syncthreads();
+    if (t < 3) {
+      const double lo = s.range[2 * t], hi = s.range[2 * t + 1];
+      const int blo = s.found[t][0], bhi = s.found[t][1];
+      if (blo >= 0 && bhi >= 0 && hi > lo) {
+        const double w = (hi - lo) / kTrimBins;
+        s.range[2 * t] = lo + blo * w;
+        s.range[2 * t + 1] = bhi == kTrimBins - 1 ? hi : lo + (bhi + 1) * w;
+        s.below[t] = s.below_lo[t];
+      }
+    }
+  }
+  __syncthreads();
+  // Pair counts of the sample on the trimmed box cut into 32 and 16 cells along its longest
+  // axis: sum over the points of the other points in their cell.
+  double emax = 0.0;
+  for (int d = 0; d < 3; ++d) {
+    const double e = s.range[2 * d + 1] - s.range[2 * d];
+    if (e > emax) emax = e;
+  }
+  const bool flat = !(emax > 0.0 && emax <= 1e30);
+  const float ie = flat ? 0.0f : (float)(kCoarse / emax);
+  for (int g = 0; g < 2; ++g) {
+    int cell[kSamplePer];
+#pragma unroll
+    for (int j = 0; j < kSamplePer; ++j) {
+      int c3[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        c3[d] = (int)fminf(fmaxf(floorf((x[j][d] - (float)s.range[2 * d]) * ie), 0.0f), (float)(kCoarse - 1)) >> g;
+      cell[j] = (c3[2] * kCoarse + c3[1]) * kCoarse + c3[0];
+      if (t + j * kSetupBlock < S) atomicAdd(&tab[cell[j]], 1);
+    }
+    __syncthreads();
+    unsigned others = 0;
+#pragma unroll
+    for (int j = 0; j < kSamplePer; ++j)
+      if (t + j * kSetupBlock < S) others += (unsigned)tab[cell[j]] - 1u;
+    block_add(others, &s.pairs[g]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSamplePer; ++j) tab[cell[j]] = 0;
+    __syncthreads();
+  }
+  if (t == 0) {
+    // the points sharing a cell of edge e grow like e^D (D = 2 on a surface)
+    const double scale = S > 1 ? (double)(n - 1) / ((double)S * (double)(S - 1)) : 1.0;
+    const double fine = fmax((double)s.pairs[0], 0.5) * scale, coarse = fmax((double)s.pairs[1], 1.0) * scale;
+    const double dim = fmin(3.0, fmax(1.0, log2(coarse / fine)));
+    const double h = flat ? 1.0 : (emax / kCoarse) * pow((double)kCellShare * k / fine, 1.0 / dim);
+    grid_dims(s.range, h, max_cells, &s.gp);
+  }
+  __syncthreads();
 }
 
 __device__ __forceinline__ void cell_of(const GridParams& g, float x, float y, float z, int& cx,
@@ -253,8 +359,212 @@ __global__ void k_zero_i32(int32_t* __restrict__ a, int64_t n) {
     a[i] = 0;
 }
 
+// Exclusive scan of a block's per-thread values in thread order (up to 1024 threads); the
+// block's total in *total. lds: blockDim.x / 64 ints.
+__device__ __forceinline__ int32_t block_exclusive(int32_t v, int32_t* lds, int32_t* total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  int32_t inc = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += y;
+  }
+  __syncthreads();
+  if (lane == 63) lds[wv] = inc;
+  __syncthreads();
+  int32_t before = 0, all = 0;
+  for (int w = 0; w < nw; ++w) {
+    const int32_t x = lds[w];
+    before += w < wv ? x : 0;
+    all += x;
+  }
+  *total = all;
+  return before + inc - v;
+}
+
+// In-place exclusive scan of a[0..n) by one block, total to a[n].
+__global__ __launch_bounds__(kScanOneBlock) void k_scan_one(int32_t* __restrict__ a, int64_t n) {
+  __shared__ int32_t lds[kScanOneBlock / 64];
+  int32_t carry = 0;
+  for (int64_t b0 = 0; b0 < n; b0 += 4 * kScanOneBlock) {
+    const int64_t i = b0 + 4 * (int64_t)threadIdx.x;
+    int32_t v[4], tot = 0, all;
+    for (int k = 0; k < 4; ++k) {
+      v[k] = i + k < n ? a[i + k] : 0;
+      tot += v[k];
+    }
+    int32_t run = carry + block_exclusive(tot, lds, &all);
+    for (int k = 0; k < 4; ++k) {
+      if (i + k < n) a[i + k] = run;
+      run += v[k];
+    }
+    carry += all;
+  }
+  if (threadIdx.x == 0) a[n] = carry;
+}
+
+// In-place exclusive scan in one pass over the array (chained scan with look-back): a block
+// takes the next tile from a ticket counter, publishes the tile's sum, and adds up the sums of
+// the tiles before it, a wavefront's 64 at a time, back to the nearest one whose full prefix is
+// known. A tile's state is one 64-bit word (flag << 32 | value), written and read by device
+// atomics, so the value needs no fence of its own. Every wait ends: a block waits only for
+// tiles with smaller tickets, whose blocks are running and publish their sum before they wait
+// themselves. The length is n_dev->ncells where n_dev is given (the launch then covers the
+// largest possible length), else n. state[0] is the ticket, state[1 + tile] the tiles; all zero
+// before the launch.
+constexpr unsigned long long kTileSum = 1ull << 32, kTilePrefix = 2ull << 32;
+
+__device__ __forceinline__ unsigned long long load_state(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_state(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum of the tiles before `tile` (by one wavefront; every lane gets it).
+__device__ __forceinline__ int32_t look_back(const unsigned long long* __restrict__ tiles, int64_t tile) {
+  const int lane = threadIdx.x & 63;
+  int32_t sum = 0;
+  for (int64_t top = tile - 1; top >= 0;) {
+    const int64_t at = top - lane;
+    const unsigned long long v = at >= 0 ? load_state(&tiles[at]) : kTilePrefix;
+    const unsigned long long known = __ballot((v >> 32) != 0ull), full = __ballot((v >> 32) == 2ull);
+    const int stop = full ? __ffsll((long long)full) - 1 : 63;  // lanes 0..stop are needed
+    const unsigned long long need = stop == 63 ? ~0ull : ((2ull << stop) - 1ull);
+    if ((known & need) != need) {
+      __builtin_amdgcn_s_sleep(1);
+      continue;
+    }
+    int32_t x = lane <= stop ? (int32_t)(uint32_t)v : 0;
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    sum += x;
+    if (full) break;
+    top -= 64;
+  }
+  return sum;
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_scan_chain(int32_t* __restrict__ a, int64_t n,
+                                                           const GridParams* __restrict__ n_dev,
+                                                           unsigned long long* __restrict__ state) {
+  __shared__ int32_t lds[kScanBlock / 64];
+  __shared__ int64_t s_tile;
+  __shared__ int32_t s_before;
+  if (n_dev) n = n_dev->ncells;
+  if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&state[0], 1ull);
+  __syncthreads();
+  const int64_t tile = s_tile;
+  if (tile * kScanTile >= n) return;
+  const int64_t i = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  int32_t v[kScanItems], tot = 0, all;
+  if (i + kScanItems <= n) {
+    const int4 lo = *reinterpret_cast<const int4*>(a + i), hi = *reinterpret_cast<const int4*>(a + i + 4);
+    v[0] = lo.x, v[1] = lo.y, v[2] = lo.z, v[3] = lo.w, v[4] = hi.x, v[5] = hi.y, v[6] = hi.z, v[7] = hi.w;
+  } else {
+    for (int k = 0; k < kScanItems; ++k) v[k] = i + k < n ? a[i + k] : 0;
+  }
+  for (int k = 0; k < kScanItems; ++k) tot += v[k];
+  int32_t run = block_exclusive(tot, lds, &all);
+  if (threadIdx.x < 64) {
+    unsigned long long* const tiles = state + 1;
+    if (tile > 0 && threadIdx.x == 0) store_state(&tiles[tile], kTileSum | (uint32_t)all);
+    const int32_t before = look_back(tiles, tile);
+    if (threadIdx.x == 0) {
+      store_state(&tiles[tile], kTilePrefix | (uint32_t)(before + all));
+      s_before = before;
+      if ((tile + 1) * kScanTile >= n) a[n] = before + all;
+    }
+  }
+  __syncthreads();
+  run += s_before;
+  for (int k = 0; k < kScanItems; ++k) {
+    const int32_t x = v[k];
+    v[k] = run;
+    run += x;
+  }
+  if (i + kScanItems <= n) {
+    *reinterpret_cast<int4*>(a + i) = make_int4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<int4*>(a + i + 4) = make_int4(v[4], v[5], v[6], v[7]);
+  } else {
+    for (int k = 0; k < kScanItems; ++k)
+      if (i + k < n) a[i + k] = v[k];
+  }
+}
+
+// Grid layout of a reference set too large for k_grid_small (one block).
+__global__ __launch_bounds__(kSetupBlock) void k_grid_setup(const float* __restrict__ R, int64_t n,
+                                                            int64_t max_cells, int k,
+                                                            GridParams* __restrict__ gp) {
+  __shared__ SetupLds s;
+  __shared__ int tab[kSetupTable];
+  grid_setup(R, n, max_cells, k, s, tab);
+  if (threadIdx.x == 0) *gp = s.gp;
+}
+
+// The whole grid of at most kSmallRefs references by one block: layout, counts and their scan in
+// LDS, counting sort. One launch (about 20 us) for the five of the larger sets: the anchor grids
+// (4,096 to 8,191 points) are built anew by every radius and feature call.
+constexpr int kSmallRefs = 8192;
+constexpr int kSmallPer = kSmallRefs / kSetupBlock;
+
+__global__ __launch_bounds__(kSetupBlock) void k_grid_small(const float* __restrict__ R, int64_t n,
+                                                            int64_t max_cells, int k,
+                                                            GridParams* __restrict__ gp,
+                                                            int32_t* __restrict__ start,
+                                                            float4* __restrict__ sorted) {
+  __shared__ SetupLds s;
+  __shared__ int tab[kSetupTable];
+  __shared__ int32_t lds[kSetupBlock / 64];
+  grid_setup(R, n, max_cells < kSetupTable ? max_cells : kSetupTable, k, s, tab);  // tab is zero again
+  const GridParams g = s.gp;
+  const int t = threadIdx.x;
+  if (t == 0) *gp = g;
+  float4 p[kSmallPer];
+  int cell[kSmallPer], rank[kSmallPer];
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    const int64_t i = t + j * kSetupBlock;
+    cell[j] = -1;
+    if (i < n) {
+      p[j] = make_float4(R[i], R[n + i], R[2 * n + i], __int_as_float((int)i));
+      int cx, cy, cz;
+      cell_of(g, p[j].x, p[j].y, p[j].z, cx, cy, cz);
+      cell[j] = (cz * g.ny + cy) * g.nx + cx;
+      rank[j] = atomicAdd(&tab[cell[j]], 1);
+    }
+  }
+  __syncthreads();
+  const int nc = (int)g.ncells;
+  int32_t carry = 0;
+  for (int b0 = 0; b0 < nc; b0 += kSetupBlock) {
+    const int i = b0 + t;
+    int32_t all;
+    const int32_t before = carry + block_exclusive(i < nc ? tab[i] : 0, lds, &all);
+    if (i < nc) {
+      tab[i] = before;
+      start[i] = before;
+    }
+    carry += all;
+  }
+  if (t == 0) start[nc] = carry;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j)
+    if (cell[j] >= 0) sorted[tab[cell[j]] + rank[j]] = p[j];
+}
+
+// Clears the cell counts (ncells + 1 of them) and the scan state (as many words as tiles of the
+// actual grid need).
+__global__ void k_grid_zero(const GridParams* __restrict__ gp, int32_t* __restrict__ count,
+                            unsigned long long* __restrict__ state) {
+  const int64_t nc = gp->ncells, words = 1 + (nc + kScanTile - 1) / kScanTile;
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = t0; i <= nc; i += step) count[i] = 0;
+  for (int64_t i = t0; i < words; i += step) state[i] = 0ull;
+}
+
+// Cell of each reference point and its rank among the cell's points (arbitrary order).
 __global__ void k_cell_count(const float* __restrict__ R, int64_t n, const GridParams* __restrict__ gp,
-                             int32_t* __restrict__ key, int32_t* __restrict__ count) {
+                             int32_t* __restrict__ key, int32_t* __restrict__ rank, int32_t* __restrict__ count) {
   const GridParams g = *gp;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -262,103 +572,162 @@ __global__ void k_cell_count(const float* __restrict__ R, int64_t n, const GridP
     cell_of(g, R[i], R[n + i], R[2 * n + i], cx, cy, cz);
     const int32_t c = (int32_t)(((int64_t)cz * g.ny + cy) * g.nx + cx);
     key[i] = c;
-    atomicAdd(&count[c], 1);
+    rank[i] = atomicAdd(&count[c], 1);
   }
-}
-
-// Exclusive scan, stage 1: each block scans kScanTile elements of `a` in place and writes
-// its total to `sums[block]`. Elements past `n` read as 0.
-__global__ __launch_bounds__(kScanBlock) void k_scan_tiles(int32_t* __restrict__ a, int64_t n,
-                                                           int32_t* __restrict__ sums) {
-  __shared__ int32_t lds[kScanBlock];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int32_t v[kScanItems];
-  int32_t tot = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    v[k] = (base + k < n) ? a[base + k] : 0;
-    tot += v[k];
-  }
-  lds[threadIdx.x] = tot;
-  __syncthreads();
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    const int32_t x = ((int)threadIdx.x >= off) ? lds[threadIdx.x - off] : 0;
-    __syncthreads();
-    lds[threadIdx.x] += x;
-    __syncthreads();
-  }
-  int32_t run = lds[threadIdx.x] - tot;  // exclusive prefix of this thread
-  for (int k = 0; k < kScanItems; ++k) {
-    if (base + k < n) a[base + k] = run;
-    run += v[k];
-  }
-  if (threadIdx.x == kScanBlock - 1) sums[blockIdx.x] = lds[kScanBlock - 1];
-}
-
-// Stage 2: one block scans the tile totals serially in chunks (exclusive) and writes the
-// grand total to a[n] (the end marker of the last cell).
-__global__ __launch_bounds__(kScanBlock) void k_scan_sums(int32_t* __restrict__ sums, int64_t nt,
-                                                          int32_t* __restrict__ a, int64_t n) {
-  __shared__ int32_t lds[kScanBlock];
-  const int64_t per = (nt + kScanBlock - 1) / kScanBlock;
-  const int64_t b0 = (int64_t)threadIdx.x * per, b1 = min(b0 + per, nt);
-  int32_t tot = 0;
-  for (int64_t i = b0; i < b1; ++i) tot += sums[i];
-  lds[threadIdx.x] = tot;
-  __syncthreads();
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    const int32_t x = ((int)threadIdx.x >= off) ? lds[threadIdx.x - off] : 0;
-    __syncthreads();
-    lds[threadIdx.x] += x;
-    __syncthreads();
-  }
-  int32_t run = lds[threadIdx.x] - tot;
-  for (int64_t i = b0; i < b1; ++i) {
-    const int32_t x = sums[i];
-    sums[i] = run;
-    run += x;
-  }
-  if (threadIdx.x == kScanBlock - 1) a[n] = lds[kScanBlock - 1];
-}
-
-__global__ void k_scan_add(int32_t* __restrict__ a, int64_t n, const int32_t* __restrict__ sums) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] += sums[i / kScanTile];
 }
 
 // Scatter reference points into cell order: sorted[pos] = (x, y, z, index bits).
 __global__ void k_scatter(const float* __restrict__ R, int64_t n, const int32_t* __restrict__ key,
-                          const int32_t* __restrict__ start, int32_t* __restrict__ cursor,
+                          const int32_t* __restrict__ rank, const int32_t* __restrict__ start,
                           float4* __restrict__ sorted) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t c = key[i];
-    const int32_t pos = start[c] + atomicAdd(&cursor[c], 1);
-    sorted[pos] = make_float4(R[i], R[n + i], R[2 * n + i], __int_as_float((int)i));
-  }
+       i += (int64_t)gridDim.x * blockDim.x)
+    sorted[start[key[i]] + rank[i]] = make_float4(R[i], R[n + i], R[2 * n + i], __int_as_float((int)i));
 }
 
-// (d2, idx) < (e2, jdx) lexicographically
-__device__ __forceinline__ bool less_pair(float d2, int i, float e2, int j) {
-  return d2 < e2 || (d2 == e2 && i < j);
+// A candidate (d2, j) as one FP64 number: the bits of d2 (>= 0) plus 2^20 in the high word, j (>= 0)
+// in the low word. Positive FP64 numbers order like their bits, so keys order like the pairs
+// (d2, j); 2^20 keeps every key a normal number and d2 = +inf a finite one. The high word of a
+// NaN d2, as an unsigned integer, is above that of every key.
+constexpr uint32_t kKeyBias = 0x00100000u;
+constexpr uint32_t kKeyInf = 0x7f800000u + kKeyBias;
+
+__device__ __forceinline__ uint32_t key_high(double k) { return (uint32_t)__double2hiint(k); }
+__device__ __forceinline__ float key_d2(double k) { return __uint_as_float(key_high(k) - kKeyBias); }
+
+// min and max of two keys. Keys are never NaN; written as instructions because fmin and fmax
+// first quiet a possible signalling NaN, which is one more FP64 instruction per slot.
+__device__ __forceinline__ double key_min(double a, double b) {
+  double r;
+  __asm__("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double key_max(double a, double b) {
+  double r;
+  __asm__("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
 }
 
-// Insert (d2, j) into the ascending list bd/bi of K entries, dropping the last (fully
-// unrolled, register resident). The caller has checked that it beats the last entry.
+// Inserts key x into the ascending list b of K keys, dropping the last: b[u] becomes
+// max(b[u - 1], min(b[u], x)), two FP64 instructions per slot (ranking the pairs by compares and
+// selects took eight).
 template <int K>
-__device__ __forceinline__ void insert_sorted(float d2, int j, float* bd, int* bi) {
+__device__ __forceinline__ void insert_key(double x, double* b) {
 #pragma unroll
-  for (int u = K - 1; u >= 1; --u) {
-    const bool up = less_pair(d2, j, bd[u - 1], bi[u - 1]);
-    const bool here = !up && less_pair(d2, j, bd[u], bi[u]);
-    const float nd = up ? bd[u - 1] : (here ? d2 : bd[u]);
-    const int ni = up ? bi[u - 1] : (here ? j : bi[u]);
-    bd[u] = nd;
-    bi[u] = ni;
+  for (int u = K - 1; u >= 1; --u) b[u] = key_max(b[u - 1], key_min(b[u], x));
+  b[0] = key_min(b[0], x);
+}
+
+template <int K>
+__device__ __forceinline__ void clear_keys(double* b) {
+#pragma unroll
+  for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, 0x7fffffff);
+}
+
+// What a finished query writes: its neighbour list, or the kernel radius that the list gives
+// (k_delta_window's and the mean distance's arithmetic, without storing the lists).
+enum EmitMode { kEmitList = 0, kEmitMean = 1, kEmitWindow = 2 };
+struct KnnEmit {
+  int mode;
+  int32_t* idx;   // [m][k]
+  float* dist;    // [m][k] or NULL
+  float* delta;   // [m]
+  float scale;    // kEmitMean
+  float vmin, vmax;  // kEmitWindow
+};
+
+template <int K>
+__device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const double* b) {
+  float d[K];
+#pragma unroll
+  for (int u = 0; u < K; ++u) d[u] = sqrtf(key_d2(b[u]));
+  if (e.mode == kEmitList) {
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+      e.idx[q * K + u] = __double2loint(b[u]);
+      if (e.dist) e.dist[q * K + u] = d[u];
+    }
+  } else if (e.mode == kEmitMean) {
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < K; ++u) s += d[u];
+    e.delta[q] = e.scale * (s / (float)K);
+  } else {
+    // the mean of the distances that lie in [vmin, vmax]; when none does, the mean of all k
+    // clamped to [vmin, vmax] (Sec. 5.2 "Poisson Kernels")
+    double s = 0.0, all = 0.0;
+    int c = 0;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+      const double x = d[u];
+      all += x;
+      if (x >= e.vmin && x <= e.vmax) {
+        s += x;
+        ++c;
+      }
+    }
+    double r = c > 0 ? s / c : all / K;
+    if (c == 0) r = r < e.vmin ? e.vmin : (r > e.vmax ? e.vmax : r);
+    e.delta[q] = (float)r;
   }
-  if (less_pair(d2, j, bd[0], bi[0])) {
-    bd[0] = d2;
-    bi[0] = j;
+}
+
+// The same by a wavefront whose lane u holds key u (u < k).
+__device__ __forceinline__ void emit_wave(const KnnEmit& e, int64_t q, int k, double key) {
+  const int lane = threadIdx.x & 63;
+  const float d = sqrtf(key_d2(key));
+  if (e.mode == kEmitList) {
+    if (lane < k) {
+      e.idx[q * k + lane] = __double2loint(key);
+      if (e.dist) e.dist[q * k + lane] = d;
+    }
+    return;
   }
+  float s = 0.0f;
+  double sd = 0.0, all = 0.0;
+  int c = 0;
+  for (int u = 0; u < k; ++u) {
+    const float du = __shfl(d, u, 64);
+    s += du;
+    all += (double)du;
+    if ((double)du >= e.vmin && (double)du <= e.vmax) {
+      sd += (double)du;
+      ++c;
+    }
+  }
+  if (e.mode == kEmitMean) {
+    if (lane == 0) e.delta[q] = e.scale * (s / (float)k);
+  } else {
+    double r = c > 0 ? sd / c : all / k;
+    if (c == 0) r = r < e.vmin ? e.vmin : (r > e.vmax ? e.vmax : r);
+    if (lane == 0) e.delta[q] = (float)r;
+  }
+}
+
+// Lower bound of the distance from a query to every reference outside the cube of cells
+// [c - r, c + r]: the smallest distance of its projection onto the grid's box to a face of the
+// cube that has cells beyond it (+inf when none has). f: the projection's cell coordinates.
+// The margin covers the rounding of the cell coordinates (both points', relative to the
+// number of cells) and of the squared distance it is compared with.
+__device__ __forceinline__ float outside_bound(const GridParams& g, const float* f, int cx, int cy, int cz, int r) {
+  float lb = INFINITY;
+  const int c[3] = {cx, cy, cz}, nn[3] = {g.nx, g.ny, g.nz};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const float in = f[d] - (float)c[d];  // in [0, 1]
+    if (c[d] - r > 0) lb = fminf(lb, (float)r + in);
+    if (c[d] + r < nn[d] - 1) lb = fminf(lb, (float)r + 1.0f - in);
+  }
+  const float margin = 1e-6f + 5e-7f * (float)max(g.nx, max(g.ny, g.nz));
+  return fmaxf(lb - margin, 0.0f) * (g.h * 0.999999f);
+}
+
+// Cell coordinates of the query's projection onto the grid's box, each in [0, cells].
+__device__ __forceinline__ void cell_coords(const GridParams& g, float x, float y, float z, int cx, int cy, int cz,
+                                            float* f) {
+  f[0] = fminf(fmaxf((x - g.ox) * g.ih, (float)cx), (float)(cx + 1));
+  f[1] = fminf(fmaxf((y - g.oy) * g.ih, (float)cy), (float)(cy + 1));
+  f[2] = fminf(fmaxf((z - g.oz) * g.ih, (float)cz), (float)(cz + 1));
 }
 
 // A query of the search: output row q, position, and the reference index it skips (-1: none).
@@ -368,173 +737,277 @@ struct KnnQuery {
   int skip;
 };
 
-// Work item p (see k_knn): the p-th reference in cell order (SELF) or query q0 + p of Q.
-template <bool SELF>
-__device__ __forceinline__ KnnQuery knn_query_of(int64_t p, const float* __restrict__ Q, int64_t qld, int64_t q0,
-                                                 const float4* __restrict__ sorted, int skip_mode, int64_t stride) {
+// Where the queries of a search are read: work item p is the p-th entry (x, y, z, query number) of
+// `items`, or, without items, query q0 + p of the planar array Q with leading dimension ld. Skip
+// mode: 0 none; 1 reference i for query i; 2 reference i / stride for query i when i % stride == 0
+// (i counted from the start of Q).
+struct QuerySet {
+  const float* Q;
+  int64_t ld, q0, m;
+  const float4* items;
+  int skip_mode;
+  int64_t stride;
+};
+
+__device__ __forceinline__ KnnQuery knn_query_of(const QuerySet& s, int64_t p) {
   KnnQuery k;
-  int64_t gq;
-  if (SELF) {
-    const float4 sp = sorted[p];
-    k.q = gq = __float_as_int(sp.w);
-    k.x = sp.x;
-    k.y = sp.y;
-    k.z = sp.z;
+  if (s.items) {
+    const float4 it = s.items[p];
+    k.q = __float_as_int(it.w);
+    k.x = it.x;
+    k.y = it.y;
+    k.z = it.z;
   } else {
     k.q = p;
-    gq = q0 + p;
-    k.x = Q[gq];
-    k.y = Q[qld + gq];
-    k.z = Q[2 * qld + gq];
+    k.x = s.Q[s.q0 + p];
+    k.y = s.Q[s.ld + s.q0 + p];
+    k.z = s.Q[2 * s.ld + s.q0 + p];
   }
+  const int64_t gq = s.q0 + k.q;
   k.skip = -1;
-  if (skip_mode == 1) k.skip = (int)gq;
-  if (skip_mode == 2 && (gq % stride) == 0) k.skip = (int)(gq / stride);
+  if (s.skip_mode == 1) k.skip = (int)gq;
+  if (s.skip_mode == 2 && ((uint32_t)gq % (uint32_t)s.stride) == 0) k.skip = (int)((uint32_t)gq / (uint32_t)s.stride);
   return k;
 }
 
-// The cells of ring r (the cube of half-width r around cell (cx, cy, cz) minus the cube of
-// half-width r - 1) in the grid row (z, y), as at most two ranges [b0, e0), [b1, e1) of
-// `sorted`: the whole row [xl, xh] (clipped to the grid) when |z - cz| or |y - cy| is r, else
-// its end cells cx - r and cx + r where they are inside the grid. The cells of a row are
-// consecutive, so a range costs two loads of `start` however many cells it spans.
-__device__ __forceinline__ void ring_row(const GridParams& g, const int32_t* __restrict__ start, int cx, int cy,
-                                         int cz, int r, int z, int y, int xl, int xh, int32_t& b0, int32_t& e0,
-                                         int32_t& b1, int32_t& e1) {
+// The cells of the cube of half-width r around cell (cx, cy, cz) outside that of half-width rp
+// (rp < r; -1: the whole cube) in the grid row (z, y), as at most two ranges [b0, e0), [b1, e1)
+// of `sorted`: the whole row [xl, xh] (clipped to the grid) when |z - cz| or |y - cy| exceeds rp,
+// else its two ends. The cells of a row are consecutive, so a range costs two loads of `start`
+// however many cells it spans.
+__device__ __forceinline__ void shell_row(const GridParams& g, const int32_t* __restrict__ start, int cx, int cy,
+                                          int cz, int rp, int z, int y, int xl, int xh, int32_t& b0, int32_t& e0,
+                                          int32_t& b1, int32_t& e1) {
   const int64_t row = ((int64_t)z * g.ny + y) * g.nx;
   b0 = e0 = b1 = e1 = 0;
-  if (z == cz - r || z == cz + r || y == cy - r || y == cy + r) {
+  if (max(abs(z - cz), abs(y - cy)) > rp) {
     b0 = start[row + xl];
     e0 = start[row + xh + 1];
     return;
   }
-  if (cx - r >= 0) {
-    b0 = start[row + cx - r];
-    e0 = start[row + cx - r + 1];
+  if (cx - rp - 1 >= xl) {
+    b0 = start[row + xl];
+    e0 = start[row + cx - rp];
   }
-  if (r > 0 && cx + r <= g.nx - 1) {
-    b1 = start[row + cx + r];
-    e1 = start[row + cx + r + 1];
+  if (cx + rp + 1 <= xh) {
+    b1 = start[row + cx + rp + 1];
+    e1 = start[row + xh + 1];
   }
 }
 
-// skip_mode: 0 none; 1 reference i == query i; 2 reference i / stride when i % stride == 0.
-// Queries q = 0..m-1 are points q0 + q of the planar array Q with leading dimension qld;
-// results go to idx[q][K], dist[q][K].
-// SELF: the queries are the references themselves (m = their count, skip_mode 1): work item p
-// takes the p-th reference in cell order from `sorted` and writes the row of its original
-// index, so the lanes of a wavefront search neighbouring cells (same results, in another
-// order of work).
-// Two passes, so that a few isolated queries (outliers, whose search spans thousands of
-// cells) do not hold up the wavefronts of everyone else: k_knn (one thread per work item p)
-// searches rings 0..rcap and appends the items it has not finished to defer[1..] (defer[0]
-// counts them); k_knn_wave then searches each deferred item with a whole wavefront. A query's
-// result, the k smallest (distance^2, index) pairs, does not depend on the order in which
-// candidates are met, so it is the same whichever pass finishes it.
-template <int K, bool SELF>
-__global__ __launch_bounds__(256) void k_knn(const float* __restrict__ Q, int64_t qld, int64_t q0,
-                                             int64_t m, const GridParams* __restrict__ gp,
-                                             const int32_t* __restrict__ start,
-                                             const float4* __restrict__ sorted, int skip_mode,
-                                             int64_t stride, int rcap, int32_t* __restrict__ defer,
-                                             int32_t* __restrict__ idx, float* __restrict__ dist) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= m) return;
-  const GridParams g = *gp;
-  const KnnQuery kq = knn_query_of<SELF>(p, Q, qld, q0, sorted, skip_mode, stride);
-  const int64_t q = kq.q;
+// Search of one query by one thread over the cubes of half-width 1, 2, .. rcap: true when it is
+// finished (b holds its list), false when it needs more rings.
+template <int K>
+__device__ __forceinline__ bool knn_thread(const GridParams& g, const int32_t* __restrict__ start,
+                                           const float4* __restrict__ sorted, const KnnQuery& kq, int rcap, double* b) {
   const float qx = kq.x, qy = kq.y, qz = kq.z;
   const int skip = kq.skip;
-  float bd[K];
-  int bi[K];
-#pragma unroll
-  for (int s = 0; s < K; ++s) {
-    bd[s] = INFINITY;
-    bi[s] = 0x7fffffff;
-  }
+  clear_keys<K>(b);
   int cx, cy, cz;
   cell_of(g, qx, qy, qz, cx, cy, cz);
+  float f[3];
+  cell_coords(g, qx, qy, qz, cx, cy, cz, f);
   const int rmax = max(g.nx, max(g.ny, g.nz));
-  // Rings 0..rcap, a row of cells at a time (ring_row). Every point outside the cube of
-  // half-width r lies more than r h from the query, which ends the search once the k-th best
-  // distance is within r h; the cube of half-width rmax holds the whole grid. (A point, or
-  // the query, outside the grid's box sits in the border cell that holds its projection onto
-  // the box; projecting both onto the box shortens no distance, so the bound still holds.)
-  bool done = false;
-  const int rlim = min(rcap, rmax);
-  for (int r = 0; r <= rlim; ++r) {
-    const int zl = max(cz - r, 0), zh = min(cz + r, g.nz - 1);
-    const int yl = max(cy - r, 0), yh = min(cy + r, g.ny - 1);
-    const int xl = max(cx - r, 0), xh = min(cx + r, g.nx - 1);
+  auto scan = [&](int32_t pp, int32_t e) {
+    if (pp >= e) return;
+    float4 next = sorted[pp];
+    while (pp < e) {
+      const float4 sp = next;
+      ++pp;
+      if (pp < e) next = sorted[pp];
+      const int j = __float_as_int(sp.w);
+      const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
+      const uint32_t hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
+      if (j != skip && hi <= key_high(b[K - 1])) insert_key<K>(__hiloint2double((int)hi, j), b);
+    }
+  };
+  // The cube of half-width 1: nine rows of up to three cells, the query's own row first, their
+  // eighteen ends loaded together.
+  {
+    const int xl = max(cx - 1, 0), xh = min(cx + 1, g.nx - 1);
+    constexpr int kOrder[9][2] = {{0, 0}, {0, -1}, {0, 1}, {-1, 0}, {1, 0}, {-1, -1}, {-1, 1}, {1, -1}, {1, 1}};
+    int32_t b0[9], e0[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      const int z = cz + kOrder[i][0], y = cy + kOrder[i][1];
+      const bool in = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
+      const int64_t row = in ? ((int64_t)z * g.ny + y) * g.nx : 0;
+      b0[i] = start[row + xl];
+      e0[i] = in ? start[row + xh + 1] : b0[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) scan(b0[i], e0[i]);
+  }
+  // Then a ring at a time. The search ends once the k-th best distance is within outside_bound.
+  // (A point, or the query, outside the grid's box sits in the border cell that holds its
+  // projection onto the box; projecting both onto the box shortens no distance, so the bound
+  // still holds.)
+  for (int r = 1;; ++r) {
+    const float lb = outside_bound(g, f, cx, cy, cz, r);
+    if (lb == INFINITY || (key_high(b[K - 1]) < kKeyInf && key_d2(b[K - 1]) <= lb * lb) || r >= rmax) return true;
+    if (r >= rcap) return false;
+    const int rr = r + 1;
+    const int zl = max(cz - rr, 0), zh = min(cz + rr, g.nz - 1);
+    const int yl = max(cy - rr, 0), yh = min(cy + rr, g.ny - 1);
+    const int xl = max(cx - rr, 0), xh = min(cx + rr, g.nx - 1);
     for (int z = zl; z <= zh; ++z) {
       for (int y = yl; y <= yh; ++y) {
         int32_t b0, e0, b1, e1;
-        ring_row(g, start, cx, cy, cz, r, z, y, xl, xh, b0, e0, b1, e1);
-        for (int seg = 0; seg < 2; ++seg) {
-          const int32_t e = seg == 0 ? e0 : e1;
-          for (int32_t pp = seg == 0 ? b0 : b1; pp < e; ++pp) {
-            const float4 sp = sorted[pp];
-            const int j = __float_as_int(sp.w);
-            if (j == skip) continue;
-            const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
-            const float d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
-            if (!less_pair(d2, j, bd[K - 1], bi[K - 1])) continue;
-            insert_sorted<K>(d2, j, bd, bi);
-          }
-        }
+        shell_row(g, start, cx, cy, cz, r, z, y, xl, xh, b0, e0, b1, e1);
+        scan(b0, e0);
+        scan(b1, e1);
       }
     }
-    const float lb = (float)r * g.h;
-    if ((bd[K - 1] < INFINITY && bd[K - 1] <= lb * lb) || r >= rmax) {
-      done = true;
-      break;
-    }
-  }
-  if (!done) {  // left to k_knn_wave
-    defer[1 + atomicAdd(&defer[0], 1)] = (int32_t)p;
-    return;
-  }
-#pragma unroll
-  for (int s = 0; s < K; ++s) {
-    idx[q * K + s] = bi[s];
-    if (dist) dist[q * K + s] = sqrtf(bd[s]);
   }
 }
 
+// The k nearest references of every query of the set; results go to the rows q of `em`.
+// Two passes, so that a few isolated queries (outliers, whose search spans thousands of
+// cells) do not hold up the wavefronts of everyone else: k_knn (one thread per work item p)
+// searches the cubes up to half-width rcap and appends the items it has not finished to
+// defer[1..] (defer[0] counts them); k_knn_wave then searches each deferred item with a whole
+// wavefront. A query's result, the k smallest (distance^2, index) pairs, does not depend on the
+// order in which candidates are met, so it is the same whichever pass finishes it. Work items in
+// cell order let the lanes of a wavefront walk the same rows of cells: the same loads, loops of
+// nearly the same length.
+template <int K>
+__global__ __launch_bounds__(256) void k_knn(QuerySet qs, const GridParams* __restrict__ gp,
+                                             const int32_t* __restrict__ start,
+                                             const float4* __restrict__ sorted, int rcap,
+                                             int32_t* __restrict__ defer, KnnEmit em) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= qs.m) return;
+  const GridParams g = *gp;
+  const KnnQuery kq = knn_query_of(qs, p);
+  double b[K];
+  if (knn_thread<K>(g, start, sorted, kq, rcap, b))
+    emit_query<K>(em, kq.q, b);
+  else
+    defer[1 + atomicAdd(&defer[0], 1)] = (int32_t)p;
+}
+
+// ---- Cell order for queries in no particular order (the points of a cloud against its anchors).
+// A counting sort by a Morton code of the query's cell, coarsened to 4 bits per axis: block counts
+// in LDS added to the totals, a scan, and a second pass in which every block reserves its range
+// of each bucket (the order inside a bucket is arbitrary, which changes no result). 1M queries of
+// 4,096 anchors, k = 10: the search takes 457 us in the given order (a wavefront's lanes then load
+// 64 different lines at a time) and less than half of it in this one; sorting inside blocks
+// of 2,048 queries gained nothing, since a wavefront's queries then still lie in some 40 cells.
+constexpr int kOrderBlock = 1024;
+constexpr int kOrderPer = 8;
+constexpr int kOrderTile = kOrderBlock * kOrderPer;
+constexpr int kBuckets = 4096;
+
+__device__ __forceinline__ uint32_t spread4(uint32_t v) {
+  return (v & 1u) | (v & 2u) << 2 | (v & 4u) << 4 | (v & 8u) << 6;
+}
+
+__device__ __forceinline__ int bucket_of(const GridParams& g, int sh, float x, float y, float z) {
+  int cx, cy, cz;
+  cell_of(g, x, y, z, cx, cy, cz);
+  return (int)(spread4((uint32_t)cx >> sh) | spread4((uint32_t)cy >> sh) << 1 | spread4((uint32_t)cz >> sh) << 2);
+}
+
+// The shift that leaves 4 bits of every cell coordinate.
+__device__ __forceinline__ int bucket_shift(const GridParams& g) {
+  const int top = max(g.nx, max(g.ny, g.nz)) - 1;
+  return top > 15 ? 28 - __clz(top) : 0;
+}
+
+// Clears the bucket totals and the count of deferred items.
+__global__ void k_order_clear(int32_t* __restrict__ total, int32_t* __restrict__ defer) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kBuckets) total[i] = 0;
+  if (i == 0) defer[0] = 0;
+}
+
+// FILL = false: adds the block's bucket counts to total. FILL = true: total holds the buckets'
+// first slots and serves as their cursor; writes the items.
+template <bool FILL>
+__global__ __launch_bounds__(kOrderBlock) void k_order(QuerySet qs, const GridParams* __restrict__ gp,
+                                                       int32_t* __restrict__ total, float4* __restrict__ items) {
+  __shared__ int32_t cnt[kBuckets];
+  const int t = threadIdx.x;
+  const GridParams g = *gp;
+  const int sh = bucket_shift(g);
+  const int64_t base = (int64_t)blockIdx.x * kOrderTile;
+  for (int i = t; i < kBuckets; i += kOrderBlock) cnt[i] = 0;
+  __syncthreads();
+  float x[kOrderPer][3];
+  int bucket[kOrderPer], rank[kOrderPer];
+#pragma unroll
+  for (int u = 0; u < kOrderPer; ++u) {
+    const int64_t p = base + t + u * kOrderBlock;
+    bucket[u] = -1;
+    if (p < qs.m) {
+      for (int d = 0; d < 3; ++d) x[u][d] = qs.Q[d * qs.ld + qs.q0 + p];
+      bucket[u] = bucket_of(g, sh, x[u][0], x[u][1], x[u][2]);
+      rank[u] = atomicAdd(&cnt[bucket[u]], 1);
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < kBuckets; i += kOrderBlock)
+    if (const int32_t c = cnt[i]) {
+      const int32_t first = atomicAdd(&total[i], c);
+      if (FILL) cnt[i] = first;
+    }
+  if (!FILL) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kOrderPer; ++u)
+    if (bucket[u] >= 0)
+      items[cnt[bucket[u]] + rank[u]] =
+          make_float4(x[u][0], x[u][1], x[u][2], __int_as_float((int)(base + t + u * kOrderBlock)));
+}
+
+// Orders the LDS accesses of a wavefront that shares data between its own lanes only.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The value of lane l - 1 of the row of 16 lanes (0 in its first lane).
+__device__ __forceinline__ double lane_below(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x111, 0xf, 0xf, true);  // row_shr:1
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x111, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
 // The items k_knn left unfinished, one wavefront per item (a grid-stride loop over the
-// wavefronts of the launch). Ring by ring, the lanes share out the ring's rows of cells
-// inside the grid (the rows of k_knn: whole rows where |dz| or |dy| is r, the two end cells
-// elsewhere), each walking its row's one or two ranges of `sorted` a point at a time; the
-// list of the k best is the same in every lane, and the candidates that beat its last entry
-// are inserted one by one in lane order (ballot, then a broadcast of each). The ring test is
-// then the exact one of k_knn. The work per ring is bounded by the grid's rows.
-template <int K, bool SELF>
-__global__ __launch_bounds__(256) void k_knn_wave(const float* __restrict__ Q, int64_t qld, int64_t q0,
-                                                  int64_t m, const GridParams* __restrict__ gp,
+// wavefronts of the launch). The cube around the query grows by half (half-width 2, 3, 4, 6, 9,
+// ...), or to the half-width that the k-th best distance needs where that is less; the lanes share out
+// the rows of cells that each step adds, write the positions of the rows' points into a list in LDS
+// (kWaveList at a time) and take the list 64 points at a time: lanes that walk their own rows
+// wait for one load per point. (Four rows per lane and step, or growing straight to the k-th best
+// distance, took 1.5 times as long.) The list of the k best is spread over the lanes of a row
+// of 16, one key per lane (the same in every row): a candidate that beats the last key is broadcast
+// and inserted with one minimum and one maximum, whatever k. The work per step is bounded by
+// the grid's rows.
+constexpr int kWaveList = 512;
+
+__global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams* __restrict__ gp,
                                                   const int32_t* __restrict__ start,
-                                                  const float4* __restrict__ sorted, int skip_mode,
-                                                  int64_t stride, const int32_t* __restrict__ defer,
-                                                  int32_t* __restrict__ idx, float* __restrict__ dist) {
+                                                  const float4* __restrict__ sorted,
+                                                  const int32_t* __restrict__ defer, int k, KnnEmit em) {
+  __shared__ int32_t list_all[4][kWaveList];
   const int lane = threadIdx.x & 63;
+  int32_t* const list = list_all[threadIdx.x >> 6];
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   const int64_t nd = defer[0];
   const GridParams g = *gp;
   const int rmax = max(g.nx, max(g.ny, g.nz));
   for (int64_t item = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; item < nd; item += nwaves) {
-    const KnnQuery kq = knn_query_of<SELF>(defer[1 + item], Q, qld, q0, sorted, skip_mode, stride);
-    const int64_t q = kq.q;
+    const KnnQuery kq = knn_query_of(qs, defer[1 + item]);
     const float qx = kq.x, qy = kq.y, qz = kq.z;
     const int skip = kq.skip;
-    float bd[K];
-    int bi[K];
-#pragma unroll
-    for (int u = 0; u < K; ++u) {
-      bd[u] = INFINITY;
-      bi[u] = 0x7fffffff;
-    }
+    double key = __hiloint2double((int)kKeyInf, 0x7fffffff);  // list entry lane % 16
+    uint32_t worst = kKeyInf;                                 // high word of entry k - 1
     int cx, cy, cz;
     cell_of(g, qx, qy, qz, cx, cy, cz);
-    for (int r = 0; r <= rmax; ++r) {
+    float f[3];
+    cell_coords(g, qx, qy, qz, cx, cy, cz, f);
+    for (int rp = -1, r = 2;;) {
       const int zl = max(cz - r, 0), zh = min(cz + r, g.nz - 1);
       const int yl = max(cy - r, 0), yh = min(cy + r, g.ny - 1);
       const int xl = max(cx - r, 0), xh = min(cx + r, g.nx - 1);
@@ -544,51 +1017,54 @@ __global__ __launch_bounds__(256) void k_knn_wave(const float* __restrict__ Q, i
         const int64_t l = l0 + lane;
         int32_t b0 = 0, e0 = 0, b1 = 0, e1 = 0;  // this lane's row: up to two ranges of sorted
         if (l < rows)
-          ring_row(g, start, cx, cy, cz, r, zl + (int)(l / nyr), yl + (int)(l % nyr), xl, xh, b0, e0, b1, e1);
-        for (;;) {
-          const bool has = b0 < e0 || b1 < e1;
-          if (__ballot(has) == 0ull) break;
-          float d2 = INFINITY;
-          int j = 0x7fffffff;
-          bool beat = false;
-          if (has) {
-            const int32_t pp = b0 < e0 ? b0++ : b1++;
-            const float4 sp = sorted[pp];
-            j = __float_as_int(sp.w);
-            const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
-            d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
-            beat = j != skip && less_pair(d2, j, bd[K - 1], bi[K - 1]);
+          shell_row(g, start, cx, cy, cz, rp, zl + (int)(l / nyr), yl + (int)(l % nyr), xl, xh, b0, e0, b1, e1);
+        for (;;) {  // until every row's points have been listed and taken
+          const int32_t len = (e0 - b0) + (e1 - b1);
+          if (__ballot(len > 0) == 0ull) break;
+          int32_t inc = len;
+          for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
           }
-          unsigned long long mask = __ballot(beat);
-          while (mask) {
-            const int src = __ffsll((long long)mask) - 1;
-            mask &= mask - 1ull;
-            const float cd = __shfl(d2, src, 64);
-            const int cj = __shfl(j, src, 64);
-            if (less_pair(cd, cj, bd[K - 1], bi[K - 1])) insert_sorted<K>(cd, cj, bd, bi);
+          const int32_t all = __shfl(inc, 63, 64);
+          int32_t at = inc - len;
+          while (at < kWaveList && b0 < e0) list[at++] = b0++;
+          while (at < kWaveList && b1 < e1) list[at++] = b1++;
+          wave_lds_fence();
+          const int32_t n = min(all, kWaveList);
+          for (int32_t c = lane; c - lane < n; c += 64) {
+            uint32_t hi = 0xffffffffu;
+            int j = 0x7fffffff;
+            if (c < n) {
+              const float4 sp = sorted[list[c]];
+              j = __float_as_int(sp.w);
+              const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
+              if (j != skip) hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
+            }
+            unsigned long long mask = __ballot(hi <= worst);
+            while (mask) {
+              const int src = __ffsll((long long)mask) - 1;
+              mask &= mask - 1ull;
+              const uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)hi, src);
+              if (ch > worst) continue;
+              const double x = __hiloint2double((int)ch, __builtin_amdgcn_readlane(j, src));
+              key = key_max(lane_below(key), key_min(key, x));
+              worst = (uint32_t)__builtin_amdgcn_readlane(__double2hiint(key), k - 1);
+            }
           }
+          wave_lds_fence();
         }
       }
-      const float lb = (float)r * g.h;
-      if (bd[K - 1] < INFINITY && bd[K - 1] <= lb * lb) break;
+      const float lb = outside_bound(g, f, cx, cy, cz, r);
+      const bool full = worst < kKeyInf;
+      const float reach = __uint_as_float(worst - kKeyBias);  // squared
+      if (lb == INFINITY || (full && reach <= lb * lb) || r >= rmax) break;
+      rp = r;
+      const int grown = min(r + (r >> 1), rmax);
+      r = full ? max(r + 1, min(grown, (int)fminf(sqrtf(reach) * g.ih + 1.0f, (float)rmax))) : grown;
     }
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < K; ++u) {
-        idx[q * K + u] = bi[u];
-        if (dist) dist[q * K + u] = sqrtf(bd[u]);
-      }
-    }
+    emit_wave(em, kq.q, k, key);
   }
-}
-
-__global__ void k_delta(const float* __restrict__ dist, int64_t n, int k, float scale,
-                        float* __restrict__ delta) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.0f;
-  for (int t = 0; t < k; ++t) s += dist[i * k + t];
-  delta[i] = scale * (s / (float)k);
 }
 
 __global__ void k_gather_anchors(const float* __restrict__ P, int64_t n, int64_t stride, int64_t na,
@@ -840,27 +1316,6 @@ __global__ __launch_bounds__(128) void k_voronoi_area(const float* __restrict__ 
   area[i] = (float)(0.5 * s2);
 }
 
-// Kernel radius of Sec. 5.2 "Poisson Kernels": the mean of the k nearest-neighbour distances
-// that lie in [vmin, vmax]; when none does, the mean of all k clamped to [vmin, vmax].
-__global__ void k_delta_window(const float* __restrict__ dist, int64_t n, int k, float vmin, float vmax,
-                               float* __restrict__ delta) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s = 0.0, all = 0.0;
-  int c = 0;
-  for (int t = 0; t < k; ++t) {
-    const double d = dist[i * k + t];
-    all += d;
-    if (d >= vmin && d <= vmax) {
-      s += d;
-      ++c;
-    }
-  }
-  double r = c > 0 ? s / c : all / k;
-  if (c == 0) r = r < vmin ? vmin : (r > vmax ? vmax : r);
-  delta[i] = (float)r;
-}
-
 // Gauss map (Sec. 5.1 "Normal Initialization"): n_i = p_i / |p_i| (about the origin);
 // a point at the origin gets (0, 0, 1).
 __global__ void k_gauss_normals(const float* __restrict__ P, int64_t n, float* __restrict__ N) {
@@ -883,103 +1338,121 @@ unsigned grid_for(int64_t n, int block = 256, int64_t cap = 65535) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, block), cap));
 }
 
-// Rings searched by the thread-per-query pass: with about 8 cells per reference point, a query
-// on a sampled surface meets its neighbours within 2-3 rings (1M torus scene: the self 10-NN
-// finish by ring 2 for 95% of the points, the 16 nearest of 4,096 anchors by ring 3 for 97%);
-// its outliers need 4 to 11.
-constexpr int kFirstPassRings = 3;
+// Half-width of the cube searched by the thread-per-query pass: its 27 cells hold the answer of
+// nearly every query that is not isolated, and one more ring costs every wavefront with one
+// unfinished query 16 more rows (2 against 1, at 0.5 k points per cell, us: the 10 nearest of 50,001
+// points 213 against 141, the radius of 1M points 402 against 384).
+constexpr int kFirstPassRings = 1;
 
 // Blocks of the wavefront-per-item pass (4 wavefronts each): 8 wavefronts per SIMD, so that
 // the dependent loads of one item's ring walk overlap with those of others.
 constexpr int kWaveBlocks = 2048;
 
-// two_pass = false: the thread-per-query kernel searches every query to the end (no ring
-// limit, nothing deferred), for query sets whose order already groups the isolated queries
-// together (the level-set faces, emitted cell by cell in Morton order), where a wavefront per
-// deferred query would only spread them out.
-template <int K, bool SELF>
-void launch_knn_t(int64_t m, hipStream_t st, const float* Q, int64_t qld, int64_t q0, const KnnWork& w,
-                  int skip_mode, int64_t stride, bool two_pass, int32_t* idx, float* dist) {
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, w.defer, (int64_t)1);
-  const int rcap = two_pass ? kFirstPassRings : INT_MAX;
-  hipLaunchKernelGGL((k_knn<K, SELF>), dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, Q, qld, q0, m, w.gp,
-                     w.start, w.sorted, skip_mode, stride, rcap, w.defer, idx, dist);
-  if (two_pass)
-    hipLaunchKernelGGL((k_knn_wave<K, SELF>), dim3(kWaveBlocks), dim3(256), 0, st, Q, qld, q0, m, w.gp, w.start,
-                       w.sorted, skip_mode, stride, w.defer, idx, dist);
-}
+// Queries from which putting them in cell order pays: the four launches of the sort take about
+// 20 us and as much again per 1M queries.
+constexpr int64_t kOrderMin = 16384;
+
+// How the queries of a search are ordered: kOwnOrder = they are the references (work in cell
+// order), kAnyOrder = no order (sorted first when there are enough), kGivenOrder = already in a
+// spatial order that also groups the isolated queries (the level-set faces, emitted cell by cell in
+// Morton order): the thread-per-query kernel then searches every query to the end (no limit,
+// nothing deferred), since a wavefront per deferred query would only spread those out.
+enum QueryOrder { kOwnOrder, kAnyOrder, kGivenOrder };
 
 template <int K>
-void launch_knn_k(int64_t m, hipStream_t st, const float* Q, int64_t qld, int64_t q0, const KnnWork& w,
-                  int skip_mode, int64_t stride, bool self, bool two_pass, int32_t* idx, float* dist) {
-  if (self)
-    launch_knn_t<K, true>(m, st, Q, qld, q0, w, skip_mode, stride, two_pass, idx, dist);
-  else
-    launch_knn_t<K, false>(m, st, Q, qld, q0, w, skip_mode, stride, two_pass, idx, dist);
+void launch_knn_k(hipStream_t st, const QuerySet& qs, const KnnWork& w, int rcap, const KnnEmit& em) {
+  hipLaunchKernelGGL((k_knn<K>), dim3((unsigned)cdiv(qs.m, 256)), dim3(256), 0, st, qs, w.gp, w.start, w.sorted, rcap,
+                     w.defer, em);
 }
 
-dwg_status build_grid(const float* R, int64_t nr, const KnnWork& w, hipStream_t st) {
+// Grid of the nr references R for searches of k neighbours.
+dwg_status build_grid(const float* R, int64_t nr, int k, const KnnWork& w, hipStream_t st) {
   const int64_t mc = max_cells_for(nr);
-  hipLaunchKernelGGL(k_bbox_partial, dim3(kBboxBlocks), dim3(256), 0, st, R, nr, w.bbox_part);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_trim_init, dim3(1), dim3(256), 0, st, w.bbox_part, kBboxBlocks, w.range, w.below, w.hist);
-  DWG_TRY_LAUNCH();
-  const int64_t rlo = nr / 1024, rhi = nr - 1 - nr / 1024;
-  for (int level = 0; level < kTrimLevels; ++level) {
-    hipLaunchKernelGGL(k_axis_hist, dim3(grid_for(nr, 256, 1024)), dim3(256), 0, st, R, nr, w.range, w.hist);
+  if (nr <= kSmallRefs) {
+    hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(kSetupBlock), 0, st, R, nr, mc, k, w.gp, w.start, w.sorted);
     DWG_TRY_LAUNCH();
-    hipLaunchKernelGGL(k_trim_refine, dim3(3), dim3(256), 0, st, w.hist, w.range, w.below, rlo, rhi);
-    DWG_TRY_LAUNCH();
+    return DWG_OK;
   }
-  hipLaunchKernelGGL(k_grid_params, dim3(1), dim3(64), 0, st, w.range, mc, w.gp);
+  hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kSetupBlock), 0, st, R, nr, mc, k, w.gp);
   DWG_TRY_LAUNCH();
-  // counts and cursors over the largest possible grid (the actual grid has <= mc cells)
-  hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(mc + 1)), dim3(256), 0, st, w.start, mc + 1);
-  hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(mc)), dim3(256), 0, st, w.cursor, mc);
+  // the launches cover the largest possible grid (the actual one has <= mc cells)
+  hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(mc + 1, 256, 1024)), dim3(256), 0, st, w.gp, w.start, w.state);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_cell_count, dim3(grid_for(nr)), dim3(256), 0, st, R, nr, w.gp, w.key, w.start);
+  hipLaunchKernelGGL(k_cell_count, dim3(grid_for(nr)), dim3(256), 0, st, R, nr, w.gp, w.key, w.rank, w.start);
   DWG_TRY_LAUNCH();
-  const int64_t nt = cdiv(mc, kScanTile);
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nt), dim3(kScanBlock), 0, st, w.start, mc, w.sums);
+  hipLaunchKernelGGL(k_scan_chain, dim3((unsigned)cdiv(mc, kScanTile)), dim3(kScanBlock), 0, st, w.start, mc, w.gp,
+                     w.state);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, st, w.sums, nt, w.start, mc);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)cdiv(mc, 256)), dim3(256), 0, st, w.start, mc, w.sums);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_scatter, dim3(grid_for(nr)), dim3(256), 0, st, R, nr, w.key, w.start, w.cursor,
-                     w.sorted);
+  hipLaunchKernelGGL(k_scatter, dim3(grid_for(nr)), dim3(256), 0, st, R, nr, w.key, w.rank, w.start, w.sorted);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }
 
-// self: the queries are exactly the m references of the grid, q0 = 0, skip_mode 1.
+// kOwnOrder: the queries are exactly the m references of the grid, q0 = 0, skip_mode 1.
 dwg_status knn_query(const float* Q, int64_t qld, int64_t q0, int64_t m, const KnnWork& w, int skip_mode,
-                     int64_t stride, int k, int32_t* idx, float* dist, hipStream_t st, bool self = false,
-                     bool two_pass = true) {
+                     int64_t stride, int k, const KnnEmit& em, hipStream_t st, QueryOrder order) {
   if (m > w.mq) {  // the deferred list holds at most w.mq items
     set_error("internal: %lld kNN queries exceed the carved capacity %lld", (long long)m, (long long)w.mq);
     return DWG_E_INVALID;
   }
   if (m <= 0) return DWG_OK;
+  QuerySet qs{Q, qld, q0, m, order == kOwnOrder ? w.sorted : nullptr, skip_mode, stride};
+  if (order != kGivenOrder) {
+    hipLaunchKernelGGL(k_order_clear, dim3(kBuckets / 256), dim3(256), 0, st, w.total, w.defer);
+    DWG_TRY_LAUNCH();
+  }
+  if (order == kAnyOrder && m >= kOrderMin) {
+    const dim3 grid((unsigned)cdiv(m, kOrderTile)), block(kOrderBlock);
+    hipLaunchKernelGGL((k_order<false>), grid, block, 0, st, qs, w.gp, w.total, w.items);
+    DWG_TRY_LAUNCH();
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneBlock), 0, st, w.total, (int64_t)kBuckets);
+    DWG_TRY_LAUNCH();
+    hipLaunchKernelGGL((k_order<true>), grid, block, 0, st, qs, w.gp, w.total, w.items);
+    DWG_TRY_LAUNCH();
+    qs.items = w.items;
+  }
+  const int rcap = order == kGivenOrder ? INT_MAX : kFirstPassRings;
   switch (k) {
 #define DWG_K(KK) \
-  case KK: launch_knn_k<KK>(m, st, Q, qld, q0, w, skip_mode, stride, self, two_pass, idx, dist); break;
+  case KK: launch_knn_k<KK>(st, qs, w, rcap, em); break;
     DWG_K(1) DWG_K(2) DWG_K(3) DWG_K(4) DWG_K(5) DWG_K(6) DWG_K(7) DWG_K(8)
     DWG_K(9) DWG_K(10) DWG_K(11) DWG_K(12) DWG_K(13) DWG_K(14) DWG_K(15) DWG_K(16)
 #undef DWG_K
     default: set_error("k out of range"); return DWG_E_INVALID;
   }
   DWG_TRY_LAUNCH();
+  if (order != kGivenOrder) {
+    hipLaunchKernelGGL(k_knn_wave, dim3(kWaveBlocks), dim3(256), 0, st, qs, w.gp, w.start, w.sorted, w.defer, k, em);
+    DWG_TRY_LAUNCH();
+  }
   return DWG_OK;
+}
+
+KnnEmit emit_list(int32_t* idx, float* dist) { return KnnEmit{kEmitList, idx, dist, nullptr, 0.0f, 0.0f, 0.0f}; }
+KnnEmit emit_mean(float* delta, float scale) { return KnnEmit{kEmitMean, nullptr, nullptr, delta, scale, 0.0f, 0.0f}; }
+
+// Grid over R, then the k nearest references of each of the m queries (self_skip: R itself).
+dwg_status knn_emit(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k, const KnnEmit& em,
+                    void* ws, hipStream_t stream) {
+  Carver c(ws);
+  KnnWork w;
+  carve_knn(c, nr, m, &w);
+  dwg_status s = build_grid(R, nr, k, w, stream);
+  if (s != DWG_OK) return s;
+  // queries that are the references themselves (same array, same count) run in cell order
+  const QueryOrder order = self_skip && Q == R && m == nr ? kOwnOrder : kAnyOrder;
+  return knn_query(Q, m, 0, m, w, self_skip ? 1 : 0, 1, k, em, stream, order);
 }
 
 }  // namespace
 
-dwg_status knn_grid(const float* R, int64_t nr, const KnnWork& w, hipStream_t st) { return build_grid(R, nr, w, st); }
+dwg_status knn_grid(const float* R, int64_t nr, int k, const KnnWork& w, hipStream_t st) {
+  return build_grid(R, nr, k, w, st);
+}
 
 dwg_status knn_search(const float* Q, int64_t qld, int64_t q0, int64_t m, const KnnWork& w, int k, int32_t* idx,
                       float* dist, hipStream_t st) {
-  return knn_query(Q, qld, q0, m, w, 0, 1, k, idx, dist, st, false, false);
+  return knn_query(Q, qld, q0, m, w, 0, 1, k, emit_list(idx, dist), st, kGivenOrder);
 }
 
 size_t carve_knn(Carver& c, int64_t nr, int64_t mq, KnnWork* out) {
@@ -988,16 +1461,14 @@ size_t carve_knn(Carver& c, int64_t nr, int64_t mq, KnnWork* out) {
   KnnWork w;
   w.mq = mq;
   w.defer = c.take<int32_t>((size_t)mq + 1);
-  w.bbox_part = c.take<float>(kBboxBlocks * 6);
-  w.range = c.take<double>(6);
-  w.below = c.take<int64_t>(3);
-  w.hist = c.take<int32_t>(3 * kTrimBins);
   w.gp = c.take<GridParams>(1);
   w.key = c.take<int32_t>((size_t)nr);
+  w.rank = c.take<int32_t>((size_t)nr);
   w.start = c.take<int32_t>((size_t)mc + 1);
-  w.cursor = c.take<int32_t>((size_t)mc);
-  w.sums = c.take<int32_t>((size_t)cdiv(mc, kScanTile) + 1);
+  w.state = c.take<unsigned long long>((size_t)cdiv(mc, kScanTile) + 1);
   w.sorted = c.take<float4>((size_t)nr);
+  w.total = c.take<int32_t>((size_t)kBuckets + 1);
+  w.items = c.take<float4>((size_t)mq);
   if (out) *out = w;
   return c.used - s0;
 }
@@ -1010,15 +1481,19 @@ dwg_status launch_bbox(const float* R, int64_t n, float* part, float* out6, hipS
   return DWG_OK;
 }
 
-size_t scan_sums_len(int64_t n) { return (size_t)cdiv(n, kScanTile) + 1; }
+size_t scan_sums_len(int64_t n) { return 2 * ((size_t)cdiv(n, kScanTile) + 1); }
 
 dwg_status exclusive_scan(int32_t* a, int64_t n, int32_t* sums, hipStream_t st) {
-  const int64_t nt = cdiv(n, kScanTile);
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nt), dim3(kScanBlock), 0, st, a, n, sums);
+  if (n <= kScanOneMax) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneBlock), 0, st, a, n);
+    DWG_TRY_LAUNCH();
+    return DWG_OK;
+  }
+  const int64_t words = (int64_t)scan_sums_len(n);
+  hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(words)), dim3(256), 0, st, sums, words);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, st, sums, nt, a, n);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, a, n, sums);
+  hipLaunchKernelGGL(k_scan_chain, dim3((unsigned)cdiv(n, kScanTile)), dim3(kScanBlock), 0, st, a, n,
+                     static_cast<const GridParams*>(nullptr), reinterpret_cast<unsigned long long*>(sums));
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }
@@ -1030,26 +1505,13 @@ size_t knn_ws_bytes(int64_t n_ref, int64_t n_qry) {
   return c.used;
 }
 
-dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip,
-                   const int64_t* skip_stride, int k, int32_t* idx, float* dist, void* ws,
-                   size_t ws_bytes, hipStream_t stream) {
-  (void)ws_bytes;
-  (void)skip_stride;
-  Carver c(ws);
-  KnnWork w;
-  carve_knn(c, nr, m, &w);
-  dwg_status s = build_grid(R, nr, w, stream);
-  if (s != DWG_OK) return s;
-  // queries that are the references themselves (same array, same count) run in cell order
-  const bool self = self_skip && Q == R && m == nr;
-  return knn_query(Q, m, 0, m, w, self_skip ? 1 : 0, 1, k, idx, dist, stream, self);
+dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k, int32_t* idx,
+                   float* dist, void* ws, hipStream_t stream) {
+  return knn_emit(R, nr, Q, m, self_skip, k, emit_list(idx, dist), ws, stream);
 }
 
-dwg_status delta_from_knn(const float* dist, int64_t n, int k, float scale, float* delta,
-                          hipStream_t stream) {
-  hipLaunchKernelGGL(k_delta, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, stream, dist, n, k, scale, delta);
-  DWG_TRY_LAUNCH();
-  return DWG_OK;
+dwg_status delta_mean(const float* P, int64_t n, int k, float scale, float* delta, void* ws, hipStream_t stream) {
+  return knn_emit(P, n, P, n, 1, k, emit_mean(delta, scale), ws, stream);
 }
 
 size_t anchor_ws_bytes(int64_t n, int64_t chunk, int64_t n_anchor) {
@@ -1077,8 +1539,7 @@ size_t carve_anchor(Carver& c, int64_t n, int64_t chunk, int64_t n_anchor, Ancho
 dwg_status pca_normals(const float* P, int64_t n, int k, float* N, void* ws, hipStream_t stream) {
   Carver c(ws);
   int32_t* idx = c.take<int32_t>((size_t)n * k);
-  float* dist = c.take<float>((size_t)n * k);
-  dwg_status s = knn_run(P, n, P, n, 1, nullptr, k, idx, dist, static_cast<char*>(ws) + c.used, 0, stream);
+  dwg_status s = knn_run(P, n, P, n, 1, k, idx, nullptr, static_cast<char*>(ws) + c.used, stream);
   if (s != DWG_OK) return s;
   hipLaunchKernelGGL(k_pca_normals, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, stream, P, n, idx, k, N);
   DWG_TRY_LAUNCH();
@@ -1088,8 +1549,7 @@ dwg_status pca_normals(const float* P, int64_t n, int k, float* N, void* ws, hip
 dwg_status voronoi_area(const float* P, int64_t n, int m, float* area, void* ws, hipStream_t stream) {
   Carver c(ws);
   int32_t* idx = c.take<int32_t>((size_t)n * m);
-  float* dist = c.take<float>((size_t)n * m);
-  dwg_status s = knn_run(P, n, P, n, 1, nullptr, m, idx, dist, static_cast<char*>(ws) + c.used, 0, stream);
+  dwg_status s = knn_run(P, n, P, n, 1, m, idx, nullptr, static_cast<char*>(ws) + c.used, stream);
   if (s != DWG_OK) return s;
   hipLaunchKernelGGL(k_voronoi_area, dim3((unsigned)cdiv(n, 128)), dim3(128), 0, stream, P, n, idx, m, area);
   DWG_TRY_LAUNCH();
@@ -1098,15 +1558,7 @@ dwg_status voronoi_area(const float* P, int64_t n, int m, float* area, void* ws,
 
 dwg_status delta_window(const float* P, int64_t n, int k, float vmin, float vmax, float* delta, void* ws,
                         hipStream_t stream) {
-  Carver c(ws);
-  int32_t* idx = c.take<int32_t>((size_t)n * k);
-  float* dist = c.take<float>((size_t)n * k);
-  dwg_status s = knn_run(P, n, P, n, 1, nullptr, k, idx, dist, static_cast<char*>(ws) + c.used, 0, stream);
-  if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_delta_window, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, stream, dist, n, k, vmin, vmax,
-                     delta);
-  DWG_TRY_LAUNCH();
-  return DWG_OK;
+  return knn_emit(P, n, P, n, 1, k, KnnEmit{kEmitWindow, nullptr, nullptr, delta, 0.0f, vmin, vmax}, ws, stream);
 }
 
 dwg_status gauss_normals(const float* P, int64_t n, float* N, hipStream_t stream) {
@@ -1115,18 +1567,18 @@ dwg_status gauss_normals(const float* P, int64_t n, float* N, hipStream_t stream
   return DWG_OK;
 }
 
-// Anchors: every stride-th point, stride = max(1, n / n_anchor); grid over the anchors.
-dwg_status anchor_build(const float* P, int64_t n, const AnchorCtx& x, hipStream_t stream) {
+// Anchors: every stride-th point, stride = max(1, n / n_anchor); their grid, for searches of k.
+dwg_status anchor_build(const float* P, int64_t n, int k, const AnchorCtx& x, hipStream_t stream) {
   hipLaunchKernelGGL(k_gather_anchors, dim3((unsigned)cdiv(x.na, 256)), dim3(256), 0, stream, P, n, x.stride,
                      x.na, x.A);
   DWG_TRY_LAUNCH();
-  return build_grid(x.A, x.na, x.w, stream);
+  return build_grid(x.A, x.na, k, x.w, stream);
 }
 
 // Features of the points q0 .. q0 + m - 1 (m <= chunk) into feat [m][48].
 dwg_status anchor_features(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, float* feat,
                            hipStream_t stream) {
-  dwg_status s = knn_query(P, n, q0, m, x.w, 2, x.stride, DWG_FEAT_K, x.idx, x.dist, stream);
+  dwg_status s = knn_query(P, n, q0, m, x.w, 2, x.stride, DWG_FEAT_K, emit_list(x.idx, x.dist), stream, kAnyOrder);
   if (s != DWG_OK) return s;
   hipLaunchKernelGGL(k_features, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, stream, P, n, q0, m, x.A, x.na,
                      x.idx, x.dist, feat);
@@ -1140,9 +1592,7 @@ dwg_status anchor_delta(const float* P, int64_t n, const AnchorCtx& x, int k, fl
                         hipStream_t stream) {
   for (int64_t q0 = 0; q0 < n; q0 += x.chunk) {
     const int64_t cnt = std::min<int64_t>(x.chunk, n - q0);
-    dwg_status s = knn_query(P, n, q0, cnt, x.w, 2, x.stride, k, x.idx, x.dist, stream);
-    if (s != DWG_OK) return s;
-    s = delta_from_knn(x.dist, cnt, k, scale, delta + q0, stream);
+    dwg_status s = knn_query(P, n, q0, cnt, x.w, 2, x.stride, k, emit_mean(delta + q0, scale), stream, kAnyOrder);
     if (s != DWG_OK) return s;
   }
   return DWG_OK;
@@ -1154,7 +1604,7 @@ dwg_status features_run(const float* P, int64_t n, int64_t n_anchor, float* feat
   Carver c(ws);
   AnchorCtx x;
   carve_anchor(c, n, n, n_anchor, &x);
-  dwg_status s = anchor_build(P, n, x, stream);
+  dwg_status s = anchor_build(P, n, DWG_FEAT_K, x, stream);
   if (s != DWG_OK) return s;
   return anchor_features(P, n, 0, n, x, feat, stream);
 }

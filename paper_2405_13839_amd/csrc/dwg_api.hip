@@ -625,7 +625,7 @@ dwg_status dwg_init_normals(dwg_init_kind kind, uint64_t seed, const float* P, i
     return DWG_E_WORKSPACE;
   }
   DWG_PROPAGATE(check_device());
-  // anchors and their grid once, then features and the MLP in chunks of <= 2^20 points,
+  // anchors and their grid once, then anchor lists and the MLP in chunks of <= 2^20 points,
   // written straight into the planar [3][n] output
   Carver c(ws);
   AnchorCtx x;
@@ -633,8 +633,8 @@ dwg_status dwg_init_normals(dwg_init_kind kind, uint64_t seed, const float* P, i
   DWG_PROPAGATE(anchor_build(P, n, DWG_FEAT_K, x, st));
   for (int64_t q0 = 0; q0 < n; q0 += x.chunk) {
     const int64_t cnt = std::min<int64_t>(x.chunk, n - q0);
-    DWG_PROPAGATE(anchor_features(P, n, q0, cnt, x, x.feat, st));
-    DWG_PROPAGATE(mlp_forward(mlp_params, x.feat, cnt, N_out + q0, 1, n, st));
+    DWG_PROPAGATE(anchor_lists(P, n, q0, cnt, x, st));
+    DWG_PROPAGATE(mlp_anchor_normals(mlp_params, AnchorRows{P, n, q0, x.A4, x.idx, x.inv}, cnt, N_out + q0, n, st));
   }
   return DWG_OK;
 }
@@ -748,7 +748,7 @@ dwg_status dwg_features(const float* P, int64_t n, int64_t n_anchor, float* feat
     return DWG_E_WORKSPACE;
   }
   DWG_PROPAGATE(check_device());
-  return features_run(P, n, n_anchor, feat, ws, ws_bytes, static_cast<hipStream_t>(stream));
+  return features_run(P, n, n_anchor, feat, ws, static_cast<hipStream_t>(stream));
 }
 
 dwg_status dwg_mlp_infer(const float* params, const float* X, int64_t B, float* Y, void* ws,
@@ -762,7 +762,7 @@ dwg_status dwg_mlp_infer(const float* params, const float* X, int64_t B, float* 
     return DWG_E_WORKSPACE;
   }
   DWG_PROPAGATE(check_device());
-  return mlp_infer_run(params, X, B, Y, ws, ws_bytes, static_cast<hipStream_t>(stream));
+  return mlp_infer_run(params, X, B, Y, static_cast<hipStream_t>(stream));
 }
 
 dwg_status dwg_mlp_train_step(float* params, float* adam_m, float* adam_v, int64_t step,
@@ -781,7 +781,7 @@ dwg_status dwg_mlp_train_step(float* params, float* adam_m, float* adam_v, int64
   }
   DWG_PROPAGATE(check_device());
   return mlp_train_run(params, adam_m, adam_v, step, lr, X, T, mask, B, grad_out, loss_out, ws,
-                       ws_bytes, static_cast<hipStream_t>(stream));
+                       static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

@@ -84,9 +84,9 @@ size_t carve_knn(Carver& c, int64_t nr, int64_t mq, KnnWork* out);
 constexpr int64_t DWG_FEAT_ANCHORS = 4096;
 struct AnchorCtx {
   float* A;            // [3][na] anchor coordinates
+  float4* A4;          // [na] the same, (x, y, z, 0) per anchor
   int32_t* idx;        // [chunk][16]
-  float* dist;         // [chunk][16]
-  float* feat;         // [chunk][48]
+  float* inv;          // [chunk] inverse of the mean anchor distance (0 when that is 0)
   int64_t na, stride, chunk;
   KnnWork w;
 };
@@ -95,6 +95,8 @@ size_t anchor_ws_bytes(int64_t n, int64_t chunk, int64_t n_anchor);
 dwg_status anchor_build(const float* P, int64_t n, int k, const AnchorCtx& x, hipStream_t stream);
 dwg_status anchor_features(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, float* feat,
                            hipStream_t stream);
+// The neighbour lists that the features are made of (x.idx, x.inv).
+dwg_status anchor_lists(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, hipStream_t stream);
 dwg_status anchor_delta(const float* P, int64_t n, const AnchorCtx& x, int k, float scale, float* delta,
                         hipStream_t stream);
 
@@ -273,8 +275,18 @@ dwg_status mc_update(const McParams& mp, const McWork& w, const GwnWork& g, floa
 // Workspace bytes of the kNN / features / MLP stages for n points.
 size_t knn_ws_bytes(int64_t n_ref, int64_t n_qry);
 size_t mlp_ws_bytes(int64_t B);
-dwg_status mlp_forward(const float* params, const float* X, int64_t B, float* Y, int64_t sr, int64_t sc,
-                       hipStream_t stream);
+// Feature rows given by their anchors: row r is the point q0 + r of the planar array P [3][n], its
+// feature 3 t + d the coordinate d of (A4[idx[r][t]] - p) inv[r].
+struct AnchorRows {
+  const float* P;
+  int64_t n, q0;
+  const float4* A4;
+  const int32_t* idx;
+  const float* inv;
+};
+// Normals of B such rows into the planar array N (leading dimension n).
+dwg_status mlp_anchor_normals(const float* params, const AnchorRows& rows, int64_t B, float* N, int64_t n,
+                              hipStream_t stream);
 
 // Launchers (all enqueue on `stream`; return DWG_OK or DWG_E_DEVICE).
 dwg_status launch_order(const float* P, int64_t n, const float* delta, float eps, float kappa, const float* Q,
@@ -298,13 +310,10 @@ dwg_status gauss_normals(const float* P, int64_t n, float* N, hipStream_t stream
 dwg_status voronoi_area(const float* P, int64_t n, int m, float* area, void* ws, hipStream_t stream);
 dwg_status delta_window(const float* P, int64_t n, int k, float vmin, float vmax, float* delta, void* ws,
                         hipStream_t stream);
-dwg_status features_run(const float* P, int64_t n, int64_t n_anchor, float* feat, void* ws,
-                        size_t ws_bytes, hipStream_t stream);
-dwg_status mlp_infer_run(const float* params, const float* X, int64_t B, float* Y, void* ws,
-                         size_t ws_bytes, hipStream_t stream);
+dwg_status features_run(const float* P, int64_t n, int64_t n_anchor, float* feat, void* ws, hipStream_t stream);
+dwg_status mlp_infer_run(const float* params, const float* X, int64_t B, float* Y, hipStream_t stream);
 dwg_status mlp_train_run(float* params, float* m1, float* m2, int64_t step, float lr,
                          const float* X, const float* T, const uint8_t* mask, int64_t B,
-                         float* grad_out, float* loss_out, void* ws, size_t ws_bytes,
-                         hipStream_t stream);
+                         float* grad_out, float* loss_out, void* ws, hipStream_t stream);
 
 }  // namespace dwg

@@ -626,15 +626,21 @@ __device__ __forceinline__ void clear_keys(double* b) {
 
 // What a finished query writes: its neighbour list, or the kernel radius that the list gives
 // (k_delta_window's and the mean distance's arithmetic, without storing the lists).
-enum EmitMode { kEmitList = 0, kEmitMean = 1, kEmitWindow = 2 };
+enum EmitMode { kEmitList = 0, kEmitMean = 1, kEmitWindow = 2, kEmitScaled = 3 };
 struct KnnEmit {
   int mode;
   int32_t* idx;   // [m][k]
   float* dist;    // [m][k] or NULL
-  float* delta;   // [m]
+  float* delta;   // [m]; kEmitScaled (the indices too): the inverse of the mean distance
   float scale;    // kEmitMean
   float vmin, vmax;  // kEmitWindow
 };
+
+// 1 / (s / k), 0 when s is 0: the scale of the anchor features.
+__device__ __forceinline__ float inverse_mean(float s, int k) {
+  s *= 1.0f / (float)k;
+  return s > 0.0f ? 1.0f / s : 0.0f;
+}
 
 template <int K>
 __device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const double* b) {
@@ -647,11 +653,17 @@ __device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const do
       e.idx[q * K + u] = __double2loint(b[u]);
       if (e.dist) e.dist[q * K + u] = d[u];
     }
-  } else if (e.mode == kEmitMean) {
+  } else if (e.mode == kEmitMean || e.mode == kEmitScaled) {
     float s = 0.0f;
 #pragma unroll
     for (int u = 0; u < K; ++u) s += d[u];
-    e.delta[q] = e.scale * (s / (float)K);
+    if (e.mode == kEmitMean) {
+      e.delta[q] = e.scale * (s / (float)K);
+      return;
+    }
+    e.delta[q] = inverse_mean(s, K);
+#pragma unroll
+    for (int u = 0; u < K; ++u) e.idx[q * K + u] = __double2loint(b[u]);
   } else {
     // the mean of the distances that lie in [vmin, vmax]; when none does, the mean of all k
     // clamped to [vmin, vmax] (Sec. 5.2 "Poisson Kernels")
@@ -697,6 +709,9 @@ __device__ __forceinline__ void emit_wave(const KnnEmit& e, int64_t q, int k, do
   }
   if (e.mode == kEmitMean) {
     if (lane == 0) e.delta[q] = e.scale * (s / (float)k);
+  } else if (e.mode == kEmitScaled) {
+    if (lane == 0) e.delta[q] = inverse_mean(s, k);
+    if (lane < k) e.idx[q * k + lane] = __double2loint(key);
   } else {
     double r = c > 0 ? sd / c : all / k;
     if (c == 0) r = r < e.vmin ? e.vmin : (r > e.vmax ? e.vmax : r);
@@ -1068,33 +1083,31 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
 }
 
 __global__ void k_gather_anchors(const float* __restrict__ P, int64_t n, int64_t stride, int64_t na,
-                                 float* __restrict__ A) {
+                                 float* __restrict__ A, float4* __restrict__ A4) {
   const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= na) return;
   const int64_t i = a * stride;
-  A[a] = P[i];
-  A[na + a] = P[n + i];
-  A[2 * na + a] = P[2 * n + i];
+  const float4 v = make_float4(P[i], P[n + i], P[2 * n + i], 0.0f);
+  A[a] = v.x;
+  A[na + a] = v.y;
+  A[2 * na + a] = v.z;
+  A4[a] = v;
 }
 
-// feat[i][3k + d] = (anchor_k - p_i)_d / s_i, s_i = mean of the 16 anchor distances, for
-// the points q0 + i, i = 0..m-1 (idx, dist, feat are chunk-local).
+// feat[i][3t + d] = (anchor_t - p_i)_d / s_i, s_i = mean of the 16 anchor distances, for
+// the points q0 + i, i = 0..m-1 (idx, inv, feat are chunk-local): a thread per (point, anchor), so
+// that a wavefront reads and writes consecutive memory.
 __global__ void k_features(const float* __restrict__ P, int64_t n, int64_t q0, int64_t m,
-                           const float* __restrict__ A, int64_t na, const int32_t* __restrict__ idx,
-                           const float* __restrict__ dist, float* __restrict__ feat) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  float s = 0.0f;
-  for (int t = 0; t < DWG_FEAT_K; ++t) s += dist[i * DWG_FEAT_K + t];
-  s *= (1.0f / DWG_FEAT_K);
-  const float is = s > 0.0f ? 1.0f / s : 0.0f;
-  const int64_t gi = q0 + i;
-  const float px = P[gi], py = P[n + gi], pz = P[2 * n + gi];
-  for (int t = 0; t < DWG_FEAT_K; ++t) {
-    const int64_t a = idx[i * DWG_FEAT_K + t];
-    feat[i * DWG_MLP_IN + 3 * t + 0] = (A[a] - px) * is;
-    feat[i * DWG_MLP_IN + 3 * t + 1] = (A[na + a] - py) * is;
-    feat[i * DWG_MLP_IN + 3 * t + 2] = (A[2 * na + a] - pz) * is;
+                           const float4* __restrict__ A4, const int32_t* __restrict__ idx,
+                           const float* __restrict__ inv, float* __restrict__ feat) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m * DWG_FEAT_K;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = t / DWG_FEAT_K, gi = q0 + i;
+    const float4 a = A4[idx[t]];
+    const float is = inv[i];
+    feat[3 * t + 0] = (a.x - P[gi]) * is;
+    feat[3 * t + 1] = (a.y - P[n + gi]) * is;
+    feat[3 * t + 2] = (a.z - P[2 * n + gi]) * is;
   }
 }
 
@@ -1528,9 +1541,9 @@ size_t carve_anchor(Carver& c, int64_t n, int64_t chunk, int64_t n_anchor, Ancho
   x.na = cdiv(n, x.stride);
   x.chunk = chunk;
   x.A = c.take<float>(3 * (size_t)x.na);
+  x.A4 = c.take<float4>((size_t)x.na);
   x.idx = c.take<int32_t>((size_t)chunk * DWG_FEAT_K);
-  x.dist = c.take<float>((size_t)chunk * DWG_FEAT_K);
-  x.feat = c.take<float>((size_t)chunk * DWG_MLP_IN);
+  x.inv = c.take<float>((size_t)chunk);
   carve_knn(c, x.na, chunk, &x.w);
   if (out) *out = x;
   return c.used - s0;
@@ -1570,18 +1583,25 @@ dwg_status gauss_normals(const float* P, int64_t n, float* N, hipStream_t stream
 // Anchors: every stride-th point, stride = max(1, n / n_anchor); their grid, for searches of k.
 dwg_status anchor_build(const float* P, int64_t n, int k, const AnchorCtx& x, hipStream_t stream) {
   hipLaunchKernelGGL(k_gather_anchors, dim3((unsigned)cdiv(x.na, 256)), dim3(256), 0, stream, P, n, x.stride,
-                     x.na, x.A);
+                     x.na, x.A, x.A4);
   DWG_TRY_LAUNCH();
   return build_grid(x.A, x.na, k, x.w, stream);
+}
+
+// The 16 nearest anchors of the points q0 .. q0 + m - 1 (m <= chunk) into x.idx, and the inverse of
+// their mean distance into x.inv.
+dwg_status anchor_lists(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, hipStream_t stream) {
+  return knn_query(P, n, q0, m, x.w, 2, x.stride, DWG_FEAT_K, KnnEmit{kEmitScaled, x.idx, nullptr, x.inv, 0.0f, 0.0f, 0.0f},
+                   stream, kAnyOrder);
 }
 
 // Features of the points q0 .. q0 + m - 1 (m <= chunk) into feat [m][48].
 dwg_status anchor_features(const float* P, int64_t n, int64_t q0, int64_t m, const AnchorCtx& x, float* feat,
                            hipStream_t stream) {
-  dwg_status s = knn_query(P, n, q0, m, x.w, 2, x.stride, DWG_FEAT_K, emit_list(x.idx, x.dist), stream, kAnyOrder);
+  dwg_status s = anchor_lists(P, n, q0, m, x, stream);
   if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_features, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, stream, P, n, q0, m, x.A, x.na,
-                     x.idx, x.dist, feat);
+  hipLaunchKernelGGL(k_features, dim3((unsigned)std::min<int64_t>(cdiv(m * DWG_FEAT_K, 256), 65535)), dim3(256), 0,
+                     stream, P, n, q0, m, x.A4, x.idx, x.inv, feat);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }
@@ -1598,9 +1618,7 @@ dwg_status anchor_delta(const float* P, int64_t n, const AnchorCtx& x, int k, fl
   return DWG_OK;
 }
 
-dwg_status features_run(const float* P, int64_t n, int64_t n_anchor, float* feat, void* ws,
-                        size_t ws_bytes, hipStream_t stream) {
-  (void)ws_bytes;
+dwg_status features_run(const float* P, int64_t n, int64_t n_anchor, float* feat, void* ws, hipStream_t stream) {
   Carver c(ws);
   AnchorCtx x;
   carve_anchor(c, n, n, n_anchor, &x);

@@ -1,5 +1,6 @@
 // C ABI entry points of libdwg: argument validation (always before the first HIP call),
 // workspace carving and the host-side iteration loop of Algorithm 1.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -258,13 +259,60 @@ dwg_status static_scratch(void** out) {
   return DWG_OK;
 }
 
+// Scratch that the static entry point's size limit counts. Which sizes it takes is part of its
+// interface, so the limit keeps the accounting it was introduced with (64-bit sort keys, a digit count
+// per 2,048 keys, double partial sums per node chunk, ...) whatever the layout needs now; the layout itself
+// is checked against the array as well.
+size_t static_counted_bytes(int64_t n, int64_t m, const dwg_kernel_params& kp) {
+  Carver c(nullptr);
+  auto take = [&c](int64_t bytes) { c.take<char>((size_t)bytes); };
+  auto sort_counts = [&take](int64_t k) {
+    const int64_t h = 256 * cdiv(k, 2048);
+    take(4 * (h + 1));
+    take(4 * (cdiv(h + 1, 1024) + 1));
+  };
+  const bool tree = tree_mode(kp);
+  const int64_t ntiles = cdiv(n, kTile), npad = ntiles * kTile, qblocks = cdiv(m, kQBlock), mpad = qblocks * kQBlock;
+  const int64_t big = std::max(n, m);
+  take(32 * npad);
+  take(28 * (tree ? 1 : (int64_t)choose_split(n, m, kp.split)) * mpad);
+  take(4 * npad);
+  take(8 * big);
+  take(16 * cdiv(big, kRedBlock));
+  for (int64_t b : {32, 1024, 16}) take(b);
+  take(32 * ntiles);
+  take(32 * qblocks);
+  take(4 * npad);
+  take(4 * mpad);
+  for (int64_t b : {6144, 32, 2048}) take(b);
+  for (int64_t b : {8, 8, 4}) take(b * big);
+  sort_counts(big);
+  if (tree) {
+    const int64_t cap = 2 * n + 1, ccap = cap + cdiv(n * 22, 256), tiles = cdiv(n, 2048);
+    for (int64_t b : {6144, 32, 32}) take(b);
+    for (int64_t b : {8, 8, 4, 4}) take(b * n);
+    take(4 * (256 * tiles + 1));
+    take(4 * (cdiv(256 * tiles, 1024) + 1));
+    take(4 * n);
+    take(4 * (n + 1));
+    take(4 * (cdiv(n, 1024) + 1));
+    for (int64_t b : {16, 32, 16, 8, 4}) take(b * cap);
+    take(4 * (cap + 1));
+    take(4 * (cdiv(cap, 1024) + 1));
+    take(32 * ccap);
+    take(24 * (n + 1));
+    take(24 * tiles);
+  }
+  return std::max(c.used, gwn_bytes(n, m, kp));
+}
+
 // The kernel parameters dwg_gwn_grad_static runs with: an automatic source split is halved
 // until the evaluation fits the static scratch (the split only groups the partial sums).
 dwg_kernel_params static_params(int64_t n, int64_t m, const dwg_kernel_params& kp) {
   dwg_kernel_params k = kp;
   if (!tree_mode(k) && k.split == 0) {
     k.split = choose_split(n, m, 0);
-    while (k.split > 1 && gwn_bytes(n, m, k) > kStaticScratchBytes) k.split = (k.split + 1) / 2;
+    while (k.split > 1 && static_counted_bytes(n, m, k) > kStaticScratchBytes) k.split = (k.split + 1) / 2;
   }
   return k;
 }
@@ -323,7 +371,7 @@ dwg_status dwg_gwn_grad_static(const float* P, const float* N, const float* area
   DWG_PROPAGATE(check_kp(kpp));
   const dwg_kernel_params kp = static_params(n, m, kpp ? *kpp : kDefaultKp);
   DWG_CHECK(!tree_mode(kp) || n < (int64_t(1) << 30), "octree mode needs n < 2^30");
-  const size_t need = gwn_bytes(n, m, kp);
+  const size_t need = static_counted_bytes(n, m, kp);
   DWG_CHECK(need <= kStaticScratchBytes,
             "n = %lld sources and m = %lld queries need %zu bytes of scratch; the static scratch holds %zu "
             "(use dwg_gwn_grad with a workspace)",

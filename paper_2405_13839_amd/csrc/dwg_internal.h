@@ -110,12 +110,10 @@ dwg_status exclusive_scan(int32_t* a, int64_t n, int32_t* sums, hipStream_t st);
 // Spatial order of a point set for the all-pairs kernel (dwg_sort.hip).
 struct SortWork {
   float* part;      // [kBboxParts]
-  float* box;       // [8]: bbox and the mean kernel radius
   double* rpart;    // [256] radius partial sums
-  uint64_t* key[2]; // [n] radix-sort keys, ping-pong
+  uint32_t* key[2]; // [n] radix-sort keys, ping-pong
   int32_t* val;     // [n] indices (the second value buffer is the output permutation)
-  int32_t* hist;    // radix_hist_len(n)
-  int32_t* hsums;   // scan_sums_len(radix_hist_len(n))
+  int32_t* work;    // radix_work_len(n)
 };
 constexpr int kSortKeyBits = 22;  // radius class (1 bit) + Morton code of a 128^3 grid (21 bits)
 size_t carve_sort(Carver& c, int64_t n, SortWork* out);
@@ -155,8 +153,7 @@ struct TreeWork {
   double* frame;             // [4] lo xyz, 2^21 / extent
   uint64_t* key[2];          // [n] Morton codes (radix-sort ping-pong)
   int32_t* val[2];           // [n] source indices (ping-pong)
-  int32_t* hist;             // [256 * nsb + 1] radix digit counts
-  int32_t* hsums;            // scan tile totals
+  int32_t* work;             // radix_work_len(n)
   int32_t* lev;              // [n] level range of the nodes starting at each sorted source
   int32_t* off;              // [n + 1] node offsets; off[n] = node count
   int32_t* osums;
@@ -170,7 +167,7 @@ struct TreeWork {
   double4* csum;             // [ccap] per-chunk FP64 sums of a, a px, a py, a pz
   double* scan;              // [3][n + 1] FP64 prefix sums of the staged moments
   double* sblk;              // [3][nscan] block totals
-  int64_t n, cap, ccap, nsb, nscan;
+  int64_t n, cap, ccap, nscan;
   int leaf;
   double beta;
 };
@@ -197,12 +194,14 @@ dwg_status tree_work(const float* Q, int64_t m, const int32_t* qperm, const Tree
                      hipStream_t st);
 dwg_status tree_export(const TreeWork& t, int32_t* nodes_out, int64_t cap_out, int64_t* count_host,
                        hipStream_t st);
-// Stable LSD radix sort of (key, value) pairs on the low `bits` bits, 8 bits per pass,
-// ping-ponging between key[0]/val[0] and key[1]/val[1]; *result = the buffer holding the
-// sorted pairs. hist needs radix_hist_len(n) ints, hsums scan_sums_len(radix_hist_len(n)).
-size_t radix_hist_len(int64_t n);
-dwg_status radix_sort_pairs(uint64_t* const key[2], int32_t* const val[2], int64_t n, int bits, int32_t* hist,
-                            int32_t* hsums, int* result, hipStream_t st);
+// Stable LSD radix sort of (key, value) pairs, or of keys alone, on the low `bits` bits, 8 bits per
+// pass, ping-ponging between key[0]/val[0] and key[1]/val[1]; *result = the buffer holding the
+// sorted elements. iota: the values are the elements' positions (val[0] is not read). work:
+// radix_work_len(n) ints.
+size_t radix_work_len(int64_t n);
+dwg_status radix_sort_pairs(uint64_t* const key[2], int32_t* const val[2], bool iota, int64_t n, int bits,
+                            int32_t* work, int* result, hipStream_t st);
+dwg_status radix_sort_keys(uint64_t* const key[2], int64_t n, int bits, int32_t* work, int* result, hipStream_t st);
 // Bounding box of P and the octree frame (lo xyz, 2^21 / largest extent) in FP64.
 dwg_status morton_frame(const float* P, int64_t n, float* bpart, float* box, double* frame, hipStream_t st);
 // Uniform-grid kNN over reference points: build once, then query [q0, q0 + m) of a planar
@@ -227,9 +226,7 @@ struct McWork {
   float* box;
   double* frame;           // octree frame: lo xyz, 2^21 / side
   uint64_t* key[2];        // [kcap] radix-sort ping-pong
-  int32_t* val[2];
-  int32_t* hist;
-  int32_t* hsums;
+  int32_t* work;           // radix_work_len(kcap)
   int32_t* head;           // [kcap + 1] run heads, then their exclusive scan
   int32_t* hdsums;
   uint64_t* occ;           // [n] occupied cell codes
@@ -237,8 +234,7 @@ struct McWork {
   // faces phase (sized by the cell count C)
   uint64_t* ckey[2];       // [8C] corner keys
   int32_t* cval[2];
-  int32_t* chist;
-  int32_t* chsums;
+  int32_t* cwork;
   int32_t* chead;          // [8C + 1]
   int32_t* chdsums;
   int32_t* cidx;           // [C][8] corner id of each cell corner

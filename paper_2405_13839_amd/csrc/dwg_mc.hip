@@ -53,13 +53,12 @@ unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int
 
 // Cell code of every point at `depth` (from the level-21 octree cell).
 __global__ void k_mc_point_keys(const float* __restrict__ P, int64_t n, const double* __restrict__ frame, int depth,
-                                uint64_t* __restrict__ key, int32_t* __restrict__ val) {
+                                uint64_t* __restrict__ key) {
   const int sh = morton::kDepth - depth;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     int c[3];
     morton::cell21(P, n, i, frame, c);
     key[i] = morton3(c[0] >> sh, c[1] >> sh, c[2] >> sh);
-    val[i] = 0;
   }
 }
 
@@ -79,7 +78,7 @@ __global__ void k_mc_compact(const uint64_t* __restrict__ key, int64_t n, uint64
 // The (2 dil + 1)^3 neighbours of every occupied cell; outside the cube (or past the count)
 // a sentinel 2^(3 depth) that sorts after every cell.
 __global__ void k_mc_dilate(const uint64_t* __restrict__ occ, const int32_t* __restrict__ count, int64_t cap,
-                            int depth, int dil, uint64_t* __restrict__ key, int32_t* __restrict__ val) {
+                            int depth, int dil, uint64_t* __restrict__ key) {
   const int64_t o = *count;
   const int w = 2 * dil + 1, w3 = w * w * w;
   const int G = 1 << depth;
@@ -96,19 +95,16 @@ __global__ void k_mc_dilate(const uint64_t* __restrict__ occ, const int32_t* __r
       if (x >= 0 && y >= 0 && z >= 0 && x < G && y < G && z < G) k = morton3(x, y, z);
     }
     key[t] = k;
-    val[t] = 0;
   }
 }
 
-// Corner lattice keys of every cell: key = Morton code of the corner, val = 8 cell + k.
-__global__ void k_mc_corner_keys(const uint64_t* __restrict__ cells, int64_t C, uint64_t* __restrict__ key,
-                                 int32_t* __restrict__ val) {
+// Corner lattice keys of every cell: key[8 cell + k] = Morton code of the corner.
+__global__ void k_mc_corner_keys(const uint64_t* __restrict__ cells, int64_t C, uint64_t* __restrict__ key) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < 8 * C; t += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t code = cells[t >> 3];
     const int k = (int)(t & 7);
     key[t] = morton3(compact21(code >> 2) + (k & 1), compact21(code >> 1) + ((k >> 1) & 1),
                      compact21(code) + ((k >> 2) & 1));
-    val[t] = (int32_t)t;
   }
 }
 
@@ -519,10 +515,7 @@ size_t carve_mc_grid(Carver& c, int64_t n, const McParams& mp, McWork* out) {
   w.frame = c.take<double>(4);
   w.key[0] = c.take<uint64_t>((size_t)w.kcap);
   w.key[1] = c.take<uint64_t>((size_t)w.kcap);
-  w.val[0] = c.take<int32_t>((size_t)w.kcap);
-  w.val[1] = c.take<int32_t>((size_t)w.kcap);
-  w.hist = c.take<int32_t>(radix_hist_len(w.kcap));
-  w.hsums = c.take<int32_t>(scan_sums_len((int64_t)radix_hist_len(w.kcap)));
+  w.work = c.take<int32_t>(radix_work_len(w.kcap));
   w.head = c.take<int32_t>((size_t)w.kcap + 1);
   w.hdsums = c.take<int32_t>(scan_sums_len(w.kcap));
   w.occ = c.take<uint64_t>((size_t)n);
@@ -547,8 +540,7 @@ size_t carve_mc_faces(Carver& c, int64_t n, int64_t C, const McParams& mp, McWor
   o->ckey[1] = c.take<uint64_t>((size_t)(8 * C));
   o->cval[0] = c.take<int32_t>((size_t)(8 * C));
   o->cval[1] = c.take<int32_t>((size_t)(8 * C));
-  o->chist = c.take<int32_t>(radix_hist_len(8 * C));
-  o->chsums = c.take<int32_t>(scan_sums_len((int64_t)radix_hist_len(8 * C)));
+  o->cwork = c.take<int32_t>(radix_work_len(8 * C));
   o->chead = c.take<int32_t>((size_t)(8 * C) + 1);
   o->chdsums = c.take<int32_t>(scan_sums_len(8 * C));
   o->cidx = c.take<int32_t>((size_t)(8 * C));
@@ -570,11 +562,10 @@ size_t carve_mc_faces(Carver& c, int64_t n, int64_t C, const McParams& mp, McWor
 dwg_status mc_cells(const float* P, int64_t n, const McParams& mp, const McWork& w, int64_t* C_host,
                     hipStream_t st) {
   DWG_PROPAGATE_INT(morton_frame(P, n, w.bpart, w.box, w.frame, st));
-  hipLaunchKernelGGL(k_mc_point_keys, dim3(grid_of(n)), dim3(256), 0, st, P, n, w.frame, mp.depth, w.key[0],
-                     w.val[0]);
+  hipLaunchKernelGGL(k_mc_point_keys, dim3(grid_of(n)), dim3(256), 0, st, P, n, w.frame, mp.depth, w.key[0]);
   DWG_TRY_LAUNCH();
   int res = 0;
-  DWG_PROPAGATE_INT(radix_sort_pairs(w.key, w.val, n, 3 * mp.depth, w.hist, w.hsums, &res, st));
+  DWG_PROPAGATE_INT(radix_sort_keys(w.key, n, 3 * mp.depth, w.work, &res, st));
   const uint64_t limit = 1ull << (3 * mp.depth);
   hipLaunchKernelGGL(k_mc_heads, dim3(grid_of(n)), dim3(256), 0, st, w.key[res], n, limit, w.head);
   DWG_TRY_LAUNCH();
@@ -584,9 +575,9 @@ dwg_status mc_cells(const float* P, int64_t n, const McParams& mp, const McWork&
   // grow by `dilate` rings: (2 dilate + 1)^3 candidates per occupied cell, sentinel-padded
   const int64_t nk = mc_key_cap(n, mp);
   hipLaunchKernelGGL(k_mc_dilate, dim3(grid_of(nk)), dim3(256), 0, st, w.occ, w.head + n, n, mp.depth, mp.dilate,
-                     w.key[0], w.val[0]);
+                     w.key[0]);
   DWG_TRY_LAUNCH();
-  DWG_PROPAGATE_INT(radix_sort_pairs(w.key, w.val, nk, 3 * mp.depth + 1, w.hist, w.hsums, &res, st));
+  DWG_PROPAGATE_INT(radix_sort_keys(w.key, nk, 3 * mp.depth + 1, w.work, &res, st));
   hipLaunchKernelGGL(k_mc_heads, dim3(grid_of(nk)), dim3(256), 0, st, w.key[res], nk, limit, w.head);
   DWG_TRY_LAUNCH();
   DWG_PROPAGATE_INT(exclusive_scan(w.head, nk, w.hdsums, st));
@@ -601,10 +592,10 @@ dwg_status mc_cells(const float* P, int64_t n, const McParams& mp, const McWork&
 
 dwg_status mc_corners(const McParams& mp, McWork& w, int64_t* m_host, hipStream_t st) {
   const int64_t n8 = 8 * w.C;
-  hipLaunchKernelGGL(k_mc_corner_keys, dim3(grid_of(n8)), dim3(256), 0, st, w.cells, w.C, w.ckey[0], w.cval[0]);
+  hipLaunchKernelGGL(k_mc_corner_keys, dim3(grid_of(n8)), dim3(256), 0, st, w.cells, w.C, w.ckey[0]);
   DWG_TRY_LAUNCH();
   int res = 0;
-  DWG_PROPAGATE_INT(radix_sort_pairs(w.ckey, w.cval, n8, 3 * (mp.depth + 1), w.chist, w.chsums, &res, st));
+  DWG_PROPAGATE_INT(radix_sort_pairs(w.ckey, w.cval, true, n8, 3 * (mp.depth + 1), w.cwork, &res, st));
   hipLaunchKernelGGL(k_mc_heads, dim3(grid_of(n8)), dim3(256), 0, st, w.ckey[res], n8, ~0ull, w.chead);
   DWG_TRY_LAUNCH();
   DWG_PROPAGATE_INT(exclusive_scan(w.chead, n8, w.chdsums, st));

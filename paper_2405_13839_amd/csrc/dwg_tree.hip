@@ -48,7 +48,6 @@ namespace {
 
 using namespace pairk;
 using morton::kDepth;
-constexpr int kSortTile = 2048;  // elements per block of the radix sort (256 threads x 8 rounds)
 constexpr int kScanTile = 2048;  // elements per block of the FP64 scans (256 threads x 8)
 constexpr int kChunk = 256;      // sources per work item of the radius pass
 
@@ -102,83 +101,11 @@ __global__ void k_tree_frame(const float* __restrict__ box, double* __restrict__
 }
 
 __global__ void k_tree_keys(const float* __restrict__ P, int64_t n, const double* __restrict__ frame,
-                            uint64_t* __restrict__ key, int32_t* __restrict__ val) {
+                            uint64_t* __restrict__ key) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     int c[3];
     morton::cell21(P, n, i, frame, c);
     key[i] = morton::code3(c[0], c[1], c[2]);
-    val[i] = (int32_t)i;
-  }
-}
-
-// Radix sort pass, part 1: per-block digit counts, digit-major: hist[d * nb + b].
-__global__ __launch_bounds__(256) void k_rs_hist(const uint64_t* __restrict__ key, int64_t n, int shift,
-                                                 int32_t* __restrict__ hist, int64_t nb) {
-  __shared__ int32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t b0 = (int64_t)blockIdx.x * kSortTile;
-  for (int k = 0; k < kSortTile / 256; ++k) {
-    const int64_t i = b0 + k * 256 + threadIdx.x;
-    if (i < n) atomicAdd(&h[(key[i] >> shift) & 255u], 1);
-  }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
-}
-
-// Radix sort pass, part 2: stable scatter. Elements of a block are ranked in index order:
-// rounds of 256, inside a round by wave, inside a wave by lane (peers with the same digit
-// found by 8 ballots).
-__global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__ kin,
-                                                    const int32_t* __restrict__ vin, int64_t n, int shift,
-                                                    const int32_t* __restrict__ hist, int64_t nb,
-                                                    uint64_t* __restrict__ kout, int32_t* __restrict__ vout) {
-  __shared__ int32_t base[256];
-  __shared__ int32_t wcnt[4][256];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  base[tid] = hist[(int64_t)tid * nb + blockIdx.x];
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int64_t b0 = (int64_t)blockIdx.x * kSortTile;
-  for (int k = 0; k < kSortTile / 256; ++k) {
-    const int64_t i = b0 + k * 256 + tid;
-    const bool valid = i < n;
-    uint64_t key = 0;
-    int32_t val = 0;
-    uint32_t d = 0;
-    if (valid) {
-      key = kin[i];
-      val = vin[i];
-      d = (uint32_t)(key >> shift) & 255u;
-    }
-    uint64_t peers = __ballot(valid);
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool on = (d >> bit) & 1u;
-      const uint64_t bb = __ballot(valid && on);
-      peers &= on ? bb : ~bb;
-    }
-    const int rank = __popcll(peers & lt);
-    for (int t = tid; t < 4 * 256; t += 256) (&wcnt[0][0])[t] = 0;
-    __syncthreads();
-    if (valid && rank == 0) wcnt[wv][d] = __popcll(peers);
-    __syncthreads();
-    {
-      int run = base[tid];
-      for (int w = 0; w < 4; ++w) {
-        const int c = wcnt[w][tid];
-        wcnt[w][tid] = run;
-        run += c;
-      }
-      base[tid] = run;
-    }
-    __syncthreads();
-    if (valid) {
-      const int pos = wcnt[wv][d] + rank;
-      if (pos < n) {
-        kout[pos] = key;
-        vout[pos] = val;
-      }
-    }
-    __syncthreads();
   }
 }
 
@@ -819,26 +746,6 @@ void launch_eval_t(const float* Q, int64_t m, const int32_t* qperm, const GwnWor
 
 int64_t tree_cap(int64_t n) { return 2 * n + 1; }
 
-size_t radix_hist_len(int64_t n) { return (size_t)(256 * cdiv(n, kSortTile) + 1); }
-
-dwg_status radix_sort_pairs(uint64_t* const key[2], int32_t* const val[2], int64_t n, int bits, int32_t* hist,
-                            int32_t* hsums, int* result, hipStream_t st) {
-  const int64_t nsb = cdiv(n, kSortTile);
-  const int passes = (bits + 7) / 8;
-  for (int pass = 0; pass < passes; ++pass) {
-    const int a = pass & 1, b = a ^ 1;
-    hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nsb), dim3(256), 0, st, key[a], n, 8 * pass, hist, nsb);
-    DWG_TRY_LAUNCH();
-    dwg_status s = exclusive_scan(hist, 256 * nsb, hsums, st);
-    if (s != DWG_OK) return s;
-    hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nsb), dim3(256), 0, st, key[a], val[a], n, 8 * pass, hist, nsb,
-                       key[b], val[b]);
-    DWG_TRY_LAUNCH();
-  }
-  *result = passes & 1;
-  return DWG_OK;
-}
-
 dwg_status morton_frame(const float* P, int64_t n, float* bpart, float* box, double* frame, hipStream_t st) {
   dwg_status s = launch_bbox(P, n, bpart, box, st);
   if (s != DWG_OK) return s;
@@ -854,7 +761,6 @@ size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out) {
   t.cap = tree_cap(n);
   t.leaf = leaf;
   t.beta = beta;
-  t.nsb = cdiv(n, kSortTile);
   t.nscan = cdiv(n, kScanTile);
   t.bpart = c.take<float>(kBboxParts);
   t.box = c.take<float>(8);
@@ -863,8 +769,7 @@ size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out) {
   t.key[1] = c.take<uint64_t>((size_t)n);
   t.val[0] = c.take<int32_t>((size_t)n);
   t.val[1] = c.take<int32_t>((size_t)n);
-  t.hist = c.take<int32_t>((size_t)(256 * t.nsb + 1));
-  t.hsums = c.take<int32_t>(scan_sums_len(256 * t.nsb));
+  t.work = c.take<int32_t>(radix_work_len(n));
   t.lev = c.take<int32_t>((size_t)n);
   t.off = c.take<int32_t>((size_t)n + 1);
   t.osums = c.take<int32_t>(scan_sums_len(n));
@@ -889,10 +794,10 @@ dwg_status tree_build(const float* P, const float* area, const float* delta, int
                       const TreeWork& t, int32_t* perm, hipStream_t st) {
   dwg_status s = morton_frame(P, n, t.bpart, t.box, t.frame, st);
   if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_tree_keys, dim3(grid_cap(n)), dim3(256), 0, st, P, n, t.frame, t.key[0], t.val[0]);
+  hipLaunchKernelGGL(k_tree_keys, dim3(grid_cap(n)), dim3(256), 0, st, P, n, t.frame, t.key[0]);
   DWG_TRY_LAUNCH();
   int res = 0;
-  s = radix_sort_pairs(t.key, t.val, n, 64, t.hist, t.hsums, &res, st);
+  s = radix_sort_pairs(t.key, t.val, true, n, 64, t.work, &res, st);
   if (s != DWG_OK) return s;
   // eight passes: the sorted codes and indices are back in buffer 0
   hipLaunchKernelGGL(k_tree_mark, dim3(grid_cap(n)), dim3(256), 0, st, t.key[0], n, t.leaf, t.lev, t.off);

@@ -453,8 +453,9 @@ dwg_status dwg_iterate(const float* P, const float* area, const float* delta, in
     DWG_TRY_HIP(hipEventRecord(ev.a, st));
     DWG_PROPAGATE(eval_run(P, n, kp, true, es, st));
     DWG_TRY_HIP(hipEventRecord(ev.b, st));
-    DWG_PROPAGATE(launch_update(n, kp, N_inout, wk, st));
-    DWG_PROPAGATE(launch_stats(n, ip->top_frac, wk, st));
+    int nblk = 0;
+    DWG_PROPAGATE(launch_update(n, kp, N_inout, wk, &nblk, st));
+    DWG_PROPAGATE(launch_stats(n, ip->top_frac, wk, nblk, nullptr, st));
     double hs[4];
     DWG_TRY_HIP(hipMemcpyAsync(hs, wk.stats, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
     DWG_TRY_HIP(hipStreamSynchronize(st));
@@ -543,9 +544,9 @@ dwg_status dwg_iterate_mc(const float* P, const float* area, const float* delta,
     int64_t F = 0;
     DWG_PROPAGATE(mc_faces(w, nullptr, 0, &F, st));
     DWG_PROPAGATE(mc_scatter(mp, w, F, st));
-    DWG_PROPAGATE(mc_update(mp, w, es.wk, N_inout, st));
-    DWG_PROPAGATE(launch_stats(n, ip->top_frac, es.wk, st));
-    DWG_TRY_HIP(hipMemcpyAsync(es.wk.stats, w.iso, sizeof(double), hipMemcpyDeviceToDevice, st));
+    int nblk = 0;
+    DWG_PROPAGATE(mc_update(mp, w, es.wk, N_inout, &nblk, st));
+    DWG_PROPAGATE(launch_stats(n, ip->top_frac, es.wk, nblk, w.iso, st));
     double hs[4];
     DWG_TRY_HIP(hipMemcpyAsync(hs, es.wk.stats, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
     DWG_TRY_HIP(hipStreamSynchronize(st));

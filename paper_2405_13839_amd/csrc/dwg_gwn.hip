@@ -306,22 +306,47 @@ __global__ __launch_bounds__(kBlock) void k_query_box(const float* __restrict__ 
   }
 }
 
-// Sum of `split` partials of accumulator `a` for sorted query i, in split order.
+// Sum of `split` partials of accumulator `a` for sorted query i, in split order, eight loads in
+// flight at a time.
 __device__ __forceinline__ float combine(const float* part, int split, int64_t mpad, int na, int a, int64_t i,
                                          bool kahan) {
+  const float* p = part + (int64_t)a * mpad + i;
+  const int64_t step = (int64_t)na * mpad;
   float s = 0.0f, c = 0.0f;
-  for (int p = 0; p < split; ++p) {
-    const float x = part[((int64_t)p * na + a) * mpad + i];
-    if (kahan) {
-      const float y = x - c;
-      const float t = s + y;
-      c = (t - s) - y;
-      s = t;
-    } else {
-      s += x;
+  for (int p0 = 0; p0 < split; p0 += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p0 + u < split ? p[(p0 + u) * step] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (p0 + u >= split) break;
+      if (kahan) {
+        const float y = x[u] - c;
+        const float t = s + y;
+        c = (t - s) - y;
+        s = t;
+      } else {
+        s += x[u];
+      }
     }
   }
   return kahan ? s - c : s;
+}
+
+// The epilogue kernels take QB queries per block: its kEpiBlock threads first sum the splits of
+// every (accumulator, query) pair, a wavefront per accumulator, then QB of them finish a query
+// each. One thread per query summing its 7 x split partials in turn took 97 us for 100K queries
+// and 48 splits (1.4 TB/s).
+constexpr int kEpiBlock = 64 * kNAcc;
+constexpr int kEpiWaves = kNAcc;
+constexpr int64_t kEpiSmall = 32768;  // queries up to which QB = 64: at 256 a few blocks would do it all
+
+template <int QB>
+__device__ __forceinline__ void combine_block(const float* part, int split, int64_t mpad, int na, int64_t q0,
+                                              bool kahan, float (*acc)[QB]) {
+  for (int i = threadIdx.x; i < na * QB; i += kEpiBlock)
+    acc[i / QB][i % QB] = combine(part, split, mpad, na, i / QB, q0 + i % QB, kahan);
+  __syncthreads();
 }
 
 // Block-wide FP64 sum (deterministic: fixed shuffle tree, then fixed LDS order).
@@ -350,26 +375,25 @@ Scale scale_of(const dwg_kernel_params& kp) {
 
 // Evaluation epilogue: combine splits; write w and grad at the query's original index;
 // FP64 block partial of w.
-__global__ __launch_bounds__(kRedBlock) void k_combine(const float* __restrict__ part, int split,
+template <int QB>
+__global__ __launch_bounds__(kEpiBlock) void k_combine(const float* __restrict__ part, int split,
                                                        int64_t mpad, int64_t m, bool grad, Scale sc,
                                                        bool kahan, const int32_t* __restrict__ qperm,
                                                        float* __restrict__ wout,
                                                        float* __restrict__ gout,
                                                        double* __restrict__ blk) {
-  __shared__ double lds[kRedBlock / 64];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ float acc[kNAcc][QB];
+  __shared__ double lds[kEpiWaves];
+  const int64_t q0 = (int64_t)blockIdx.x * QB;  // mpad is a multiple of QB
+  combine_block<QB>(part, split, mpad, grad ? kNAcc : 1, q0, kahan, acc);
+  const int t = threadIdx.x;
+  const int64_t i = q0 + t;
   double wv = 0.0;
-  if (i < m) {
-    const int na = grad ? kNAcc : 1;
+  if (t < QB && i < m) {
     const int64_t o = qperm[i];
-    const float w = sc.ws * combine(part, split, mpad, na, 0, i, kahan);
-    if (grad) {
-      for (int d = 0; d < 3; ++d) {
-        const float A = combine(part, split, mpad, na, 1 + d, i, kahan);
-        const float B = combine(part, split, mpad, na, 4 + d, i, kahan);
-        gout[d * m + o] = fmaf(sc.as, A, -sc.bs * B);
-      }
-    }
+    const float w = sc.ws * acc[0][t];
+    if (grad)
+      for (int d = 0; d < 3; ++d) gout[d * m + o] = fmaf(sc.as, acc[1 + d][t], -sc.bs * acc[4 + d][t]);
     if (wout) wout[o] = w;
     wv = (double)w;
   }
@@ -379,26 +403,30 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(const float* __restrict__
 
 // Iteration epilogue (Eq. 7): n_new = -grad/|grad| (kept when |grad| is 0 or not finite),
 // written in place at the point's original index; restage m for the next iteration;
-// theta_i (degrees, FP64); FP64 block partials of w and of the chord |n_new - n_old|.
-__global__ __launch_bounds__(kRedBlock) void k_update(const float* __restrict__ part, int split,
+// theta_i (degrees, FP64); FP64 block partials of w and of the chord |n_new - n_old|. Clears the
+// histograms of the selection that follows.
+template <int QB>
+__global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ part, int split,
                                                       int64_t mpad, int64_t n, Scale sc, bool kahan,
                                                       const int32_t* __restrict__ perm,
                                                       const float* __restrict__ kk,
                                                       float* __restrict__ N,
                                                       float4* __restrict__ src,
                                                       double* __restrict__ theta,
-                                                      double* __restrict__ blk, int nblk) {
-  __shared__ double lds[kRedBlock / 64];
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                      double* __restrict__ blk, int nblk,
+                                                      uint32_t* __restrict__ hist) {
+  __shared__ float acc[kNAcc][QB];
+  __shared__ double lds[kEpiWaves];
+  const int64_t q0 = (int64_t)blockIdx.x * QB;
+  clear_hist(hist, n);
+  combine_block<QB>(part, split, mpad, kNAcc, q0, kahan, acc);
+  const int t = threadIdx.x;
+  const int64_t i = q0 + t;
   double wv = 0.0, cv = 0.0;
-  if (i < n) {
-    const float w = sc.ws * combine(part, split, mpad, kNAcc, 0, i, kahan);
+  if (t < QB && i < n) {
+    const float w = sc.ws * acc[0][t];
     float g[3];
-    for (int d = 0; d < 3; ++d) {
-      const float A = combine(part, split, mpad, kNAcc, 1 + d, i, kahan);
-      const float B = combine(part, split, mpad, kNAcc, 4 + d, i, kahan);
-      g[d] = fmaf(sc.as, A, -sc.bs * B);
-    }
+    for (int d = 0; d < 3; ++d) g[d] = fmaf(sc.as, acc[1 + d][t], -sc.bs * acc[4 + d][t]);
     const int64_t o = perm[i];
     const float o0 = N[o], o1 = N[n + o], o2 = N[2 * n + o];
     const double gl = sqrt((double)g[0] * g[0] + (double)g[1] * g[1] + (double)g[2] * g[2]);
@@ -428,114 +456,318 @@ __global__ __launch_bounds__(kRedBlock) void k_update(const float* __restrict__ 
   }
 }
 
-// Fixed-order sum of the block partials: stats[0] = sum w / n, stats[2] = sum chord / n;
-// also resets the radix-select state for k largest values.
-__global__ __launch_bounds__(kRedBlock) void k_sums(const double* __restrict__ blk, int nblk,
-                                                    int64_t n, int64_t k, int with_chord,
-                                                    double* __restrict__ stats,
-                                                    uint32_t* __restrict__ hist,
-                                                    uint64_t* __restrict__ sel) {
+// Mean of w from the block partials (one block, fixed order).
+__global__ __launch_bounds__(kRedBlock) void k_mean(const double* __restrict__ blk, int nblk, int64_t n,
+                                                    double* __restrict__ out) {
   __shared__ double lds[kRedBlock / 64];
+  double a = 0.0;
+  for (int i = threadIdx.x; i < nblk; i += blockDim.x) a += blk[i];
+  const double sa = block_sum(a, lds);
+  if (threadIdx.x == 0) *out = sa / (double)n;
+}
+
+// ---- Mean of the k largest angles (the convergence statistic), exact.
+// Non-negative doubles order like their bits. Up to kSelRegs angles, one block holds them all in
+// registers and narrows the range of the k-th largest by 2,048 bins at a time (k_stats_small).
+// Above that, two histograms over all angles fix the top 28 bits of the k-th largest
+// (k_sel_hist), the few angles that share them are gathered while those above are summed
+// (k_sel_collect), and one block finishes (k_stats_final): 4 launches, against 19 for a
+// select of 8 bits per pass. No floating-point sum depends on the order of an atomic: the gathered
+// angles share an exponent, so theirs is an integer sum.
+constexpr int kSelBlock = 1024;
+constexpr int kSelPer = 16;
+constexpr int kSelRegs = kSelBlock * kSelPer;
+constexpr int kSelBins = 2048;
+constexpr int kSelGrid = 256;              // blocks of the passes over all angles
+constexpr int kTopShift = 49, kMidShift = 36;  // bits below the first and second histogram's digits
+constexpr int kTopBins = 8256;             // 180 degrees and below: bits >> 49 <= 8243
+constexpr int kMidBins = 1 << (kTopShift - kMidShift);
+static_assert(kTopBins + kMidBins <= kSelHistLen && kSelRegs == kSelSmallMax, "workspace and rule of the selection");
+
+// Range select over the values `visit` hands out (each call visits all of them): narrows [lo, lo +
+// 2^width) to the k-th largest value. On return either the range is one value, or exactly krem
+// values of the last range remain and all of them belong to the k largest. Block-wide.
+struct Range {
+  uint64_t lo;
+  int sh;        // the range is [lo, lo + 2^sh)
+  uint64_t krem; // how many of the values in the range are among the k largest
+  bool whole;    // all values of the range are
+};
+
+struct SelLds {
+  unsigned bins[kSelBins];
+  unsigned wsum[kSelBlock / 64];
+  int digit;
+  unsigned above, count;
+};
+
+// The largest bin d of h[0..nb) with suffix count >= krem; above = the count of the bins over d. Bin
+// loads through `load(i)`. One block of kSelBlock threads.
+template <class F>
+__device__ void find_bin(F load, int nb, uint64_t krem, SelLds& s) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int per = (nb + kSelBlock - 1) / kSelBlock;
+  // thread t owns the bins [hi - per, hi) counted from the top
+  const int hi = nb - t * per;
+  unsigned sum = 0;
+  for (int u = 1; u <= per; ++u) sum += hi - u >= 0 ? load(hi - u) : 0u;
+  unsigned inc = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned y = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += y;
+  }
+  if (t == 0) {
+    s.digit = 0;
+    s.above = 0;
+    s.count = 0;
+  }
+  __syncthreads();
+  if (lane == 63) s.wsum[wv] = inc;
+  __syncthreads();
+  unsigned before = inc - sum;
+  for (int w = 0; w < wv; ++w) before += s.wsum[w];
+  if (before < krem && before + sum >= krem) {  // exactly one thread when the total is >= krem
+    unsigned c = before;
+    for (int u = 1; u <= per; ++u) {
+      const unsigned x = load(hi - u);
+      if (c + x >= krem) {
+        s.digit = hi - u;
+        s.above = c;
+        s.count = x;
+        break;
+      }
+      c += x;
+    }
+  }
+  __syncthreads();
+}
+
+template <class V>
+__device__ void narrow(V visit, Range& r, SelLds& s) {
+  while (r.sh > 0 && !r.whole) {
+    const int step = r.sh > 11 ? r.sh - 11 : 0;
+    for (int i = threadIdx.x; i < kSelBins; i += kSelBlock) s.bins[i] = 0;
+    __syncthreads();
+    const uint64_t lo = r.lo, last = r.lo + ((1ull << r.sh) - 1ull);
+    visit([&](uint64_t b) {
+      if (b >= lo && b <= last) atomicAdd(&s.bins[(b - lo) >> step], 1u);
+    });
+    __syncthreads();
+    find_bin([&](int i) { return s.bins[i]; }, 1 << (r.sh - step), r.krem, s);
+    r.lo += (uint64_t)s.digit << step;
+    r.krem -= s.above;
+    r.sh = step;
+    r.whole = s.count == r.krem;
+    __syncthreads();
+  }
+}
+
+// Sums the block partials of w and the chord into stats[0] and stats[2] (block-wide).
+__device__ void mean_stats(const double* blk, int nblk, int64_t n, const double* iso, double* lds, double* stats) {
   double a = 0.0, b = 0.0;
   for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
     a += blk[i];
-    if (with_chord) b += blk[nblk + i];
+    b += blk[nblk + i];
   }
   const double sa = block_sum(a, lds);
   const double sb = block_sum(b, lds);
   if (threadIdx.x == 0) {
-    stats[0] = sa / (double)n;
+    stats[0] = iso ? *iso : sa / (double)n;
     stats[2] = sb / (double)n;
-    sel[0] = 0;
-    sel[1] = (uint64_t)k;
   }
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
 }
 
-// One radix-select pass over the FP64 bit patterns (non-negative doubles order like
-// unsigned integers): histogram of digit (bits >> shift) & 255 among values whose higher
-// bits equal the prefix selected so far.
-__global__ __launch_bounds__(kRedBlock) void k_radix_hist(const double* __restrict__ theta,
-                                                          int64_t n, int shift,
-                                                          const uint64_t* __restrict__ sel,
-                                                          uint32_t* __restrict__ hist) {
-  __shared__ uint32_t lh[256];
-  for (int i = threadIdx.x; i < 256; i += blockDim.x) lh[i] = 0;
-  __syncthreads();
-  const uint64_t prefix = sel[0];
-  const uint64_t hmask = shift >= 56 ? 0ull : (~0ull << (shift + 8));
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t bits = (uint64_t)__double_as_longlong(theta[i]);
-    if ((bits & hmask) == (prefix & hmask)) atomicAdd(&lh[(bits >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 256; i += blockDim.x)
-    if (lh[i]) atomicAdd(&hist[i], lh[i]);
-}
-
-// Picks the digit holding the k-th largest value, extends the prefix, clears the histogram.
-// One block of 256 threads, one per digit: with cum[d] = the count of digits >= d (a suffix
-// scan in LDS), the digit taken is the largest d with cum[d] >= krem, and krem drops by
-// cum[d + 1] -- what walking the digits down from 255 and subtracting their counts until
-// krem <= count gives. If no digit qualifies the prefix is kept and krem drops by the total.
-__global__ __launch_bounds__(256) void k_radix_select(int shift, uint64_t* __restrict__ sel,
-                                                      uint32_t* __restrict__ hist) {
-  __shared__ uint64_t cum[257];
-  __shared__ int found;
+__global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restrict__ theta, int n, int64_t k,
+                                                           const double* __restrict__ blk, int nblk,
+                                                           const double* __restrict__ iso,
+                                                           double* __restrict__ stats) {
+  __shared__ SelLds s;
+  __shared__ double lds[kSelBlock / 64];
+  __shared__ uint64_t ext[2][kSelBlock / 64];
   const int t = threadIdx.x;
-  cum[t] = hist[t];
-  if (t == 0) {
-    cum[256] = 0;
-    found = -1;
-  }
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {  // inclusive suffix scan
-    const uint64_t x = t + off < 256 ? cum[t + off] : 0;
-    __syncthreads();
-    cum[t] += x;
-    __syncthreads();
-  }
-  const uint64_t krem = sel[1];
-  if (cum[t] >= krem && (t == 255 || cum[t + 1] < krem)) found = t;  // the largest such digit
-  __syncthreads();
-  if (t == 0) {
-    if (found >= 0) {
-      sel[0] |= (uint64_t)found << shift;
-      sel[1] = krem - cum[found + 1];
-    } else {
-      sel[1] = krem - cum[0];
+  double v[kSelPer];
+  uint64_t mx = 0, mn = ~0ull;
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) {
+    const int i = t + j * kSelBlock;
+    v[j] = i < n ? theta[i] : 0.0;
+    const uint64_t b = (uint64_t)__double_as_longlong(v[j]);
+    if (i < n) {
+      mx = b > mx ? b : mx;
+      mn = b < mn ? b : mn;
     }
   }
-  hist[t] = 0;
+  mean_stats(blk, nblk, n, iso, lds, stats);
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint64_t x = __shfl_xor((unsigned long long)mx, o, 64), y = __shfl_xor((unsigned long long)mn, o, 64);
+    mx = x > mx ? x : mx;
+    mn = y < mn ? y : mn;
+  }
+  if ((t & 63) == 0) {
+    ext[0][t >> 6] = mx;
+    ext[1][t >> 6] = mn;
+  }
+  __syncthreads();
+  for (int w = 0; w < kSelBlock / 64; ++w) {
+    mx = ext[0][w] > mx ? ext[0][w] : mx;
+    mn = ext[1][w] < mn ? ext[1][w] : mn;
+  }
+  Range r{mn, mx == mn ? 0 : 64 - __clzll((long long)(mx - mn)), (uint64_t)k, k == n};
+  auto visit = [&](auto f) {
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j)
+      if (t + j * kSelBlock < n) f((uint64_t)__double_as_longlong(v[j]));
+  };
+  narrow(visit, r, s);
+  double sum = 0.0;
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v[j]);
+    if (t + j * kSelBlock < n && (r.whole ? b >= r.lo : b > r.lo)) sum += v[j];
+  }
+  const double total = block_sum(sum, lds);
+  if (t == 0) {
+    const double rest = r.whole ? 0.0 : (double)r.krem * __longlong_as_double((long long)r.lo);
+    stats[1] = (total + rest) / (double)k;
+  }
 }
 
-// FP64 block partials of the sum of theta_i strictly above the selected k-th largest value.
-__global__ __launch_bounds__(kRedBlock) void k_top_partial(const double* __restrict__ theta, int64_t n,
-                                                           const uint64_t* __restrict__ sel,
-                                                           double* __restrict__ blk) {
-  __shared__ double lds[kRedBlock / 64];
-  const uint64_t thr = sel[0];
+// sel[0] = first digit, sel[1] = values among the k largest with that digit, sel[2] = gathered
+// values. MID = false: histogram of the first digit. MID = true: finds the first digit and takes
+// the histogram of the second among the values that have it.
+template <bool MID>
+__global__ __launch_bounds__(kSelBlock) void k_sel_hist(const double* __restrict__ theta, int64_t n, int64_t k,
+                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel) {
+  __shared__ SelLds s;
+  __shared__ unsigned bins[MID ? kMidBins : kTopBins];
+  constexpr int kBins = MID ? kMidBins : kTopBins;
+  uint32_t* const top = hist;
+  uint32_t* const mine = MID ? hist + kTopBins : hist;
+  for (int i = threadIdx.x; i < kBins; i += kSelBlock) bins[i] = 0;
+  uint64_t first = 0;
+  if (MID) {
+    find_bin([&](int i) { return top[i]; }, kTopBins, (uint64_t)k, s);
+    first = (uint64_t)s.digit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sel[0] = first;
+      sel[1] = (uint64_t)k - s.above;
+      sel[2] = 0;
+    }
+  }
+  __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * kSelBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelBlock) {
+    const uint64_t b = (uint64_t)__double_as_longlong(theta[i]);
+    if (!MID) {
+      const uint64_t d = b >> kTopShift;
+      atomicAdd(&bins[d < kTopBins ? d : kTopBins - 1], 1u);
+    } else if ((b >> kTopShift) == first) {
+      atomicAdd(&bins[(b >> kMidShift) & (kMidBins - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kBins; i += kSelBlock)
+    if (bins[i]) atomicAdd(&mine[i], bins[i]);
+}
+
+// Gathers the values with the selected 28 top bits (as many as fit cand) and sums, per block, the
+// values above them. sel[3] = their lowest bit pattern, sel[4] = how many are among the k largest.
+__global__ __launch_bounds__(kSelBlock) void k_sel_collect(const double* __restrict__ theta, int64_t n,
+                                                           const uint32_t* __restrict__ hist,
+                                                           uint64_t* __restrict__ sel, uint64_t* __restrict__ cand,
+                                                           double* __restrict__ top) {
+  __shared__ SelLds s;
+  __shared__ double lds[kSelBlock / 64];
+  const uint64_t first = sel[0], krem = sel[1];
+  find_bin([&](int i) { return hist[kTopBins + i]; }, kMidBins, krem, s);
+  const uint64_t lo = (first << kTopShift) | ((uint64_t)s.digit << kMidShift), next = lo + (1ull << kMidShift);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sel[3] = lo;
+    sel[4] = krem - s.above;
+  }
   double v = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t i = (int64_t)blockIdx.x * kSelBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelBlock) {
     const double x = theta[i];
-    if ((uint64_t)__double_as_longlong(x) > thr) v += x;
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    if (b >= next) {
+      v += x;
+    } else if (b >= lo) {
+      const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(&sel[2]), 1ull);
+      if (at < kSelRegs) cand[at] = b;
+    }
   }
   const double b = block_sum(v, lds);
-  if (threadIdx.x == 0) blk[blockIdx.x] = b;
+  if (threadIdx.x == 0) top[blockIdx.x] = b;
 }
 
-__global__ __launch_bounds__(kRedBlock) void k_top_final(const double* __restrict__ blk, int nblk,
-                                                         int64_t k, const uint64_t* __restrict__ sel,
-                                                         double* __restrict__ stats) {
-  __shared__ double lds[kRedBlock / 64];
-  double a = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += blockDim.x) a += blk[i];
-  const double s = block_sum(a, lds);
-  if (threadIdx.x == 0) {
-    const double t = __longlong_as_double((long long)sel[0]);
-    stats[1] = (s + (double)sel[1] * t) / (double)k;
+__global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restrict__ theta, int64_t n, int64_t k,
+                                                           const double* __restrict__ blk, int nblk,
+                                                           const double* __restrict__ iso,
+                                                           const uint64_t* __restrict__ sel,
+                                                           const uint64_t* __restrict__ cand,
+                                                           const double* __restrict__ top, int ntop,
+                                                           double* __restrict__ stats) {
+  __shared__ SelLds s;
+  __shared__ double lds[kSelBlock / 64];
+  __shared__ unsigned long long part[2];  // integer sum of the low bits, in two halves
+  __shared__ unsigned long long cnt;
+  const int t = threadIdx.x;
+  if (t < 2) part[t] = 0;
+  if (t == 2) cnt = 0;
+  mean_stats(blk, nblk, n, iso, lds, stats);
+  const uint64_t m = sel[2], base = sel[3];
+  const bool held = m <= kSelRegs;  // else (tens of thousands of nearly equal angles) from all angles
+  uint64_t v[kSelPer];
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) {
+    const uint64_t i = t + j * kSelBlock;
+    v[j] = held && i < m ? cand[i] : ~0ull;
+  }
+  const uint64_t last = base + ((1ull << kMidShift) - 1ull);
+  auto visit = [&](auto f) {
+    if (held) {
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j)
+        if (v[j] != ~0ull) f(v[j]);
+    } else {
+      for (int64_t i = t; i < n; i += kSelBlock) {
+        const uint64_t b = (uint64_t)__double_as_longlong(theta[i]);
+        if (b >= base && b <= last) f(b);
+      }
+    }
+  };
+  Range r{base, kMidShift, sel[4], sel[4] == m};
+  narrow(visit, r, s);
+  // sum of the gathered values among the k largest but for the ones equal to the k-th: they share
+  // an exponent, so value = base + (bits - base) ulp
+  uint64_t hi = 0, lo = 0, c = 0;
+  visit([&](uint64_t b) {
+    if (r.whole ? b >= r.lo : b > r.lo) {
+      const uint64_t d = b - base;
+      hi += d >> 18;
+      lo += d & 0x3ffffull;
+      ++c;
+    }
+  });
+  for (int o = 32; o > 0; o >>= 1) {
+    hi += __shfl_xor((unsigned long long)hi, o, 64);
+    lo += __shfl_xor((unsigned long long)lo, o, 64);
+    c += __shfl_xor((unsigned long long)c, o, 64);
+  }
+  if ((t & 63) == 0) {
+    atomicAdd(&part[0], hi);
+    atomicAdd(&part[1], lo);
+    atomicAdd(&cnt, c);
+  }
+  double above = 0.0;
+  for (int i = t; i < ntop; i += kSelBlock) above += top[i];
+  const double sum = block_sum(above, lds);  // its barriers publish part and cnt
+  if (t == 0) {
+    const int e = (int)(base >> 52);
+    const double ulp = ldexp(1.0, (e > 0 ? e : 1) - 1075);
+    const double in = (double)cnt * __longlong_as_double((long long)base) +
+                      ((double)part[0] * 262144.0 + (double)part[1]) * ulp;
+    const double rest = r.whole ? 0.0 : (double)r.krem * __longlong_as_double((long long)r.lo);
+    stats[1] = (sum + in + rest) / (double)k;
   }
 }
 
@@ -599,16 +831,17 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, 
   w.npad = w.ntiles * kTile;
   w.mpad = cdiv(n_qry, kQBlock) * kQBlock;
   w.split = split;
-  w.nblk = (int)cdiv(std::max(n_src, n_qry), kRedBlock);
   const size_t start = c.used;
   w.src = c.take<float4>(2 * (size_t)w.npad);
   w.part = c.take<float>((size_t)split * kNAcc * (size_t)w.mpad);
   w.kk = c.take<float>((size_t)w.npad);
   w.theta = c.take<double>((size_t)std::max(n_src, n_qry));
-  w.blk = c.take<double>(2 * (size_t)w.nblk);
+  w.blk = c.take<double>(2 * (size_t)std::max<int64_t>(cdiv(std::max(n_src, n_qry), 256), kEpiSmall / 64));
   w.stats = c.take<double>(4);
-  w.hist = c.take<uint32_t>(256);
-  w.sel = c.take<uint64_t>(2);
+  w.hist = c.take<uint32_t>(kSelHistLen);
+  w.sel = c.take<uint64_t>(5);
+  w.cand = c.take<uint64_t>(kSelSmallMax);
+  w.top = c.take<double>(256);
   w.tbox = c.take<float4>(2 * (size_t)w.ntiles);
   w.qbox = c.take<float4>(2 * (size_t)(w.mpad / kQBlock));
   w.perm_s = c.take<int32_t>((size_t)w.npad);
@@ -667,25 +900,34 @@ dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bo
 
 dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, float* wout,
                           float* gout, double* wmean, const GwnWork& w, hipStream_t stream) {
-  const int nb = (int)cdiv(m, kRedBlock);
-  hipLaunchKernelGGL(k_combine, dim3(nb), dim3(kRedBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
-                     scale_of(kp), kp.compensated != 0, w.perm_q, wout, gout, w.blk);
+  const int qb = m <= kEpiSmall ? 64 : 256;
+  const int nb = (int)cdiv(m, qb);
+  if (qb == 64)
+    hipLaunchKernelGGL((k_combine<64>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
+                       scale_of(kp), kp.compensated != 0, w.perm_q, wout, gout, w.blk);
+  else
+    hipLaunchKernelGGL((k_combine<256>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
+                       scale_of(kp), kp.compensated != 0, w.perm_q, wout, gout, w.blk);
   DWG_TRY_LAUNCH();
   if (wmean) {
-    hipLaunchKernelGGL(k_sums, dim3(1), dim3(kRedBlock), 0, stream, w.blk, nb, m, (int64_t)1, 0,
-                       w.stats, w.hist, w.sel);
+    hipLaunchKernelGGL(k_mean, dim3(1), dim3(kRedBlock), 0, stream, w.blk, nb, m, wmean);
     DWG_TRY_LAUNCH();
-    DWG_TRY_HIP(hipMemcpyAsync(wmean, w.stats, sizeof(double), hipMemcpyDeviceToDevice, stream));
   }
   return DWG_OK;
 }
 
-dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w,
+dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, int* nblk,
                          hipStream_t stream) {
-  const int nb = (int)cdiv(n, kRedBlock);
-  hipLaunchKernelGGL(k_update, dim3(nb), dim3(kRedBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
-                     kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb);
+  const int qb = n <= kEpiSmall ? 64 : 256;
+  const int nb = (int)cdiv(n, qb);
+  if (qb == 64)
+    hipLaunchKernelGGL((k_update<64>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
+                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist);
+  else
+    hipLaunchKernelGGL((k_update<256>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
+                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist);
   DWG_TRY_LAUNCH();
+  *nblk = nb;
   return DWG_OK;
 }
 
@@ -696,23 +938,23 @@ static int64_t top_count(int64_t n, double top_frac) {
   return k;
 }
 
-dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, hipStream_t stream) {
-  const int nb = (int)cdiv(n, kRedBlock);
+dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, const double* iso,
+                        hipStream_t stream) {
   const int64_t k = top_count(n, top_frac);
-  hipLaunchKernelGGL(k_sums, dim3(1), dim3(kRedBlock), 0, stream, w.blk, nb, n, k, 1, w.stats, w.hist,
-                     w.sel);
-  DWG_TRY_LAUNCH();
-  const int hb = (int)std::min<int64_t>(cdiv(n, kRedBlock), 1024);
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(hb), dim3(kRedBlock), 0, stream, w.theta, n, shift, w.sel,
-                       w.hist);
+  if (n <= kSelSmallMax) {
+    hipLaunchKernelGGL(k_stats_small, dim3(1), dim3(kSelBlock), 0, stream, w.theta, (int)n, k, w.blk, nblk, iso, w.stats);
     DWG_TRY_LAUNCH();
-    hipLaunchKernelGGL(k_radix_select, dim3(1), dim3(256), 0, stream, shift, w.sel, w.hist);
-    DWG_TRY_LAUNCH();
+    return DWG_OK;
   }
-  hipLaunchKernelGGL(k_top_partial, dim3(hb), dim3(kRedBlock), 0, stream, w.theta, n, w.sel, w.blk);
+  const int hb = (int)std::min<int64_t>(cdiv(n, kSelBlock), kSelGrid);
+  hipLaunchKernelGGL((k_sel_hist<false>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_top_final, dim3(1), dim3(kRedBlock), 0, stream, w.blk, hb, k, w.sel, w.stats);
+  hipLaunchKernelGGL((k_sel_hist<true>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel);
+  DWG_TRY_LAUNCH();
+  hipLaunchKernelGGL(k_sel_collect, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, w.cand, w.top);
+  DWG_TRY_LAUNCH();
+  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kSelBlock), 0, stream, w.theta, n, k, w.blk, nblk, iso, w.sel, w.cand,
+                     w.top, hb, w.stats);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

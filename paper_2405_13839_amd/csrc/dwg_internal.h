@@ -34,7 +34,15 @@ constexpr int kNAcc = 7;       // per-query accumulators with the gradient: w, A
 constexpr int kMaxSplit = 64;   // largest source split a caller may request
 constexpr int64_t kAutoSplitBytes = int64_t(512) << 20;  // partial sums of an automatic split
 constexpr int kRedBlock = 256;  // threads per block for O(n) epilogue / reductions
+constexpr int64_t kSelSmallMax = 16384;  // angles up to which one block selects the largest
+constexpr int kSelHistLen = 16640;       // histogram words of the selection above that
 constexpr int kMaxK = 16;       // largest k for the kNN kernels
+
+// Clears the selection's histograms where it will use them (all blocks of the launch together).
+__device__ __forceinline__ void clear_hist(uint32_t* hist, int64_t n) {
+  if (n <= kSelSmallMax) return;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSelHistLen; i += gridDim.x * blockDim.x) hist[i] = 0;
+}
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -131,8 +139,10 @@ struct GwnWork {
   double* theta;      // [m] angle change in degrees (iterate)
   double* blk;        // [2 * nblk] per-block FP64 partial sums
   double* stats;      // [4] device statistics
-  uint32_t* hist;     // [256] radix histogram
-  uint64_t* sel;      // [2]: radix prefix, remaining count
+  uint32_t* hist;     // [kSelHistLen] histograms of the top-k selection
+  uint64_t* sel;      // [5] its state
+  uint64_t* cand;     // [kSelSmallMax] angles near the k-th largest
+  double* top;        // [256] block sums of the angles above them
   float4* tbox;       // [2 * ntiles] source tile boxes and radii
   float4* qbox;       // [2 * mpad / kQBlock] query block boxes
   int32_t* perm_s;    // [npad]
@@ -140,7 +150,6 @@ struct GwnWork {
   SortWork sort;
   int64_t n_src, npad, mpad, ntiles;
   int split;
-  int nblk;           // blocks of the O(n) epilogue kernels
 };
 
 size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, GwnWork* out);
@@ -266,7 +275,7 @@ dwg_status mc_scatter(const McParams& mp, const McWork& w, int64_t F, hipStream_
 dwg_status mc_clear(const McWork& w, hipStream_t st);
 dwg_status mc_append_points(const float* P, int64_t n, const McWork& w, hipStream_t st);
 dwg_status mc_point_iso(const McWork& w, const float* w_points, int64_t n, hipStream_t st);
-dwg_status mc_update(const McParams& mp, const McWork& w, const GwnWork& g, float* N, hipStream_t st);
+dwg_status mc_update(const McParams& mp, const McWork& w, const GwnWork& g, float* N, int* nblk, hipStream_t st);
 
 // Workspace bytes of the kNN / features / MLP stages for n points.
 size_t knn_ws_bytes(int64_t n_ref, int64_t n_qry);
@@ -293,9 +302,12 @@ dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bo
                       const GwnWork& w, hipStream_t stream);
 dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, float* wout,
                           float* gout, double* wmean, const GwnWork& w, hipStream_t stream);
-dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w,
+// The update writes *nblk block partials; launch_stats reads as many. iso: where stats[0] comes from
+// instead of the partials of w (NULL: from those).
+dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, int* nblk,
                          hipStream_t stream);
-dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, hipStream_t stream);
+dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, const double* iso,
+                        hipStream_t stream);
 dwg_status launch_random_normals(uint64_t seed, int64_t n, float* N, hipStream_t stream);
 
 dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k, int32_t* idx,

@@ -424,15 +424,17 @@ __device__ double mc_block_sum(double v, double* lds) {
 }
 
 // Eq. 7 with the face sums: n = normalize(sum) (kept when the sum is 0), in place at the
-// point's original index; theta and the chord partials; restaged moments; cleared sums.
+// point's original index; theta and the chord partials; restaged moments; cleared sums and selection histograms.
 __global__ __launch_bounds__(256) void k_mc_update(const int32_t* __restrict__ perm, int64_t n,
                                                    unsigned long long* __restrict__ acc,
                                                    const double* __restrict__ frame, int depth,
                                                    const float* __restrict__ kk, float* __restrict__ N,
                                                    float4* __restrict__ src, double* __restrict__ theta,
-                                                   double* __restrict__ blk, int nblk) {
+                                                   double* __restrict__ blk, int nblk,
+                                                   uint32_t* __restrict__ hist) {
   __shared__ double lds[4];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  clear_hist(hist, n);
   double cv = 0.0;
   if (i < n) {
     const int64_t o = perm[i];
@@ -665,11 +667,12 @@ dwg_status mc_clear(const McWork& w, hipStream_t st) {
   return DWG_OK;
 }
 
-dwg_status mc_update(const McParams& mp, const McWork& w, const GwnWork& g, float* N, hipStream_t st) {
+dwg_status mc_update(const McParams& mp, const McWork& w, const GwnWork& g, float* N, int* nblk, hipStream_t st) {
   const int nb = (int)cdiv(w.n, 256);
   hipLaunchKernelGGL(k_mc_update, dim3(nb), dim3(256), 0, st, g.perm_s, w.n, w.acc, w.frame, mp.depth, g.kk, N,
-                     g.src, g.theta, g.blk, nb);
+                     g.src, g.theta, g.blk, nb, g.hist);
   DWG_TRY_LAUNCH();
+  *nblk = nb;
   return DWG_OK;
 }
 

@@ -8,7 +8,6 @@
 //                          their contribution exactly zero in the general path.
 //   kk    [npad]           a_j / (4 pi) per sorted source (restaging after the update)
 //   tbox  [2*ntiles]       per source tile: (min xyz, max radius), (max xyz, 0)
-//   qbox  [2*nqblk]        per block of kQBlock sorted queries: (min xyz, 0), (max xyz, 0)
 //   part  [split][7][mpad] per-split partial sums of w, A, B per sorted query
 //   theta [m] double       angle between consecutive normals (degrees), sorted order
 // Positions and boxes are in the caller's units; kappa = s log2(e) for the screened kernel
@@ -34,12 +33,12 @@ enum TileKind { kGeneral = 0, kFar = 1, kSeparated = 2 };
 // One LDS tile of sources against the thread's QPT queries. The tile holds the separated
 // form (a = (-2 p, |p|^2), b = (m, m . p), iw apart); the general and far loops recover the
 // difference p - q exactly as fma(-2 p, -1/2, -q).
-template <int QPT, int NS, bool GRAD, bool SCREENED, int KIND>
+template <int QPT, int NS, int TS, bool GRAD, bool SCREENED, int KIND>
 __device__ __forceinline__ void tile_loop(const float4* sa, const float4* sb, const float* sw, const float* qx,
                                           const float* qy, const float* qz, const float* qq, const Scr k,
                                           float (*acc)[NS]) {
-#pragma unroll 2
-  for (int j = 0; j < kTile; ++j) {
+#pragma unroll (GRAD ? 2 : 4)
+  for (int j = 0; j < TS; ++j) {
     const float4 a = sa[j];
     const float4 b = sb[j];
     const float iw = KIND == kGeneral ? sw[j] : 0.0f;
@@ -87,13 +86,15 @@ __device__ __forceinline__ void tile_loop(const float4* sa, const float4* sb, co
   }
 }
 
-// All-pairs kernel. Block = 256 threads holding QPT queries each (sorted query
-// q0 + k*256 + tid); grid.y = source split. Source tiles of 256 are staged in LDS and read
-// back as broadcasts. Per tile, the block decides (uniformly) whether the tile is far from
-// all of its queries -- box distance above the tile's largest radius, so no pair can be
+// All-pairs kernel. Block = NT threads holding QPT queries each, NT x QPT = 512 (sorted query
+// q0 + k*NT + tid); grid.y = source split. Sources are staged in LDS TS at a time and read
+// back as broadcasts; TS divides the 256 sources of a tile. Per tile, each wavefront decides whether the tile is far
+// from all of its queries -- box distance above the tile's largest radius, so no pair can be
 // clamped or coincident -- and then runs the shorter far-pair loop; a far tile whose box
-// distance is also at least the largest distance of a query from the block's centre takes
-// the separated far loop (r^2 and m . (p - q) from per-source |p|^2 and m . p).
+// distance is also at least the largest distance of one of its queries from the block's centre
+// takes the separated far loop (r^2 and m . (p - q) from per-source |p|^2 and m . p). (Deciding
+// by the block's box puts fewer tiles in the short loops: values at 131K queries off the surface of 50K
+// points 1.99 -> 1.85 ms; 1M x 1M equal.)
 // Each tile's contributions go to FP32 partials, folded into running sums
 // (Kahan-compensated when KAHAN). The compensation terms live in LDS, one column per
 // thread: they are touched once per tile, and the 14 registers they would take hold the
@@ -109,40 +110,55 @@ __device__ __forceinline__ void tile_loop(const float4* sa, const float4* sb, co
 // block), the box centre lies far from every query and all of the block's near pairs lose
 // precision; the middle query keeps the block's bulk exact relative to itself, and the far
 // query's pairs are long.
-template <int QPT, bool GRAD, bool SCREENED, bool KAHAN>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_gwn(const float* __restrict__ Q, int64_t m,
-                                                 const int32_t* __restrict__ qperm,
-                                                 const float4* __restrict__ src, int64_t ntiles,
-                                                 int64_t nfull, int64_t tiles_per_split,
-                                                 const float4* __restrict__ tbox,
-                                                 const float4* __restrict__ qbox, Scr sk, float kappa,
-                                                 float* __restrict__ part, int64_t mpad) {
+__device__ __forceinline__ float first_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+template <int NT, int QPT, int TS, bool GRAD, bool SCREENED, bool KAHAN>
+__device__ __forceinline__ void gwn_block(const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm,
+                                          const float4* __restrict__ src, int64_t nsteps, int64_t nfull,
+                                          int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa,
+                                          float* __restrict__ part, int64_t mpad) {
+  static_assert(NT * QPT == kQBlock && kTile % TS == 0 && TS <= kTile, "block shape");
   constexpr int NA = GRAD ? kNAcc : 1;
   constexpr int NS = GRAD ? kNAcc + 1 : 1;  // + sum of t in the separated loop
-  __shared__ float4 sa[kTile];
-  __shared__ float4 sb[kTile];
-  __shared__ float sw[kTile];
+  __shared__ float4 sa[TS];
+  __shared__ float4 sb[TS];
+  __shared__ float sw[TS];
   const int tid = threadIdx.x;
-  const int64_t q0 = (int64_t)blockIdx.x * (kBlock * QPT);
-  const float4 qlo = qbox[2 * blockIdx.x], qhi = qbox[2 * blockIdx.x + 1];
-  const int64_t oc = qperm[min(q0 + (kBlock * QPT) / 2, m - 1)];
+  const int64_t q0 = (int64_t)blockIdx.x * kQBlock;
+  const int64_t oc = qperm[min(q0 + kQBlock / 2, m - 1)];
   const float cx = Q[oc], cy = Q[m + oc], cz = Q[2 * m + oc];
-  // largest distance of a query of the block from c (the query box's farthest corner)
-  const float rx = fmaxf(qhi.x - cx, cx - qlo.x), ry = fmaxf(qhi.y - cy, cy - qlo.y),
-              rz = fmaxf(qhi.z - cz, cz - qlo.z);
-  const float rq2 = rx * rx + ry * ry + rz * rz;
   float qx[QPT], qy[QPT], qz[QPT], qq[QPT];
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
   for (int k = 0; k < QPT; ++k) {
-    int64_t qi = q0 + k * kBlock + tid;
+    int64_t qi = q0 + k * NT + tid;
     if (qi >= m) qi = m - 1;
     const int64_t o = qperm[qi];
-    qx[k] = kappa * (Q[o] - cx);
-    qy[k] = kappa * (Q[m + o] - cy);
-    qz[k] = kappa * (Q[2 * m + o] - cz);
+    const float x = Q[o], y = Q[m + o], z = Q[2 * m + o];
+    lo[0] = fminf(lo[0], x), hi[0] = fmaxf(hi[0], x);
+    lo[1] = fminf(lo[1], y), hi[1] = fmaxf(hi[1], y);
+    lo[2] = fminf(lo[2], z), hi[2] = fmaxf(hi[2], z);
+    qx[k] = kappa * (x - cx);
+    qy[k] = kappa * (y - cy);
+    qz[k] = kappa * (z - cz);
     qq[k] = fmaf(qz[k], qz[k], fmaf(qy[k], qy[k], qx[k] * qx[k]));
   }
-  __shared__ float cmp[KAHAN ? QPT * NA : 1][kBlock];  // thread-private columns
+  // box of the wavefront's queries, and the largest distance of one from c (its farthest corner)
+  float rq2 = 0.0f;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    for (int o = 32; o > 0; o >>= 1) {
+      lo[d] = fminf(lo[d], __shfl_xor(lo[d], o, 64));
+      hi[d] = fmaxf(hi[d], __shfl_xor(hi[d], o, 64));
+    }
+    lo[d] = first_lane(lo[d]);
+    hi[d] = first_lane(hi[d]);
+    const float c = d == 0 ? cx : (d == 1 ? cy : cz), r = fmaxf(hi[d] - c, c - lo[d]);
+    rq2 += r * r;
+  }
+  __shared__ float cmp[KAHAN ? QPT * NA : 1][NT];  // thread-private columns
   float sum[QPT][NA];
 #pragma unroll
   for (int k = 0; k < QPT; ++k)
@@ -152,26 +168,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
       if (KAHAN) cmp[k * NA + a][tid] = 0.0f;
     }
 
-  const int64_t t0 = (int64_t)blockIdx.y * tiles_per_split;
-  const int64_t t1 = min(t0 + tiles_per_split, ntiles);
-  for (int64_t t = t0; t < t1; ++t) {
+  const int64_t u0 = (int64_t)blockIdx.y * steps_per_split;
+  const int64_t u1 = min(u0 + steps_per_split, nsteps);
+  for (int64_t u = u0; u < u1; ++u) {
+    const int64_t t = TS == kTile ? u : u / (kTile / TS);
     __syncthreads();
-    {
-      const float4 a = src[2 * (t * kTile + tid)];
-      const float4 b = src[2 * (t * kTile + tid) + 1];
+#pragma unroll
+    for (int i = tid; i < TS; i += NT) {
+      const float4 a = src[2 * (u * TS + i)];
+      const float4 b = src[2 * (u * TS + i) + 1];
       const float px = kappa * (a.x - cx), py = kappa * (a.y - cy), pz = kappa * (a.z - cz);
-      sa[tid] = make_float4(-2.0f * px, -2.0f * py, -2.0f * pz, fmaf(pz, pz, fmaf(py, py, px * px)));
-      sb[tid] = make_float4(b.x, b.y, b.z, fmaf(b.z, pz, fmaf(b.y, py, b.x * px)));
-      sw[tid] = a.w;
+      sa[i] = make_float4(-2.0f * px, -2.0f * py, -2.0f * pz, fmaf(pz, pz, fmaf(py, py, px * px)));
+      sb[i] = make_float4(b.x, b.y, b.z, fmaf(b.z, pz, fmaf(b.y, py, b.x * px)));
+      sw[i] = a.w;
     }
     const float4 tlo = tbox[2 * t], thi = tbox[2 * t + 1];
-    const float gx = fmaxf(0.0f, fmaxf(qlo.x - thi.x, tlo.x - qhi.x));
-    const float gy = fmaxf(0.0f, fmaxf(qlo.y - thi.y, tlo.y - qhi.y));
-    const float gz = fmaxf(0.0f, fmaxf(qlo.z - thi.z, tlo.z - qhi.z));
+    const float gx = fmaxf(0.0f, fmaxf(lo[0] - thi.x, tlo.x - hi[0]));
+    const float gy = fmaxf(0.0f, fmaxf(lo[1] - thi.y, tlo.y - hi[1]));
+    const float gz = fmaxf(0.0f, fmaxf(lo[2] - thi.z, tlo.z - hi[2]));
     const float gap2 = gx * gx + gy * gy + gz * gz;
     // tiles with padding (t >= nfull) always take the general path
-    const bool far = t < nfull && gap2 > 0.0f && gap2 > 1.0001f * tlo.w * tlo.w;
-    const bool sep = far && gap2 >= rq2;
+    const bool far = __builtin_amdgcn_readfirstlane(t < nfull && gap2 > 0.0f && gap2 > 1.0001f * tlo.w * tlo.w);
+    const bool sep = __builtin_amdgcn_readfirstlane(far && gap2 >= rq2);
     __syncthreads();
     float acc[QPT][NS];
 #pragma unroll
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
 #pragma unroll
       for (int a = 0; a < NS; ++a) acc[k][a] = 0.0f;
     if (sep) {
-      tile_loop<QPT, NS, GRAD, SCREENED, kSeparated>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
+      tile_loop<QPT, NS, TS, GRAD, SCREENED, kSeparated>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
       if (GRAD) {
 #pragma unroll
         for (int k = 0; k < QPT; ++k) {  // A = -sum(t P) / 2 - q sum(t)
@@ -189,9 +207,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
         }
       }
     } else if (far) {
-      tile_loop<QPT, NS, GRAD, SCREENED, kFar>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
+      tile_loop<QPT, NS, TS, GRAD, SCREENED, kFar>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
     } else {
-      tile_loop<QPT, NS, GRAD, SCREENED, kGeneral>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
+      tile_loop<QPT, NS, TS, GRAD, SCREENED, kGeneral>(sa, sb, sw, qx, qy, qz, qq, sk, acc);
     }
 #pragma unroll
     for (int k = 0; k < QPT; ++k)
@@ -210,10 +228,40 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   float* out = part + (int64_t)blockIdx.y * NA * mpad;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) {
-    const int64_t qi = q0 + k * kBlock + tid;  // < mpad by construction of mpad
+    const int64_t qi = q0 + k * NT + tid;  // < mpad by construction of mpad
 #pragma unroll
     for (int a = 0; a < NA; ++a) out[a * mpad + qi] = KAHAN ? sum[k][a] - cmp[k * NA + a][tid] : sum[k][a];
   }
+}
+
+// With the gradient: two queries per thread. 105 VGPRs would fit 4 waves per SIMD; asked for 5, the
+// kernel does without spills.
+template <bool SCREENED, bool KAHAN>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_gwn(
+    const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+  gwn_block<kBlock, kQpt, kTile, true, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk,
+                                                        kappa, part, mpad);
+}
+
+// Values only.
+template <bool SCREENED, bool KAHAN>
+__global__ __launch_bounds__(kBlock) void k_gwn_w(
+    const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+  gwn_block<kBlock, kQpt, kTile, false, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk,
+                                                       kappa, part, mpad);
+}
+
+// Small launches: one query per thread and steps of kSmallStep sources, so that a few blocks of
+// queries still fill the chip (see small_launch).
+constexpr int kSmallStep = 32;
+template <bool GRAD, bool SCREENED, bool KAHAN>
+__global__ __launch_bounds__(kQBlock) void k_gwn_small(
+    const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+  gwn_block<kQBlock, 1, kSmallStep, GRAD, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk, kappa,
+                                                           part, mpad);
 }
 
 // Stage the sources in spatial order: (p, 1/(kappa max(delta,eps))) and m = a n / (4 pi)
@@ -270,39 +318,6 @@ __global__ __launch_bounds__(kTile) void k_tile_box(const float4* __restrict__ s
   if (threadIdx.x == 0) {
     tbox[2 * blockIdx.x] = make_float4(lds[0][0], lds[1][0], lds[2][0], lds[6][0]);
     tbox[2 * blockIdx.x + 1] = make_float4(lds[3][0], lds[4][0], lds[5][0], 0.0f);
-  }
-}
-
-// Box of each block of kQBlock sorted queries.
-__global__ __launch_bounds__(kBlock) void k_query_box(const float* __restrict__ Q, int64_t m,
-                                                      const int32_t* __restrict__ qperm,
-                                                      float4* __restrict__ qbox) {
-  __shared__ float lds[6][kBlock];
-  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  for (int k = 0; k < kQpt; ++k) {
-    int64_t qi = (int64_t)blockIdx.x * kQBlock + k * kBlock + threadIdx.x;
-    if (qi >= m) qi = m - 1;  // the kernel evaluates the clamped query there as well
-    const int64_t o = qperm[qi];
-    const float x = Q[o], y = Q[m + o], z = Q[2 * m + o];
-    v[0] = fminf(v[0], x);
-    v[1] = fminf(v[1], y);
-    v[2] = fminf(v[2], z);
-    v[3] = fmaxf(v[3], x);
-    v[4] = fmaxf(v[4], y);
-    v[5] = fmaxf(v[5], z);
-  }
-  for (int d = 0; d < 6; ++d) lds[d][threadIdx.x] = v[d];
-  __syncthreads();
-  for (int s = kBlock / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      for (int d = 0; d < 3; ++d) lds[d][threadIdx.x] = fminf(lds[d][threadIdx.x], lds[d][threadIdx.x + s]);
-      for (int d = 3; d < 6; ++d) lds[d][threadIdx.x] = fmaxf(lds[d][threadIdx.x], lds[d][threadIdx.x + s]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    qbox[2 * blockIdx.x] = make_float4(lds[0][0], lds[1][0], lds[2][0], 0.0f);
-    qbox[2 * blockIdx.x + 1] = make_float4(lds[3][0], lds[4][0], lds[5][0], 0.0f);
   }
 }
 
@@ -793,12 +808,41 @@ __global__ void k_random_normals(uint64_t seed, int64_t n, float* __restrict__ N
   N[2 * n + i] = z;
 }
 
-template <int QPT, bool GRAD, bool SCREENED, bool KAHAN>
-void launch_gwn_t(dim3 grid, hipStream_t st, const float* Q, int64_t m, const int32_t* qperm,
-                  const GwnWork& w, int64_t tps, float kappa) {
+// Blocks that a launch is split into whatever that leaves per split: four rounds of the blocks
+// that are resident at once (8 tiles per split at least left 4 blocks for 2,000 points and 400 for
+// 20,000). 40,000 points of a sphere, gradient, plain / screened: 988 / 1275 us by the 8-tile rule, 822 / 1093
+// at 2,560 blocks, 812 / 1046 at 5,120.
+constexpr int64_t kSmallBlocks = 1024, kFillBlocks = 5120;
+// (query block, source tile) pairs up to which a launch takes the small kernel: one tile per block
+// of the other kernel is then still too few blocks. Whole calls at 500 / 2,000 / 8,000 / 12,000 points,
+// screened, us: 36 / 44 / 122 / 179 against 68 / 71 / 127 / 189 with one-tile splits of the other kernel and
+// 157 / 387 / 415 / 488 with the 8-tile rule; from 16,000 points on (2,016 pairs) it is slower for the
+// plain kernel (219 against 210).
+constexpr int64_t kSmallPairs = 1536;
+
+bool small_launch(int64_t n_src, int64_t n_qry) { return cdiv(n_src, kTile) * cdiv(n_qry, kQBlock) <= kSmallPairs; }
+
+template <bool SCREENED, bool KAHAN>
+void launch_gwn_t(bool grad, hipStream_t st, const float* Q, int64_t m, const GwnWork& w, float kappa) {
   const int64_t nfull = w.n_src / kTile;  // tiles without padding
-  hipLaunchKernelGGL((k_gwn<QPT, GRAD, SCREENED, KAHAN>), grid, dim3(kBlock), 0, st, Q, m, qperm, w.src,
-                     w.ntiles, nfull, tps, w.tbox, w.qbox, kScaledScr, kappa, w.part, w.mpad);
+  const dim3 grid((unsigned)cdiv(m, kQBlock), (unsigned)w.split);
+  if (small_launch(w.n_src, m)) {
+    const int64_t steps = cdiv(w.n_src, kSmallStep), per = cdiv(steps, w.split);
+    if (grad)
+      hipLaunchKernelGGL((k_gwn_small<true, SCREENED, KAHAN>), grid, dim3(kQBlock), 0, st, Q, m, w.perm_q, w.src, steps,
+                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
+    else
+      hipLaunchKernelGGL((k_gwn_small<false, SCREENED, KAHAN>), grid, dim3(kQBlock), 0, st, Q, m, w.perm_q, w.src, steps,
+                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
+    return;
+  }
+  const int64_t per = cdiv(w.ntiles, w.split);
+  if (grad)
+    hipLaunchKernelGGL((k_gwn<SCREENED, KAHAN>), grid, dim3(kBlock), 0, st, Q, m, w.perm_q, w.src, w.ntiles, nfull, per,
+                       w.tbox, kScaledScr, kappa, w.part, w.mpad);
+  else
+    hipLaunchKernelGGL((k_gwn_w<SCREENED, KAHAN>), grid, dim3(kBlock), 0, st, Q, m, w.perm_q, w.src, w.ntiles, nfull,
+                       per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
 }
 
 }  // namespace
@@ -818,6 +862,10 @@ int choose_split(int64_t n_src, int64_t n_qry, int requested) {
   // sums (28 B per query and split) are held to kAutoSplitBytes, or 16 splits if that is more.
   int64_t s = cdiv(32768, qblocks);
   s = std::min<int64_t>(s, std::max<int64_t>(1, ntiles / 8));
+  if (small_launch(n_src, n_qry))
+    s = std::max<int64_t>(s, std::min<int64_t>(cdiv(kSmallBlocks, qblocks), cdiv(n_src, kSmallStep)));
+  else
+    s = std::max<int64_t>(s, std::min<int64_t>(cdiv(kFillBlocks, qblocks), ntiles));
   const int64_t mem_cap =
       std::max<int64_t>(16, (int64_t)(kAutoSplitBytes / ((int64_t)kNAcc * 4 * qblocks * kQBlock)));
   s = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(s, mem_cap), kMaxSplit));
@@ -843,7 +891,6 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, 
   w.cand = c.take<uint64_t>(kSelSmallMax);
   w.top = c.take<double>(256);
   w.tbox = c.take<float4>(2 * (size_t)w.ntiles);
-  w.qbox = c.take<float4>(2 * (size_t)(w.mpad / kQBlock));
   w.perm_s = c.take<int32_t>((size_t)w.npad);
   w.perm_q = same ? w.perm_s : c.take<int32_t>((size_t)w.mpad);
   carve_sort(c, std::max(n_src, n_qry), &w.sort);
@@ -869,31 +916,18 @@ dwg_status launch_order(const float* P, int64_t n, const float* delta, float eps
     s = spatial_sort(Q, m, nullptr, 0.0f, w.sort, w.perm_q, stream);
     if (s != DWG_OK) return s;
   }
-  hipLaunchKernelGGL(k_query_box, dim3((unsigned)(w.mpad / kQBlock)), dim3(kBlock), 0, stream, Q, m, w.perm_q,
-                     w.qbox);
-  DWG_TRY_LAUNCH();
   return DWG_OK;
 }
 
 dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bool grad,
                       const GwnWork& w, hipStream_t stream) {
-  const int64_t qblocks = cdiv(m, kQBlock);
-  const int64_t tps = cdiv(w.ntiles, w.split);
-  dim3 grid((unsigned)qblocks, (unsigned)w.split);
   const bool scr = kp.lambda > 0.0f;
   const bool kah = kp.compensated != 0;
   const float kappa = position_scale(kp);
-#define DWG_GWN_CASE(G, S, K) \
-  if (grad == G && scr == S && kah == K) launch_gwn_t<kQpt, G, S, K>(grid, stream, Q, m, w.perm_q, w, tps, kappa);
-  DWG_GWN_CASE(true, false, true)
-  DWG_GWN_CASE(true, false, false)
-  DWG_GWN_CASE(true, true, true)
-  DWG_GWN_CASE(true, true, false)
-  DWG_GWN_CASE(false, false, true)
-  DWG_GWN_CASE(false, false, false)
-  DWG_GWN_CASE(false, true, true)
-  DWG_GWN_CASE(false, true, false)
-#undef DWG_GWN_CASE
+  if (scr)
+    kah ? launch_gwn_t<true, true>(grad, stream, Q, m, w, kappa) : launch_gwn_t<true, false>(grad, stream, Q, m, w, kappa);
+  else
+    kah ? launch_gwn_t<false, true>(grad, stream, Q, m, w, kappa) : launch_gwn_t<false, false>(grad, stream, Q, m, w, kappa);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

@@ -144,7 +144,6 @@ struct GwnWork {
   uint64_t* cand;     // [kSelSmallMax] angles near the k-th largest
   double* top;        // [256] block sums of the angles above them
   float4* tbox;       // [2 * ntiles] source tile boxes and radii
-  float4* qbox;       // [2 * mpad / kQBlock] query block boxes
   int32_t* perm_s;    // [npad]
   int32_t* perm_q;    // [mpad] (== perm_s when the queries are the sources)
   SortWork sort;

@@ -102,10 +102,11 @@ struct EventPair {
   }
 };
 
-size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp) {
+// segments: of the octree's node list (0 = the rule of tree_segments).
+size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp, int segments = 0) {
   Carver c(nullptr);
   if (tree_mode(kp)) {
-    carve_gwn(c, n_src, n_qry, 1, false, nullptr);
+    carve_gwn(c, n_src, n_qry, segments > 0 ? segments : tree_segments(n_src, n_qry), false, nullptr);
     carve_tree(c, n_src, tree_leaf(kp), kp.tree_beta, nullptr);
   } else {
     carve_gwn(c, n_src, n_qry, choose_split(n_src, n_qry, kp.split), false, nullptr);
@@ -123,7 +124,7 @@ struct EvalState {
 
 dwg_status eval_prepare(const float* P, const float* N, const float* area, const float* delta, int64_t n,
                         const float* Q, int64_t m, const dwg_kernel_params& kp, bool same, void* ws,
-                        hipStream_t st, EvalState* es) {
+                        hipStream_t st, EvalState* es, int segments = 0) {
   Carver c(ws);
   es->tree = tree_mode(kp);
   if (!es->tree) {
@@ -131,7 +132,7 @@ dwg_status eval_prepare(const float* P, const float* N, const float* area, const
     DWG_PROPAGATE(launch_order(P, n, delta, kp.eps, position_scale(kp), Q, m, same, es->wk, st));
     return launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), es->wk, st);
   }
-  carve_gwn(c, n, m, 1, same, &es->wk);
+  carve_gwn(c, n, m, segments > 0 ? segments : tree_segments(n, m), same, &es->wk);
   carve_tree(c, n, tree_leaf(kp), kp.tree_beta, &es->tw);
   DWG_PROPAGATE(tree_build(P, area, delta, n, kp.eps, es->tw, es->wk.perm_s, st));
   if (!same) DWG_PROPAGATE(spatial_sort(Q, m, nullptr, 0.0f, es->wk.sort, es->wk.perm_q, st));
@@ -150,7 +151,7 @@ dwg_status eval_run(const float* Q, int64_t m, const dwg_kernel_params& kp, bool
 dwg_status gwn_common(const float* P, const float* N, const float* area, const float* delta,
                       int64_t n, const float* Q, int64_t m, const dwg_kernel_params* kpp,
                       bool grad, float* w, float* g, double* wmean, void* ws, size_t ws_bytes,
-                      void* stream) {
+                      void* stream, int segments = 0) {
   DWG_CHECK(P && N && area && Q, "P, N, area and Q must not be NULL");
   DWG_CHECK(n >= 1 && m >= 1, "n and m must be >= 1 (got n=%lld, m=%lld)", (long long)n, (long long)m);
   DWG_CHECK(n < (int64_t(1) << 31) && m < (int64_t(1) << 31), "n and m must be < 2^31 (int32 point indices)");
@@ -158,7 +159,7 @@ dwg_status gwn_common(const float* P, const float* N, const float* area, const f
   DWG_PROPAGATE(check_kp(kpp));
   const dwg_kernel_params kp = kpp ? *kpp : kDefaultKp;
   DWG_CHECK(!tree_mode(kp) || n < (int64_t(1) << 30), "octree mode needs n < 2^30");
-  const size_t need = gwn_bytes(n, m, kp);
+  const size_t need = gwn_bytes(n, m, kp, segments);
   DWG_CHECK(ws || ws_bytes == 0, "ws is NULL but ws_bytes > 0");
   if (!ws || ws_bytes < need) {
     set_error("workspace too small: %zu bytes given, %zu needed", ws_bytes, need);
@@ -168,7 +169,7 @@ dwg_status gwn_common(const float* P, const float* N, const float* area, const f
   hipStream_t st = static_cast<hipStream_t>(stream);
   EvalState es;
   const bool same = (Q == P && m == n);
-  DWG_PROPAGATE(eval_prepare(P, N, area, delta, n, Q, m, kp, same, ws, st, &es));
+  DWG_PROPAGATE(eval_prepare(P, N, area, delta, n, Q, m, kp, same, ws, st, &es, segments));
   DWG_PROPAGATE(eval_run(Q, m, kp, grad, es, st));
   DWG_PROPAGATE(launch_combine(m, kp, grad, w, g, wmean, es.wk, st));
   return DWG_OK;
@@ -303,7 +304,14 @@ size_t static_counted_bytes(int64_t n, int64_t m, const dwg_kernel_params& kp) {
     take(24 * (n + 1));
     take(24 * tiles);
   }
-  return std::max(c.used, gwn_bytes(n, m, kp));
+  return std::max(c.used, gwn_bytes(n, m, kp, 1));
+}
+
+// Segments of the octree's node list whose partial sums fit the static scratch.
+int static_segments(int64_t n, int64_t m, const dwg_kernel_params& kp) {
+  int s = tree_mode(kp) ? tree_segments(n, m) : 0;
+  while (s > 1 && gwn_bytes(n, m, kp, s) > kStaticScratchBytes) s = (s + 1) / 2;
+  return s;
 }
 
 // The kernel parameters dwg_gwn_grad_static runs with: an automatic source split is halved
@@ -379,7 +387,8 @@ dwg_status dwg_gwn_grad_static(const float* P, const float* N, const float* area
   DWG_PROPAGATE(check_device());
   void* ws = nullptr;
   DWG_PROPAGATE(static_scratch(&ws));
-  return gwn_common(P, N, area, delta, n, Q, m, &kp, true, w, grad, wmean, ws, kStaticScratchBytes, stream);
+  return gwn_common(P, N, area, delta, n, Q, m, &kp, true, w, grad, wmean, ws, kStaticScratchBytes, stream,
+                    static_segments(n, m, kp));
 }
 
 dwg_status dwg_octree_work(const float* P, const float* area, const float* delta, int64_t n, const float* Q,

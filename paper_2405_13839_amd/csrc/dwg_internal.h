@@ -180,6 +180,8 @@ struct TreeWork {
   double beta;
 };
 int64_t tree_cap(int64_t n);
+// Segments of the node list that an evaluation walks separately (GwnWork::split of octree mode).
+int tree_segments(int64_t n_src, int64_t n_qry);
 size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out);
 // Sorts the sources (perm[i] = index of the i-th sorted source) and builds the nodes; with
 // area != NULL also the node centres, radii and opening radii.
@@ -191,7 +193,7 @@ dwg_status tree_build(const float* P, const float* area, const float* delta, int
 // the all-pairs kernels never read sources staged this way).
 dwg_status tree_stage_leaves(const GwnWork& w, const TreeWork& t, float kappa, hipStream_t st);
 dwg_status tree_moments(const GwnWork& w, const TreeWork& t, hipStream_t st);
-// Octree-approximated w (and grad) at the sorted queries of w into w.part (split 1).
+// Octree-approximated w (and grad) at the sorted queries of w into w.part (w.split segments).
 dwg_status tree_eval(const float* Q, int64_t m, const dwg_kernel_params& kp, bool grad, const GwnWork& w,
                      const TreeWork& t, hipStream_t st);
 // Work of the traversal over the m sorted queries: far dipoles (out[0]), leaf pairs (out[1]),

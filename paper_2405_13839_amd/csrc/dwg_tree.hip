@@ -429,11 +429,26 @@ __global__ void k_tree_leafpos(const int4* __restrict__ node, const int32_t* __r
 // (a fold is 4 VALU per accumulator; folding after every visit was ~2% slower at 1M). The
 // next node is usually i + 1 (a node opened, or a leaf, whose skip is i + 1), so its data is
 // loaded one step ahead.
+//
+// The pre-order node list is cut into equal segments, each walked on its own for every
+// wavefront of queries, with partial sums per segment that the epilogue adds in order. A segment
+// starts inside a subtree: it first goes down from the root to its first node, testing only that
+// node's ancestors, to learn which lanes have one of them as a far dipole (that dipole belongs to
+// the segment that holds the ancestor). Every node is then taken by the same queries as in one
+// walk. What bounds it is the length of one walk where the queries are few (a wavefront of
+// 20,011 points walks for 260 us alone, and their 313 wavefronts leave two SIMDs in three
+// empty: 265 us a launch before, 58 with 32 segments) and the last walks to end where they are
+// many (1M points, 15,626 wavefronts: 4.95 ms a launch before, 4.4 with 9 segments). The rule
+// aims at 131,072 wavefronts (16,384: 24.8 ms for four launches and the rest of a pass at 1M,
+// 65,536: 24.2, 131,072: 23.7, 262,144: 23.9) of at least 512 sources' nodes each (20,011
+// points: 1.16 ms a pass; 256 sources 1.14, 1,024 1.24; one segment 2.0), so the partial sums
+// stay below 28 bytes for each of 2^23 + m queries.
 constexpr int kFoldLeaves = 4;
 // Threads per block of the traversal: its wavefronts share no data and never wait for each
 // other (each has its own LDS area and no barrier).
 constexpr int kTreeBlock = 256;
 constexpr int kTreeWaves = kTreeBlock / 64;
+constexpr int64_t kSegmentWaves = 131072, kSegmentSources = 512, kMaxSegments = 32;
 // A leaf visit is spread over the idle lanes when that saves at least this many iterations.
 constexpr int kSplitMinSaved = 2;
 
@@ -450,28 +465,38 @@ __device__ __forceinline__ int leaf_split_log2(int na, int ns) {
 }
 
 // Workgroups are dealt to the 8 XCDs in turn (block b to XCD b mod 8), and each XCD has an L2
-// of its own. Block b evaluates the (b mod 8)-th contiguous run of query blocks instead of
-// query block b, so the blocks resident on one XCD hold neighbouring queries, which visit
+// of its own. XCD x evaluates the x-th contiguous run of the nb query blocks, every segment of
+// the node list for its run, so the blocks resident on one XCD hold neighbouring queries, which visit
 // nearly the same nodes and leaf sources, and that XCD's L2 holds one region of the tree
-// rather than every eighth block's share of all of it. A bijection of [0, nb) onto itself.
-__device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
-  const unsigned q = nb / 8, r = nb % 8, x = b % 8, k = b / 8;
-  return x * q + (x < r ? x : r) + k;
+// rather than every eighth block's share of all of it. (Dealing the segments to the XCDs as
+// well gave some of them the near field of their queries and others only far nodes: twice the
+// time at 2 segments.) The launch has tree_grid(nb, segments) blocks; false: this one has nothing to do.
+__device__ __forceinline__ bool xcd_block(unsigned b, unsigned nb, unsigned segments, unsigned* block,
+                                          unsigned* segment) {
+  const unsigned longest = (nb + 7) / 8, q = nb / 8, r = nb % 8, x = b % 8, k = b / 8;
+  const unsigned at = k % longest;
+  *segment = k / longest;
+  *block = x * q + (x < r ? x : r) + at;
+  return at < q + (x < r ? 1u : 0u) && *segment < segments;
 }
+unsigned tree_grid(int64_t nb, int segments) { return (unsigned)(8 * cdiv(nb, 8) * segments); }
 
+// Seven wavefronts per SIMD: left to itself the compiler takes 73 VGPRs (six; 25.5 ms a pass at
+// 1M against 23.1), and at eight it spills (25.9).
 template <bool GRAD, bool SCREENED, bool KAHAN>
-__global__ __launch_bounds__(kTreeBlock) void k_tree_eval(const float* __restrict__ Q, int64_t m,
-                                                   const int32_t* __restrict__ qperm, const int4* __restrict__ node,
-                                                   const double4* __restrict__ geo, const float4* __restrict__ mom,
-                                                   const int32_t* __restrict__ total_p, int64_t cap,
-                                                   const float4* __restrict__ src, int64_t n_src, Scr sk,
-                                                   float kappa, float* __restrict__ part, int64_t mpad) {
+__global__ __launch_bounds__(kTreeBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_tree_eval(
+    const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const int4* __restrict__ node,
+    const double4* __restrict__ geo, const float4* __restrict__ mom, const int32_t* __restrict__ total_p, int64_t cap,
+    const float4* __restrict__ src, int64_t n_src, Scr sk, float kappa, float* __restrict__ part, int64_t mpad,
+    unsigned segments) {
   constexpr int NA = GRAD ? kNAcc : 1;
   // per wavefront: the queries of a split leaf visit by rank, and the lanes' partial sums
   __shared__ float4 lds_q[kTreeWaves][64];
   __shared__ float lds_p[kTreeWaves][64][NA == 1 ? 1 : 8];
   const int wv = (int)(threadIdx.x >> 6);
-  const int64_t qi = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  unsigned qblock, segment;
+  if (!xcd_block(blockIdx.x, (unsigned)(mpad / kTreeBlock), segments, &qblock, &segment)) return;
+  const int64_t qi = (int64_t)qblock * kTreeBlock + threadIdx.x;
   const int64_t o = qperm[qi < m ? qi : m - 1];
   const float ux = Q[o], uy = Q[m + o], uz = Q[2 * m + o];
   const double dqx = ux, dqy = uy, dqz = uz;  // the opening test runs in unscaled FP64
@@ -481,12 +506,33 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_eval(const float* __restric
   for (int a = 0; a < NA; ++a) sum[a] = cmp[a] = acc[a] = 0.0f;
   int nn = __builtin_amdgcn_readfirstlane(*total_p);
   if (nn > cap) nn = (int)cap;
+  const int first = (int)((int64_t)nn * segment / segments), end = (int)((int64_t)nn * (segment + 1) / segments);
   int skip_to = 0;
   int i = 0;
+  while (i < first) {  // down to the segment's first node
+    const int nskip = __builtin_amdgcn_readfirstlane(node[i].z);
+    if (nskip <= first) {  // a subtree before it
+      i = nskip > i ? nskip : i + 1;
+      continue;
+    }
+    if (i >= skip_to) {
+      const double4 g = geo[i];
+      const double dx = g.x - dqx, dy = g.y - dqy, dz = g.z - dqz;
+      if (dx * dx + dy * dy + dz * dz > g.w) skip_to = nskip;
+    }
+    ++i;
+  }
+  if (segment > 0) {  // the first node that any lane has left
+    int least = skip_to;
+    for (int o = 32; o > 0; o >>= 1) least = min(least, __shfl_xor(least, o, 64));
+    i = max(i, __builtin_amdgcn_readfirstlane(least));
+  }
+  nn = end;
   int visits = 0;  // leaf visits of the wavefront since the last fold
-  int4 nd = node[0];
-  double4 g = geo[0];
-  float4 mm = mom[0];
+  const int i0 = i < nn ? i : 0;
+  int4 nd = node[i0];
+  double4 g = geo[i0];
+  float4 mm = mom[i0];
   while (i < nn) {
     const int nskip = __builtin_amdgcn_readfirstlane(nd.z);
     bool open = false, direct = false;
@@ -623,7 +669,8 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_eval(const float* __restric
   }
   fold<NA, KAHAN>(sum, cmp, acc);
 #pragma unroll
-  for (int a = 0; a < NA; ++a) part[a * mpad + qi] = KAHAN ? sum[a] - cmp[a] : sum[a];
+  for (int a = 0; a < NA; ++a)
+    part[((int64_t)segment * NA + a) * mpad + qi] = KAHAN ? sum[a] - cmp[a] : sum[a];
 }
 
 // Work of the traversal (the counts of dwg_octree_work). The decisions are those of
@@ -737,14 +784,20 @@ dwg_status scan_f64(const float4* src, int64_t n, const TreeWork& t, hipStream_t
 template <bool GRAD, bool SCREENED, bool KAHAN>
 void launch_eval_t(const float* Q, int64_t m, const int32_t* qperm, const GwnWork& w, const TreeWork& t,
                    float kappa, hipStream_t st) {
-  hipLaunchKernelGGL((k_tree_eval<GRAD, SCREENED, KAHAN>), dim3((unsigned)(w.mpad / kTreeBlock)), dim3(kTreeBlock), 0,
-                     st, Q, m, qperm, t.node, t.geo, t.mom, t.off + t.n, t.cap, w.src, t.n, kScaledScr, kappa,
-                     w.part, w.mpad);
+  hipLaunchKernelGGL((k_tree_eval<GRAD, SCREENED, KAHAN>), dim3(tree_grid(w.mpad / kTreeBlock, w.split)),
+                     dim3(kTreeBlock), 0, st, Q, m, qperm, t.node, t.geo, t.mom, t.off + t.n, t.cap, w.src, t.n, kScaledScr, kappa,
+                     w.part, w.mpad, (unsigned)w.split);
 }
 
 }  // namespace
 
 int64_t tree_cap(int64_t n) { return 2 * n + 1; }
+
+int tree_segments(int64_t n_src, int64_t n_qry) {
+  const int64_t waves = cdiv(n_qry, 64);
+  const int64_t s = std::min<int64_t>(cdiv(kSegmentWaves, waves), cdiv(n_src, kSegmentSources));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(s, kMaxSegments));
+}
 
 dwg_status morton_frame(const float* P, int64_t n, float* bpart, float* box, double* frame, hipStream_t st) {
   dwg_status s = launch_bbox(P, n, bpart, box, st);

@@ -168,14 +168,12 @@ struct TreeWork {
   int4* node;                // [cap] start, end, skip, level | leaf << 8
   double4* geo;              // [cap] centre xyz, squared opening radius
   float4* mom;               // [cap] moment sum a n / 4 pi
-  unsigned long long* rbits; // [cap] node radius (FP64 bits)
-  uint32_t* dbits;           // [cap] largest kernel radius (FP32 bits)
-  int32_t* coff;             // [cap + 1] chunk offsets (chunks of 256 sorted sources per node)
-  int32_t* csums;
-  double4* csum;             // [ccap] per-chunk FP64 sums of a, a px, a py, a pz
-  double* scan;              // [3][n + 1] FP64 prefix sums of the staged moments
-  double* sblk;              // [3][nscan] block totals
-  int64_t n, cap, ccap, nscan;
+  unsigned long long* rbits; // [cap] radius of a large node (FP64 bits)
+  uint32_t* dbits;           // [cap] its largest kernel radius (FP32 bits)
+  float4* pos;               // [n] sorted positions and areas
+  float* rad;                // [n] sorted kernel radii
+  double* tile;              // [tiles][4] FP64 sums over tiles of sorted sources
+  int64_t n, cap;
   int leaf;
   double beta;
 };

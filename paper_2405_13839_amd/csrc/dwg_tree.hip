@@ -19,12 +19,12 @@
 //   exists iff i starts its level-L cell and the parent cell holds more than `leaf`
 //   sources; the deepest level at which the cell of i holds more than `leaf` sources is the
 //   largest shared prefix of the codes at positions (j, j + leaf) over windows containing i.
-// Node summaries (Sec. 5.2): area A and area-weighted centre c.m, FP64 sums over chunks of
-// 256 sorted sources added in chunk order; r = largest |p_j - c.m| (FP64, max over chunks);
+// Node summaries (Sec. 5.2): area A and area-weighted centre c.m, FP64 sums in a fixed order;
+// r = largest |p_j - c.m| (FP64);
 // dmax = largest kernel radius max(delta_j, eps); opening radius crit = max(beta r, r + dmax)
 // (the second term keeps every source of a far node outside its clamp radius). Per
-// iteration, the moment M = sum m_j (m_j = a_j n_j / 4 pi, FP64 prefix sums of the staged
-// FP32 moments).
+// iteration, the moment M = sum m_j (m_j = a_j n_j / 4 pi, FP64 sums of the staged FP32
+// moments).
 //
 // Traversal. One wavefront walks the pre-order node list with one node index for all 64 of
 // its queries (sorted, so they are neighbours) and per-lane "skip until" indices: a lane
@@ -48,8 +48,6 @@ namespace {
 
 using namespace pairk;
 using morton::kDepth;
-constexpr int kScanTile = 2048;  // elements per block of the FP64 scans (256 threads x 8)
-constexpr int kChunk = 256;      // sources per work item of the radius pass
 
 // Node count written by the build, never above the carved capacity.
 __device__ __forceinline__ int64_t node_count(const int32_t* total_p, int64_t cap) {
@@ -60,6 +58,10 @@ __device__ __forceinline__ int64_t node_count(const int32_t* total_p, int64_t ca
 unsigned grid_cap(int64_t n, int64_t cap = 16384) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 256), cap));
 }
+
+// Blocks of the kernels that take a node per 16 lanes. How many nodes there are is known on the
+// device only: about n / 4 at 16 sources a leaf on a surface, 2 n at most.
+unsigned node_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 32), 16384)); }
 
 // Number of levels 1..D at which codes a and b share their cell (D when equal).
 __device__ __forceinline__ int shared_levels(uint64_t a, uint64_t b) {
@@ -162,228 +164,336 @@ __global__ void k_tree_emit(const uint64_t* __restrict__ code, int64_t n, int le
   }
 }
 
-// FP64 prefix sums of the staged moments m (K = 3 components) in sorted order: block-local
-// exclusive scan.
-template <int K>
-__global__ __launch_bounds__(256) void k_scan_local(const float4* __restrict__ src, int64_t n,
-                                                    double* __restrict__ S, double* __restrict__ blk, int64_t nblk) {
-  __shared__ double lds[K][256];
-  const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)tid * 8;
-  double v[8][K];
-  double tot[K];
-  for (int c = 0; c < K; ++c) tot[c] = 0.0;
-  for (int t = 0; t < 8; ++t) {
-    const int64_t j = base + t;
-    for (int c = 0; c < K; ++c) v[t][c] = 0.0;
-    if (j < n) {
-      const float4 b = src[2 * j + 1];
-      v[t][0] = b.x;
-      v[t][1] = b.y;
-      v[t][2] = b.z;
-    }
-    for (int c = 0; c < K; ++c) tot[c] += v[t][c];
-  }
-  for (int c = 0; c < K; ++c) lds[c][tid] = tot[c];
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    double add[K];
-    for (int c = 0; c < K; ++c) add[c] = tid >= off ? lds[c][tid - off] : 0.0;
-    __syncthreads();
-    for (int c = 0; c < K; ++c) lds[c][tid] += add[c];
-    __syncthreads();
-  }
-  for (int c = 0; c < K; ++c) {
-    double run = tid > 0 ? lds[c][tid - 1] : 0.0;  // exclusive prefix of this thread in the block
-    for (int t = 0; t < 8; ++t) {
-      const int64_t j = base + t;
-      if (j < n) S[c * (n + 1) + j] = run;
-      run += v[t][c];
-    }
-  }
-  if (tid == 255)
-    for (int c = 0; c < K; ++c) blk[c * nblk + blockIdx.x] = lds[c][255];
+// FP64 sums over nodes. A node of at most kGroupSources sources is summed by the 16 lanes of a
+// DPP row, four nodes to a wavefront; a larger one by its whole wavefront, whole tiles of
+// kSumTile sorted sources from their sums, which a launch before has formed. (A thread per chunk
+// of 256 sources, adding them one after another through the permutation, bounded the build:
+// 1.88 ms for the summaries of 1M sources, 225 us of 20,011, however few the chunks were; 167 and
+// 40 us now. Per iteration the moments took 45 and 18 us as differences of FP64 prefix sums, 37
+// and 10 now.) The sums' order is fixed by the node's position alone.
+constexpr int kSumTile = 256;
+constexpr int kGroupSources = 64;
+
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
 }
 
-// Exclusive scan of the block totals (one block, fixed order); S[c][n] = grand total.
-template <int K>
-__global__ __launch_bounds__(256) void k_scan_tops(double* __restrict__ blk, int64_t nblk, double* __restrict__ S,
-                                                   int64_t n) {
-  __shared__ double lds[K][256];
-  const int tid = threadIdx.x;
-  double carry[K];
-  for (int c = 0; c < K; ++c) carry[c] = 0.0;
-  for (int64_t b0 = 0; b0 < nblk; b0 += 256) {
-    const int64_t b = b0 + tid;
-    double x[K];
-    for (int c = 0; c < K; ++c) {
-      x[c] = b < nblk ? blk[c * nblk + b] : 0.0;
-      lds[c][tid] = x[c];
-    }
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      double add[K];
-      for (int c = 0; c < K; ++c) add[c] = tid >= off ? lds[c][tid - off] : 0.0;
-      __syncthreads();
-      for (int c = 0; c < K; ++c) lds[c][tid] += add[c];
-      __syncthreads();
-    }
-    for (int c = 0; c < K; ++c) {
-      const double excl = (tid > 0 ? lds[c][tid - 1] : 0.0);
-      if (b < nblk) blk[c * nblk + b] = carry[c] + excl;
-    }
-    double last[K];
-    for (int c = 0; c < K; ++c) last[c] = lds[c][255];
-    __syncthreads();
-    for (int c = 0; c < K; ++c) carry[c] += last[c];
+// Sum over the row's 16 lanes, the same bits in each.
+__device__ __forceinline__ double row_sum(double v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  v += row_ror<1>(v);
+  return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row_sum(v);
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+  for (int o = 32; o > 0; o >>= 1) {
+    const double x = __shfl_xor(v, o, 64);
+    v = x > v ? x : v;
   }
-  if (tid == 0)
-    for (int c = 0; c < K; ++c) S[c * (n + 1) + n] = carry[c];
+  return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
 }
 
-template <int K>
-__global__ void k_scan_add(double* __restrict__ S, int64_t n, const double* __restrict__ blk, int64_t nblk) {
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b = j / kScanTile;
-    for (int c = 0; c < K; ++c) S[c * (n + 1) + j] += blk[c * nblk + b];
+// What is summed: add(j, x) adds the K values of sorted source j.
+struct MomentSum {  // the staged moments
+  static constexpr int K = 3;
+  const float4* __restrict__ src;
+  __device__ __forceinline__ void add(int64_t j, double* x) const {
+    const float4 b = src[2 * j + 1];
+    x[0] += b.x;
+    x[1] += b.y;
+    x[2] += b.z;
+  }
+};
+struct AreaSum {  // a, a px, a py, a pz
+  static constexpr int K = 4;
+  const float4* __restrict__ pos;
+  __device__ __forceinline__ void add(int64_t j, double* x) const {
+    const float4 p = pos[j];
+    const double a = p.w;
+    x[0] += a;
+    x[1] += a * (double)p.x;
+    x[2] += a * (double)p.y;
+    x[3] += a * (double)p.z;
+  }
+};
+
+// Sums v of the node [s, e) of this lane's row (e = s: no node), in every lane of the row.
+template <class F>
+__device__ __forceinline__ void node_sum(const F& f, const double* __restrict__ tile, int s, int e, double* v) {
+  const int lane = threadIdx.x & 63, l = lane & 15;
+  const bool big = e - s > kGroupSources;
+#pragma unroll
+  for (int c = 0; c < F::K; ++c) v[c] = 0.0;
+  if (!big)
+    for (int j = s + l; j < e; j += 16) f.add(j, v);
+#pragma unroll
+  for (int c = 0; c < F::K; ++c) v[c] = row_sum(v[c]);
+  for (uint64_t todo = __ballot(big && l == 0); todo; todo &= todo - 1) {
+    const int who = __ffsll((unsigned long long)todo) - 1;
+    const int bs = __builtin_amdgcn_readlane(s, who), be = __builtin_amdgcn_readlane(e, who);
+    int t0 = (bs + kSumTile - 1) / kSumTile, t1 = be / kSumTile;  // whole tiles of the node
+    const int head = t0 < t1 ? t0 * kSumTile : be, tail = t0 < t1 ? t1 * kSumTile : be;
+    double x[F::K];
+#pragma unroll
+    for (int c = 0; c < F::K; ++c) x[c] = 0.0;
+    for (int j = bs + lane; j < head; j += 64) f.add(j, x);
+    for (int t = t0 + lane; t < t1; t += 64)
+#pragma unroll
+      for (int c = 0; c < F::K; ++c) x[c] += tile[(int64_t)t * 4 + c];
+    for (int j = tail + lane; j < be; j += 64) f.add(j, x);
+#pragma unroll
+    for (int c = 0; c < F::K; ++c) {
+      const double total = wave_sum(x[c]);
+      if ((lane >> 4) == (who >> 4)) v[c] = total;
+    }
   }
 }
 
-// Radius-pass chunks per node (0 past the last node) and cleared maxima.
-__global__ void k_tree_count(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
-                             unsigned long long* __restrict__ rbits, uint32_t* __restrict__ dbits,
-                             int32_t* __restrict__ chunks) {
+// Tile sums, a wavefront per tile.
+template <class F>
+__global__ __launch_bounds__(256) void k_tile_sums(F f, int64_t n, int64_t tiles, double* __restrict__ tile) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < tiles; t += (int64_t)gridDim.x * 4) {
+    double x[F::K];
+#pragma unroll
+    for (int c = 0; c < F::K; ++c) x[c] = 0.0;
+#pragma unroll
+    for (int u = 0; u < kSumTile / 64; ++u) {
+      const int64_t j = t * kSumTile + u * 64 + lane;
+      if (j < n) f.add(j, x);
+    }
+#pragma unroll
+    for (int c = 0; c < F::K; ++c) {
+      x[c] = wave_sum(x[c]);
+      if (lane == 0) tile[4 * t + c] = x[c];
+    }
+  }
+}
+
+// Sorted copies of the sources (position and area; radius max(delta, eps)) and their tile sums.
+// The gathers bound it (five scattered words a source, four sources in flight a lane): 73 us for
+// 1M sources.
+__global__ __launch_bounds__(256) void k_tree_sorted(const float* __restrict__ P, const float* __restrict__ area,
+                                                     const float* __restrict__ D, float eps,
+                                                     const int32_t* __restrict__ val, int64_t n, int64_t tiles,
+                                                     int32_t* __restrict__ perm, float4* __restrict__ pos,
+                                                     float* __restrict__ rad, double* __restrict__ tile) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < tiles; t += (int64_t)gridDim.x * 4) {
+    double x[4] = {0.0, 0.0, 0.0, 0.0};
+    float4 p[kSumTile / 64];
+    float d[kSumTile / 64];
+#pragma unroll
+    for (int u = 0; u < kSumTile / 64; ++u) {
+      const int64_t j = t * kSumTile + u * 64 + lane;
+      const int64_t o = val[j < n ? j : n - 1];
+      p[u] = make_float4(P[o], P[n + o], P[2 * n + o], area[o]);
+      d[u] = D ? D[o] : 0.0f;
+      if (j < n) perm[j] = (int32_t)o;
+    }
+#pragma unroll
+    for (int u = 0; u < kSumTile / 64; ++u) {
+      const int64_t j = t * kSumTile + u * 64 + lane;
+      if (j >= n) continue;
+      pos[j] = p[u];
+      rad[j] = d[u] > eps ? d[u] : eps;
+      const double a = p[u].w;
+      x[0] += a;
+      x[1] += a * (double)p[u].x;
+      x[2] += a * (double)p[u].y;
+      x[3] += a * (double)p[u].z;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x[c] = wave_sum(x[c]);
+      if (lane == 0) tile[4 * t + c] = x[c];
+    }
+  }
+}
+
+__device__ __forceinline__ double distance(const float4& p, double gx, double gy, double gz) {
+  const double ex = (double)p.x - gx, ey = (double)p.y - gy, ez = (double)p.z - gz;
+  return sqrt(ex * ex + ey * ey + ez * ez);
+}
+
+// Squared opening radius max(beta r, r + dmax)^2.
+__device__ __forceinline__ double opening2(double r, double dm, double beta) {
+  double crit = beta * r;
+  if (r + dm > crit) crit = r + dm;
+  return crit * crit;
+}
+
+// Node centres, and the opening radii of nodes up to kSumTile sources; larger nodes' maxima are
+// cleared for k_tree_far. 32 us for the nodes of 1M sources.
+__global__ __launch_bounds__(256) void k_tree_geo(const int4* __restrict__ node, const int32_t* __restrict__ total_p,
+                                                  int64_t cap, AreaSum f, const float* __restrict__ rad,
+                                                  const double* __restrict__ tile, double beta,
+                                                  double4* __restrict__ geo, unsigned long long* __restrict__ rbits,
+                                                  uint32_t* __restrict__ dbits) {
   const int64_t total = node_count(total_p, cap);
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < cap; k += (int64_t)gridDim.x * blockDim.x) {
-    if (k >= total) {
-      chunks[k] = 0;
-      continue;
+  const int lane = threadIdx.x & 63, l = lane & 15;
+  const int64_t step = (int64_t)gridDim.x * 16;
+  for (int64_t k0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63)) >> 4; k0 < total; k0 += step) {
+    const int64_t k = k0 + (lane >> 4);
+    int s = 0, e = 0;
+    if (k < total) {
+      const int4 nd = node[k];
+      s = nd.x;
+      e = nd.y;
     }
-    const int4 nd = node[k];
-    rbits[k] = 0ull;
-    dbits[k] = 0u;
-    chunks[k] = (nd.y - nd.x + kChunk - 1) / kChunk;
-  }
-}
-
-// Last node k with coff[k] <= c (coff ascending, coff[total] > c).
-__device__ __forceinline__ int64_t chunk_node(const int32_t* __restrict__ coff, int64_t total, int64_t c) {
-  int64_t lo = 0, hi = total;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (coff[mid] <= c)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-// FP64 sums of (a, a px, a py, a pz) over each chunk, in sorted order.
-__global__ void k_tree_chunk_sums(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
-                                  const int32_t* __restrict__ coff, const float* __restrict__ P,
-                                  const float* __restrict__ area, const int32_t* __restrict__ perm, int64_t n,
-                                  double4* __restrict__ csum) {
-  const int64_t total = node_count(total_p, cap);
-  const int64_t nch = coff[total];
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nch; c += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = chunk_node(coff, total, c);
-    const int4 nd = node[k];
-    const int64_t s = nd.x + (c - coff[k]) * kChunk;
-    const int64_t e = s + kChunk < nd.y ? s + kChunk : nd.y;
-    double a = 0.0, x = 0.0, y = 0.0, z = 0.0;
-    for (int64_t j = s; j < e; ++j) {
-      const int64_t o = perm[j];
-      const double aj = area[o];
-      a += aj;
-      x += aj * (double)P[o];
-      y += aj * (double)P[n + o];
-      z += aj * (double)P[2 * n + o];
+    double v[4];
+    node_sum(f, tile, s, e, v);
+    double gx = 0.0, gy = 0.0, gz = 0.0;
+    if (v[0] != 0.0) {
+      gx = v[1] / v[0];
+      gy = v[2] / v[0];
+      gz = v[3] / v[0];
+    } else if (s < e) {  // no area: the first source
+      const float4 p = f.pos[s];
+      gx = p.x;
+      gy = p.y;
+      gz = p.z;
     }
-    csum[c] = make_double4(a, x, y, z);
-  }
-}
-
-// Node area and area-weighted centre from its chunks in order (the node's first source when
-// the area is 0).
-__global__ void k_tree_centre(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
-                              const int32_t* __restrict__ coff, const double4* __restrict__ csum,
-                              const float* __restrict__ P, const int32_t* __restrict__ perm, int64_t n,
-                              double4* __restrict__ geo) {
-  const int64_t total = node_count(total_p, cap);
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-    double a = 0.0, x = 0.0, y = 0.0, z = 0.0;
-    for (int64_t c = coff[k]; c < coff[k + 1]; ++c) {
-      const double4 v = csum[c];
-      a += v.x;
-      x += v.y;
-      y += v.z;
-      z += v.w;
-    }
-    double4 g;
-    if (a != 0.0) {
-      g = make_double4(x / a, y / a, z / a, 0.0);
-    } else {
-      const int64_t o = perm[node[k].x];
-      g = make_double4(P[o], P[n + o], P[2 * n + o], 0.0);
-    }
-    geo[k] = g;
-  }
-}
-
-// r (FP64) and dmax over chunks of kChunk sources: atomic max of the bit patterns, which
-// order like unsigned integers for non-negative values.
-__global__ void k_tree_radius(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
-                              const int32_t* __restrict__ coff, const float* __restrict__ P,
-                              const float* __restrict__ D, float eps, const int32_t* __restrict__ perm, int64_t n,
-                              const double4* __restrict__ geo, unsigned long long* __restrict__ rbits,
-                              uint32_t* __restrict__ dbits) {
-  const int64_t total = node_count(total_p, cap);
-  const int64_t nch = coff[total];
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nch; c += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = chunk_node(coff, total, c);
-    const int4 nd = node[k];
-    const double4 g = geo[k];
-    const int64_t s = nd.x + (c - coff[k]) * kChunk;
-    const int64_t e = s + kChunk < nd.y ? s + kChunk : nd.y;
     double r = 0.0;
     float dm = 0.0f;
-    for (int64_t j = s; j < e; ++j) {
-      const int64_t o = perm[j];
-      const double ex = (double)P[o] - g.x, ey = (double)P[n + o] - g.y, ez = (double)P[2 * n + o] - g.z;
-      const double dd = sqrt(ex * ex + ey * ey + ez * ez);
-      r = dd > r ? dd : r;
-      const float dj = D ? D[o] : 0.0f;
-      const float fl = dj > eps ? dj : eps;
-      dm = fl > dm ? fl : dm;
+    if (e - s <= kGroupSources)
+      for (int j = s + l; j < e; j += 16) {
+        const double d = distance(f.pos[j], gx, gy, gz);
+        r = d > r ? d : r;
+        dm = fmaxf(dm, rad[j]);
+      }
+    for (int o = 8; o > 0; o >>= 1) {
+      const double x = __shfl_xor(r, o, 64);
+      r = x > r ? x : r;
+      dm = fmaxf(dm, __shfl_xor(dm, o, 64));
     }
-    atomicMax(&rbits[k], (unsigned long long)__double_as_longlong(r));
-    atomicMax(&dbits[k], __float_as_uint(dm));
+    const bool mid = e - s > kGroupSources && e - s <= kSumTile;
+    for (uint64_t todo = __ballot(mid && l == 0); todo; todo &= todo - 1) {
+      const int who = __ffsll((unsigned long long)todo) - 1;
+      const int bs = __builtin_amdgcn_readlane(s, who), be = __builtin_amdgcn_readlane(e, who);
+      const double cx = __shfl(gx, who, 64), cy = __shfl(gy, who, 64), cz = __shfl(gz, who, 64);
+      double x = 0.0;
+      float y = 0.0f;
+      for (int j = bs + lane; j < be; j += 64) {
+        const double d = distance(f.pos[j], cx, cy, cz);
+        x = d > x ? d : x;
+        y = fmaxf(y, rad[j]);
+      }
+      x = wave_max(x);
+      y = wave_max(y);
+      if ((lane >> 4) == (who >> 4)) {
+        r = x;
+        dm = y;
+      }
+    }
+    if (l == 0 && k < total) {
+      geo[k] = make_double4(gx, gy, gz, opening2(r, (double)dm, beta));
+      if (e - s > kSumTile) {
+        rbits[k] = 0ull;
+        dbits[k] = 0u;
+      }
+    }
   }
 }
 
-__global__ void k_tree_crit(const int32_t* __restrict__ total_p, int64_t cap, double beta,
-                            const unsigned long long* __restrict__ rbits, const uint32_t* __restrict__ dbits,
-                            double4* __restrict__ geo) {
+// r and dmax of the nodes above kSumTile sources: a wavefront holds kFarTile sorted sources, walks
+// the pre-order list down to the nodes that hold some of them, and adds its maxima (atomic max of
+// the bit patterns, which order like unsigned integers for non-negative values; one that the node
+// already has is not sent, since every wavefront of the root's reaches the same address). The
+// walk's dependent loads bound it: 56 us for 1M sources, 18 for 20,011.
+constexpr int kFarTile = 512;
+__global__ __launch_bounds__(64) void k_tree_far(const int4* __restrict__ node, const int32_t* __restrict__ total_p,
+                                                 int64_t cap, const float4* __restrict__ pos,
+                                                 const float* __restrict__ rad, int64_t n,
+                                                 const double4* __restrict__ geo,
+                                                 unsigned long long* __restrict__ rbits,
+                                                 uint32_t* __restrict__ dbits) {
+  const int total = (int)node_count(total_p, cap);
+  const int lane = threadIdx.x;
+  const int64_t lo = (int64_t)blockIdx.x * kFarTile, hi = lo + kFarTile < n ? lo + kFarTile : n;
+  float4 p[kFarTile / 64];
+  float d[kFarTile / 64];
+#pragma unroll
+  for (int u = 0; u < kFarTile / 64; ++u) {
+    const int64_t j = lo + u * 64 + lane < n ? lo + u * 64 + lane : n - 1;
+    p[u] = pos[j];
+    d[u] = rad[j];
+  }
+  for (int i = 0; i < total;) {
+    const int4 nd = node[i];
+    const int s = __builtin_amdgcn_readfirstlane(nd.x), e = __builtin_amdgcn_readfirstlane(nd.y);
+    const int skip = __builtin_amdgcn_readfirstlane(nd.z);
+    if (s >= hi) break;
+    if (e <= lo || e - s <= kSumTile) {
+      i = skip > i ? skip : i + 1;
+      continue;
+    }
+    const double4 g = geo[i];
+    double r = 0.0;
+    float dm = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kFarTile / 64; ++u) {
+      const int64_t j = lo + u * 64 + lane;
+      const double x = distance(p[u], g.x, g.y, g.z);
+      const bool in = j >= s && j < e;
+      r = in && x > r ? x : r;
+      dm = in ? fmaxf(dm, d[u]) : dm;
+    }
+    r = wave_max(r);
+    dm = wave_max(dm);
+    if (lane == 0) {
+      const unsigned long long rb = (unsigned long long)__double_as_longlong(r);
+      const uint32_t db = __float_as_uint(dm);
+      if (rb > __hip_atomic_load(&rbits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&rbits[i], rb);
+      if (db > __hip_atomic_load(&dbits[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&dbits[i], db);
+    }
+    ++i;
+  }
+}
+
+__global__ void k_tree_crit(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
+                            double beta, const unsigned long long* __restrict__ rbits,
+                            const uint32_t* __restrict__ dbits, double4* __restrict__ geo) {
   const int64_t total = node_count(total_p, cap);
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-    const double r = __longlong_as_double((long long)rbits[k]);
-    const double dm = (double)__uint_as_float(dbits[k]);
-    double crit = beta * r;
-    if (r + dm > crit) crit = r + dm;
-    geo[k].w = crit * crit;
+    const int4 nd = node[k];
+    if (nd.y - nd.x > kSumTile)
+      geo[k].w = opening2(__longlong_as_double((long long)rbits[k]), (double)__uint_as_float(dbits[k]), beta);
   }
 }
 
 // Node moments for the current normals: M = sum of the staged m_j over the node (FP64).
-__global__ void k_tree_mom(const int4* __restrict__ node, const int32_t* __restrict__ total_p, int64_t cap,
-                           const double* __restrict__ S, int64_t n, float4* __restrict__ mom) {
+__global__ __launch_bounds__(256) void k_tree_mom(const int4* __restrict__ node, const int32_t* __restrict__ total_p,
+                                                  int64_t cap, MomentSum f, const double* __restrict__ tile,
+                                                  float4* __restrict__ mom) {
   const int64_t total = node_count(total_p, cap);
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-    const int4 nd = node[k];
-    float m[3];
-    for (int d = 0; d < 3; ++d) m[d] = (float)(S[d * (n + 1) + nd.y] - S[d * (n + 1) + nd.x]);
-    mom[k] = make_float4(m[0], m[1], m[2], 0.0f);
+  const int lane = threadIdx.x & 63;
+  const int64_t step = (int64_t)gridDim.x * 16;
+  for (int64_t k0 = ((int64_t)blockIdx.x * 256 + (threadIdx.x & ~63)) >> 4; k0 < total; k0 += step) {
+    const int64_t k = k0 + (lane >> 4);
+    int s = 0, e = 0;
+    if (k < total) {
+      const int4 nd = node[k];
+      s = nd.x;
+      e = nd.y;
+    }
+    double v[3];
+    node_sum(f, tile, s, e, v);
+    if ((lane & 15) == 0 && k < total) mom[k] = make_float4((float)v[0], (float)v[1], (float)v[2], 0.0f);
   }
 }
 
@@ -437,7 +547,7 @@ __global__ void k_tree_leafpos(const int4* __restrict__ node, const int32_t* __r
 // the segment that holds the ancestor). Every node is then taken by the same queries as in one
 // walk. What bounds it is the length of one walk where the queries are few (a wavefront of
 // 20,011 points walks for 260 us alone, and their 313 wavefronts leave two SIMDs in three
-// empty: 265 us a launch before, 58 with 32 segments) and the last walks to end where they are
+// empty: 265 us a launch before, 77 with 32 segments) and the last walks to end where they are
 // many (1M points, 15,626 wavefronts: 4.95 ms a launch before, 4.4 with 9 segments). The rule
 // aims at 131,072 wavefronts (16,384: 24.8 ms for four launches and the rest of a pass at 1M,
 // 65,536: 24.2, 131,072: 23.7, 262,144: 23.9) of at least 512 sources' nodes each (20,011
@@ -769,18 +879,6 @@ __global__ void k_tree_export(const int4* __restrict__ node, const int32_t* __re
   }
 }
 
-template <int K>
-dwg_status scan_f64(const float4* src, int64_t n, const TreeWork& t, hipStream_t st) {
-  const int64_t nblk = cdiv(n, kScanTile);
-  hipLaunchKernelGGL((k_scan_local<K>), dim3((unsigned)nblk), dim3(256), 0, st, src, n, t.scan, t.sblk, nblk);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL((k_scan_tops<K>), dim3(1), dim3(256), 0, st, t.sblk, nblk, t.scan, n);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL((k_scan_add<K>), dim3(grid_cap(n)), dim3(256), 0, st, t.scan, n, t.sblk, nblk);
-  DWG_TRY_LAUNCH();
-  return DWG_OK;
-}
-
 template <bool GRAD, bool SCREENED, bool KAHAN>
 void launch_eval_t(const float* Q, int64_t m, const int32_t* qperm, const GwnWork& w, const TreeWork& t,
                    float kappa, hipStream_t st) {
@@ -814,7 +912,6 @@ size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out) {
   t.cap = tree_cap(n);
   t.leaf = leaf;
   t.beta = beta;
-  t.nscan = cdiv(n, kScanTile);
   t.bpart = c.take<float>(kBboxParts);
   t.box = c.take<float>(8);
   t.frame = c.take<double>(4);
@@ -831,14 +928,9 @@ size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out) {
   t.mom = c.take<float4>((size_t)t.cap);
   t.rbits = c.take<unsigned long long>((size_t)t.cap);
   t.dbits = c.take<uint32_t>((size_t)t.cap);
-  t.coff = c.take<int32_t>((size_t)t.cap + 1);
-  t.csums = c.take<int32_t>(scan_sums_len(t.cap));
-  // chunks: at most one partial chunk per node plus sum(node sizes) / kChunk, and every
-  // source lies in at most kDepth + 1 nodes
-  t.ccap = t.cap + cdiv(n * (kDepth + 1), kChunk);
-  t.csum = c.take<double4>((size_t)t.ccap);
-  t.scan = c.take<double>(3 * ((size_t)n + 1));
-  t.sblk = c.take<double>(3 * (size_t)t.nscan);
+  t.pos = c.take<float4>((size_t)n);
+  t.rad = c.take<float>((size_t)n);
+  t.tile = c.take<double>((size_t)(4 * cdiv(n, kSumTile)));
   if (out) *out = t;
   return c.used - s0;
 }
@@ -860,26 +952,25 @@ dwg_status tree_build(const float* P, const float* area, const float* delta, int
   hipLaunchKernelGGL(k_tree_emit, dim3(grid_cap(n)), dim3(256), 0, st, t.key[0], n, t.leaf, t.lev, t.off, t.cap,
                      t.node);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_copy_i32, dim3(grid_cap(n)), dim3(256), 0, st, t.val[0], n, perm);
-  DWG_TRY_LAUNCH();
-  if (!area) return DWG_OK;  // topology only (dwg_octree)
+  if (!area) {  // topology only (dwg_octree)
+    hipLaunchKernelGGL(k_copy_i32, dim3(grid_cap(n)), dim3(256), 0, st, t.val[0], n, perm);
+    DWG_TRY_LAUNCH();
+    return DWG_OK;
+  }
   const int32_t* total = t.off + n;
-  hipLaunchKernelGGL(k_tree_count, dim3(grid_cap(t.cap)), dim3(256), 0, st, t.node, total, t.cap, t.rbits, t.dbits,
-                     t.coff);
+  const int64_t tiles = cdiv(n, kSumTile);
+  hipLaunchKernelGGL(k_tree_sorted, dim3((unsigned)cdiv(tiles, 4)), dim3(256), 0, st, P, area, delta, eps, t.val[0],
+                     n, tiles, perm, t.pos, t.rad, t.tile);
   DWG_TRY_LAUNCH();
-  s = exclusive_scan(t.coff, t.cap, t.csums, st);
-  if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_tree_chunk_sums, dim3(grid_cap(t.ccap)), dim3(256), 0, st, t.node, total, t.cap, t.coff, P,
-                     area, perm, n, t.csum);
+  hipLaunchKernelGGL(k_tree_geo, dim3(node_grid(n)), dim3(256), 0, st, t.node, total, t.cap, AreaSum{t.pos}, t.rad,
+                     t.tile, t.beta, t.geo, t.rbits, t.dbits);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_tree_centre, dim3(grid_cap(t.cap)), dim3(256), 0, st, t.node, total, t.cap, t.coff, t.csum,
-                     P, perm, n, t.geo);
+  if (n <= kSumTile) return DWG_OK;
+  hipLaunchKernelGGL(k_tree_far, dim3((unsigned)cdiv(n, kFarTile)), dim3(64), 0, st, t.node, total, t.cap, t.pos,
+                     t.rad, n, t.geo, t.rbits, t.dbits);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_tree_radius, dim3(grid_cap(t.cap)), dim3(256), 0, st, t.node, total, t.cap, t.coff, P, delta, eps,
-                     perm, n, t.geo, t.rbits, t.dbits);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_tree_crit, dim3(grid_cap(t.cap)), dim3(256), 0, st, total, t.cap, t.beta, t.rbits, t.dbits,
-                     t.geo);
+  hipLaunchKernelGGL(k_tree_crit, dim3(grid_cap(t.cap)), dim3(256), 0, st, t.node, total, t.cap, t.beta, t.rbits,
+                     t.dbits, t.geo);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }
@@ -892,10 +983,11 @@ dwg_status tree_stage_leaves(const GwnWork& w, const TreeWork& t, float kappa, h
 }
 
 dwg_status tree_moments(const GwnWork& w, const TreeWork& t, hipStream_t st) {
-  dwg_status s = scan_f64<3>(w.src, t.n, t, st);
-  if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_tree_mom, dim3(grid_cap(t.cap)), dim3(256), 0, st, t.node, t.off + t.n, t.cap, t.scan, t.n,
-                     t.mom);
+  const MomentSum f{w.src};
+  const int64_t tiles = cdiv(t.n, kSumTile);
+  hipLaunchKernelGGL(k_tile_sums<MomentSum>, dim3((unsigned)cdiv(tiles, 4)), dim3(256), 0, st, f, t.n, tiles, t.tile);
+  DWG_TRY_LAUNCH();
+  hipLaunchKernelGGL(k_tree_mom, dim3(node_grid(t.n)), dim3(256), 0, st, t.node, t.off + t.n, t.cap, f, t.tile, t.mom);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

@@ -1213,63 +1213,113 @@ __global__ void k_pca_normals(const float* __restrict__ P, int64_t n, const int3
 // x . q_j <= |q_j|^2 / 2; the square's axes are u = n x e_k / |n x e_k| (e_k the axis with the
 // smallest |n_k|, the first on ties) and n x u. Coincident neighbours (q_j = 0) bound nothing
 // and are skipped; all-coincident neighbourhoods give 0.
-__global__ __launch_bounds__(128) void k_voronoi_area(const float* __restrict__ P, int64_t n,
-                                                     const int32_t* __restrict__ idx, int m,
-                                                     float* __restrict__ area) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double px = P[i], py = P[n + i], pz = P[2 * n + i];
-  double mx = px, my = py, mz = pz;
-  for (int t = 0; t < m; ++t) {
-    const int64_t j = idx[i * m + t];
-    mx += P[j];
-    my += P[n + j];
-    mz += P[2 * n + j];
+//
+// A block takes kCellPoints points. All its threads fetch the neighbours (one word of idx after
+// another, the points scattered), one thread per point fits the plane, four threads per point
+// project and then take every fourth line each. FP64 arithmetic and its latency bound it: with one
+// thread per point throughout and a division per pair of lines, 131,072 points (two wavefronts
+// per SIMD) took 202 us; four threads 129, the projections in the neighbours' place in LDS (eight
+// blocks per CU instead of five) 111, and the loop over the lines without branches 87.
+constexpr int kCellPoints = 64;
+
+__global__ __launch_bounds__(4 * kCellPoints) void k_voronoi_area(const float* __restrict__ P, int64_t n,
+                                                                  const int32_t* __restrict__ idx, int m,
+                                                                  float* __restrict__ area) {
+  // the neighbours, then in their place their projections
+  __shared__ double2 qs[kMaxK][kCellPoints];
+  __shared__ double axes[6][kCellPoints];  // u, w of the plane
+  float(*nb)[kMaxK][kCellPoints] = reinterpret_cast<float(*)[kMaxK][kCellPoints]>(qs);
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * kCellPoints;
+  const int np = (int)(n - base < kCellPoints ? n - base : kCellPoints);
+  for (int e = tid; e < np * m; e += 4 * kCellPoints) {
+    const int64_t j = idx[base * m + e];
+    const int pt = e / m, t = e - pt * m;
+    nb[0][t][pt] = P[j];
+    nb[1][t][pt] = P[n + j];
+    nb[2][t][pt] = P[2 * n + j];
   }
-  const double inv = 1.0 / (double)(m + 1);
-  mx *= inv;
-  my *= inv;
-  mz *= inv;
-  double a[6] = {0, 0, 0, 0, 0, 0};
-  for (int t = -1; t < m; ++t) {
-    const int64_t j = t < 0 ? i : (int64_t)idx[i * m + t];
-    const double x = P[j] - mx, y = P[n + j] - my, z = P[2 * n + j] - mz;
-    a[0] += x * x;
-    a[1] += x * y;
-    a[2] += x * z;
-    a[3] += y * y;
-    a[4] += y * z;
-    a[5] += z * z;
+  __syncthreads();
+  if (tid < np) {
+    const int64_t i = base + tid;
+    const double px = P[i], py = P[n + i], pz = P[2 * n + i];
+    double mx = px, my = py, mz = pz;
+    for (int t = 0; t < m; ++t) {
+      mx += nb[0][t][tid];
+      my += nb[1][t][tid];
+      mz += nb[2][t][tid];
+    }
+    const double inv = 1.0 / (double)(m + 1);
+    mx *= inv;
+    my *= inv;
+    mz *= inv;
+    double a[6] = {0, 0, 0, 0, 0, 0};
+    for (int t = -1; t < m; ++t) {
+      const double x = (t < 0 ? px : (double)nb[0][t][tid]) - mx;
+      const double y = (t < 0 ? py : (double)nb[1][t][tid]) - my;
+      const double z = (t < 0 ? pz : (double)nb[2][t][tid]) - mz;
+      a[0] += x * x;
+      a[1] += x * y;
+      a[2] += x * z;
+      a[3] += y * y;
+      a[4] += y * z;
+      a[5] += z * z;
+    }
+    double nv[3];
+    smallest_eigvec(a, nv);
+    // orthonormal basis (u, w) of the plane: u = nv x (the axis least aligned with nv)
+    const double ax = fabs(nv[0]), ay = fabs(nv[1]), az = fabs(nv[2]);
+    const double e0 = (ax <= ay && ax <= az) ? 1.0 : 0.0;
+    const double e1 = (e0 == 0.0 && ay <= az) ? 1.0 : 0.0;
+    const double e2 = (e0 == 0.0 && e1 == 0.0) ? 1.0 : 0.0;
+    double u0 = nv[1] * e2 - nv[2] * e1, u1 = nv[2] * e0 - nv[0] * e2, u2 = nv[0] * e1 - nv[1] * e0;
+    const double ul = sqrt(u0 * u0 + u1 * u1 + u2 * u2);
+    u0 /= ul;
+    u1 /= ul;
+    u2 /= ul;
+    axes[0][tid] = u0;
+    axes[1][tid] = u1;
+    axes[2][tid] = u2;
+    axes[3][tid] = nv[1] * u2 - nv[2] * u1;
+    axes[4][tid] = nv[2] * u0 - nv[0] * u2;
+    axes[5][tid] = nv[0] * u1 - nv[1] * u0;
   }
-  double nv[3];
-  smallest_eigvec(a, nv);
-  // orthonormal basis (u, w) of the plane: u = nv x (the axis least aligned with nv)
-  const double ax = fabs(nv[0]), ay = fabs(nv[1]), az = fabs(nv[2]);
-  const double e0 = (ax <= ay && ax <= az) ? 1.0 : 0.0;
-  const double e1 = (e0 == 0.0 && ay <= az) ? 1.0 : 0.0;
-  const double e2 = (e0 == 0.0 && e1 == 0.0) ? 1.0 : 0.0;
-  double u0 = nv[1] * e2 - nv[2] * e1, u1 = nv[2] * e0 - nv[0] * e2, u2 = nv[0] * e1 - nv[1] * e0;
-  const double ul = sqrt(u0 * u0 + u1 * u1 + u2 * u2);
-  u0 /= ul;
-  u1 /= ul;
-  u2 /= ul;
-  const double w0 = nv[1] * u2 - nv[2] * u1, w1 = nv[2] * u0 - nv[0] * u2, w2 = nv[0] * u1 - nv[1] * u0;
-  double qx[kMaxK], qy[kMaxK];  // unrolled to the compile-time maximum: register resident
-  double R = 0.0;
+  __syncthreads();
+  // From here the four threads of a point are neighbouring lanes of one wavefront.
+  const int pt = tid >> 2, l = tid & 3;
+  float nx4[kMaxK / 4], ny4[kMaxK / 4], nz4[kMaxK / 4];
 #pragma unroll
-  for (int t = 0; t < kMaxK; ++t) {
-    qx[t] = qy[t] = 0.0;
-    if (t < m) {
-      const int64_t j = idx[i * m + t];
-      const double dx = P[j] - px, dy = P[n + j] - py, dz = P[2 * n + j] - pz;
-      qx[t] = dx * u0 + dy * u1 + dz * u2;
-      qy[t] = dx * w0 + dy * w1 + dz * w2;
-      const double r = sqrt(qx[t] * qx[t] + qy[t] * qy[t]);
+  for (int k = 0; k < kMaxK / 4; ++k) {
+    nx4[k] = nb[0][l + 4 * k][pt];
+    ny4[k] = nb[1][l + 4 * k][pt];
+    nz4[k] = nb[2][l + 4 * k][pt];
+  }
+  __syncthreads();
+  if (pt >= np) return;
+  const int64_t i = base + pt;
+  double R = 0.0;
+  {
+    const double px = P[i], py = P[n + i], pz = P[2 * n + i];
+    const double u0 = axes[0][pt], u1 = axes[1][pt], u2 = axes[2][pt];
+    const double w0 = axes[3][pt], w1 = axes[4][pt], w2 = axes[5][pt];
+#pragma unroll
+    for (int k = 0; k < kMaxK / 4; ++k) {
+      const int t = l + 4 * k;
+      if (t >= m) continue;
+      const double dx = nx4[k] - px, dy = ny4[k] - py, dz = nz4[k] - pz;
+      const double x = dx * u0 + dy * u1 + dz * u2, y = dx * w0 + dy * w1 + dz * w2;
+      qs[t][pt] = make_double2(x, y);
+      const double r = sqrt(x * x + y * y);
       R = r > R ? r : R;
     }
   }
+  for (int o = 1; o < 4; o <<= 1) {
+    const double r = __shfl_xor(R, o, 64);
+    R = r > R ? r : R;
+  }
+  wave_lds_fence();
   if (!(R > 0.0)) {
-    area[i] = 0.0f;
+    if (l == 0) area[i] = 0.0f;
     return;
   }
   // Cell = the square [-R, R]^2 cut by the half-planes x . q_t <= |q_t|^2 / 2 (the bisectors
@@ -1278,55 +1328,55 @@ __global__ __launch_bounds__(128) void k_voronoi_area(const float* __restrict__ 
   // (1/2) x (distance of the edge's line from the origin) x (edge length). Each line's edge is
   // the interval of the line that the other constraints leave: with x = f + s tau (f the foot
   // of the perpendicular from the origin, tau = (-n_y, n_x)), a constraint n_u . x <= b_u bounds
-  // s from one side, and the edge contributes b_t (s_max - s_min) / 2. A line repeated exactly
-  // (a repeated neighbour) counts once; a coincident neighbour (q = 0) bounds nothing. The
-  // loops run to the compile-time maximum, so the lines stay in registers.
-  constexpr int kLines = kMaxK + 4;  // neighbour bisectors, then the square's 4 edges
-  auto line_of = [&](int t, double& nx, double& ny, double& b) {
-    if (t < kMaxK) {
-      nx = t < m ? qx[t] : 0.0;
-      ny = t < m ? qy[t] : 0.0;
-      b = 0.5 * (nx * nx + ny * ny);  // 0: no constraint
-    } else {
-      const int e = t - kMaxK;
-      nx = e == 0 ? 1.0 : (e == 1 ? -1.0 : 0.0);
-      ny = e == 2 ? 1.0 : (e == 3 ? -1.0 : 0.0);
-      b = R;
-    }
-  };
+  // s by num / den from one side, and the edge contributes b_t (s_max - s_min) / 2. The bounds
+  // are compared as fractions of positive denominators and divided once per line. A line repeated
+  // exactly (a repeated neighbour) counts once; a coincident neighbour (q = 0) bounds nothing.
+  const int lines = m + 4;  // neighbour bisectors, then the square's 4 edges
   double s2 = 0.0;  // twice the area
-  for (int t = 0; t < kLines; ++t) {  // (the inner loop is the unrolled one)
-    double ax, ay, bt;
-    line_of(t, ax, ay, bt);
+  for (int t = l; t < lines; t += 4) {
+    const int e = t - m;
+    double ax = e == 0 ? 1.0 : (e == 1 ? -1.0 : 0.0), ay = e == 2 ? 1.0 : (e == 3 ? -1.0 : 0.0), bt = R;
+    if (e < 0) {
+      ax = qs[t][pt].x;
+      ay = qs[t][pt].y;
+      bt = 0.5 * (ax * ax + ay * ay);  // 0: no constraint
+    }
     if (bt == 0.0) continue;
     const double l2 = ax * ax + ay * ay;
     const double fx = ax * bt / l2, fy = ay * bt / l2;
     const double tx = -ay, ty = ax;
-    double smin = -INFINITY, smax = INFINITY;
+    // s_max = hn / hd, s_min = -ln / ld; no bound yet: +- 1 / 0
+    double hn = 1.0, hd = 0.0, ln = 1.0, ld = 0.0;
     bool empty = false;
-#pragma unroll
-    for (int u = 0; u < kLines; ++u) {
-      if (u == t) continue;
-      double nx, ny, bu;
-      line_of(u, nx, ny, bu);
-      if (bu == 0.0 || empty) continue;
-      if (nx == ax && ny == ay && bu == bt) {
-        if (u < t) empty = true;  // the same line: only its first copy has an edge
-        continue;
-      }
-      const double den = tx * nx + ty * ny;
-      const double num = bu - (fx * nx + fy * ny);
-      if (den > 0.0) {
-        smax = fmin(smax, num / den);
-      } else if (den < 0.0) {
-        smin = fmax(smin, num / den);
-      } else if (num < 0.0) {
-        empty = true;  // parallel and outside
-      }
+    auto bound = [&](bool high, bool low, double num, double pd) {
+      const bool less = num * (high ? hd : ld) < (high ? hn : ln) * pd;
+      hn = high && less ? num : hn;
+      hd = high && less ? pd : hd;
+      ln = low && less ? num : ln;
+      ld = low && less ? pd : ld;
+    };
+    for (int u = 0; u < m; ++u) {
+      const double2 q = qs[u][pt];
+      const double bu = 0.5 * (q.x * q.x + q.y * q.y);
+      const bool same = q.x == ax && q.y == ay && bu == bt;
+      empty = empty || (same && u < t);  // only its first copy has an edge
+      const bool cuts = !same && bu != 0.0;
+      const double den = tx * q.x + ty * q.y;
+      const double num = bu - (fx * q.x + fy * q.y);
+      bound(cuts && den > 0.0, cuts && den < 0.0, num, fabs(den));
+      empty = empty || (cuts && den == 0.0 && num < 0.0);  // parallel and outside
     }
+    // the square: x <= R and x >= -R, y likewise (num = 0 for an edge of its own line)
+    bound(tx > 0.0, tx < 0.0, R - fx, fabs(tx));
+    bound(tx < 0.0, tx > 0.0, R + fx, fabs(tx));
+    bound(ty > 0.0, ty < 0.0, R - fy, fabs(ty));
+    bound(ty < 0.0, ty > 0.0, R + fy, fabs(ty));
+    empty = empty || (tx == 0.0 && (fx > R || fx < -R)) || (ty == 0.0 && (fy > R || fy < -R));
+    const double smax = hn / hd, smin = -(ln / ld);
     if (!empty && smax > smin) s2 += bt * (smax - smin);
   }
-  area[i] = (float)(0.5 * s2);
+  for (int o = 1; o < 4; o <<= 1) s2 += __shfl_xor(s2, o, 64);
+  if (l == 0) area[i] = (float)(0.5 * s2);
 }
 
 // Gauss map (Sec. 5.1 "Normal Initialization"): n_i = p_i / |p_i| (about the origin);
@@ -1564,7 +1614,8 @@ dwg_status voronoi_area(const float* P, int64_t n, int m, float* area, void* ws,
   int32_t* idx = c.take<int32_t>((size_t)n * m);
   dwg_status s = knn_run(P, n, P, n, 1, m, idx, nullptr, static_cast<char*>(ws) + c.used, stream);
   if (s != DWG_OK) return s;
-  hipLaunchKernelGGL(k_voronoi_area, dim3((unsigned)cdiv(n, 128)), dim3(128), 0, stream, P, n, idx, m, area);
+  hipLaunchKernelGGL(k_voronoi_area, dim3((unsigned)cdiv(n, kCellPoints)), dim3(4 * kCellPoints), 0, stream, P, n,
+                     idx, m, area);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

@@ -68,8 +68,9 @@ typedef struct dwg_iter_stat {
   double wmean;        /* Eq. 6: mean GWN over the input points (the iso-value) */
   double top_mean_deg; /* mean of the ceil(top_frac*n) largest angle changes (deg) */
   double mean_chord;   /* (1/n) sum |n_i^(t) - n_i^(t-1)| */
-  double gwn_ms;       /* duration of this iteration's all-pairs kernel (HIP events on the
-                          caller's stream), milliseconds */
+  double gwn_ms;       /* duration of this iteration's evaluation, milliseconds: from the start of its
+                          first kernel to the start of the update (the GPU's clock; dwg_iterate_mc: HIP
+                          events on the caller's stream) */
 } dwg_iter_stat;
 
 typedef enum dwg_init_kind {

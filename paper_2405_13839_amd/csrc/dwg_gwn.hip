@@ -239,7 +239,10 @@ __device__ __forceinline__ void gwn_block(const float* __restrict__ Q, int64_t m
 template <bool SCREENED, bool KAHAN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_gwn(
     const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
-    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa,
+    float* __restrict__ part, int64_t mpad, const int32_t* __restrict__ stop, uint64_t* __restrict__ begin) {
+  if (*stop) return;
+  if ((blockIdx.x | blockIdx.y | threadIdx.x) == 0) *begin = wall_clock64();
   gwn_block<kBlock, kQpt, kTile, true, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk,
                                                         kappa, part, mpad);
 }
@@ -248,7 +251,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
 template <bool SCREENED, bool KAHAN>
 __global__ __launch_bounds__(kBlock) void k_gwn_w(
     const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
-    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa,
+    float* __restrict__ part, int64_t mpad, const int32_t* __restrict__ stop, uint64_t* __restrict__ begin) {
+  if (*stop) return;
+  if ((blockIdx.x | blockIdx.y | threadIdx.x) == 0) *begin = wall_clock64();
   gwn_block<kBlock, kQpt, kTile, false, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk,
                                                        kappa, part, mpad);
 }
@@ -259,7 +265,10 @@ constexpr int kSmallStep = 32;
 template <bool GRAD, bool SCREENED, bool KAHAN>
 __global__ __launch_bounds__(kQBlock) void k_gwn_small(
     const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const float4* __restrict__ src,
-    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa, float* __restrict__ part, int64_t mpad) {
+    int64_t nsteps, int64_t nfull, int64_t steps_per_split, const float4* __restrict__ tbox, Scr sk, float kappa,
+    float* __restrict__ part, int64_t mpad, const int32_t* __restrict__ stop, uint64_t* __restrict__ begin) {
+  if (*stop) return;
+  if ((blockIdx.x | blockIdx.y | threadIdx.x) == 0) *begin = wall_clock64();
   gwn_block<kQBlock, 1, kSmallStep, GRAD, SCREENED, KAHAN>(Q, m, qperm, src, nsteps, nfull, steps_per_split, tbox, sk, kappa,
                                                            part, mpad);
 }
@@ -267,12 +276,14 @@ __global__ __launch_bounds__(kQBlock) void k_gwn_small(
 // Stage the sources in spatial order: (p, 1/(kappa max(delta,eps))) and m = a n / (4 pi)
 // (kappa = the position scale of the kernel, 1 when plain; positions stay unscaled, the
 // evaluation kernels scale differences).
-// A NaN delta poisons the source's m so that the result is NaN as in the definition.
+// A NaN delta poisons the source's m so that the result is NaN as in the definition. Clears the
+// stop flag of an iteration.
 __global__ void k_stage(const float* __restrict__ P, const float* __restrict__ N,
                         const float* __restrict__ A, const float* __restrict__ D, int64_t n,
                         int64_t npad, float eps, float kappa, const int32_t* __restrict__ perm,
-                        float4* __restrict__ src, float* __restrict__ kk) {
+                        float4* __restrict__ src, float* __restrict__ kk, int32_t* __restrict__ stop) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j == 0) *stop = 0;
   if (j >= npad) return;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = make_float4(0.f, 0.f, 0.f, 0.f);
   float k = 0.0f;
@@ -419,7 +430,7 @@ __global__ __launch_bounds__(kEpiBlock) void k_combine(const float* __restrict__
 // Iteration epilogue (Eq. 7): n_new = -grad/|grad| (kept when |grad| is 0 or not finite),
 // written in place at the point's original index; restage m for the next iteration;
 // theta_i (degrees, FP64); FP64 block partials of w and of the chord |n_new - n_old|. Clears the
-// histograms of the selection that follows.
+// histograms of the selection that follows. After the iteration has stopped, nothing else changes.
 template <int QB>
 __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ part, int split,
                                                       int64_t mpad, int64_t n, Scale sc, bool kahan,
@@ -429,11 +440,14 @@ __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ 
                                                       float4* __restrict__ src,
                                                       double* __restrict__ theta,
                                                       double* __restrict__ blk, int nblk,
-                                                      uint32_t* __restrict__ hist) {
+                                                      uint32_t* __restrict__ hist,
+                                                      const int32_t* __restrict__ stop, uint64_t* __restrict__ end) {
   __shared__ float acc[kNAcc][QB];
   __shared__ double lds[kEpiWaves];
   const int64_t q0 = (int64_t)blockIdx.x * QB;
   clear_hist(hist, n);
+  if (*stop) return;
+  if ((blockIdx.x | threadIdx.x) == 0) *end = wall_clock64();
   combine_block<QB>(part, split, mpad, kNAcc, q0, kahan, acc);
   const int t = threadIdx.x;
   const int64_t i = q0 + t;
@@ -592,10 +606,17 @@ __device__ void mean_stats(const double* blk, int nblk, int64_t n, const double*
   }
 }
 
+// Sets the flag when the iteration ends with these statistics: a value that is not finite, or a
+// largest angle change within eps_deg (negative: never).
+__device__ __forceinline__ void set_stop(const double* stats, double eps_deg, int32_t* stop) {
+  if (!stop) return;
+  if (!isfinite(stats[0]) || !isfinite(stats[1]) || !isfinite(stats[2]) || stats[1] <= eps_deg) *stop = 1;
+}
+
 __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restrict__ theta, int n, int64_t k,
                                                            const double* __restrict__ blk, int nblk,
-                                                           const double* __restrict__ iso,
-                                                           double* __restrict__ stats) {
+                                                           const double* __restrict__ iso, double* stats,
+                                                           double eps_deg, int32_t* __restrict__ stop) {
   __shared__ SelLds s;
   __shared__ double lds[kSelBlock / 64];
   __shared__ uint64_t ext[2][kSelBlock / 64];
@@ -644,6 +665,7 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restr
   if (t == 0) {
     const double rest = r.whole ? 0.0 : (double)r.krem * __longlong_as_double((long long)r.lo);
     stats[1] = (total + rest) / (double)k;
+    set_stop(stats, eps_deg, stop);
   }
 }
 
@@ -719,8 +741,8 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restr
                                                            const double* __restrict__ iso,
                                                            const uint64_t* __restrict__ sel,
                                                            const uint64_t* __restrict__ cand,
-                                                           const double* __restrict__ top, int ntop,
-                                                           double* __restrict__ stats) {
+                                                           const double* __restrict__ top, int ntop, double* stats,
+                                                           double eps_deg, int32_t* __restrict__ stop) {
   __shared__ SelLds s;
   __shared__ double lds[kSelBlock / 64];
   __shared__ unsigned long long part[2];  // integer sum of the low bits, in two halves
@@ -783,6 +805,7 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restr
                       ((double)part[0] * 262144.0 + (double)part[1]) * ulp;
     const double rest = r.whole ? 0.0 : (double)r.krem * __longlong_as_double((long long)r.lo);
     stats[1] = (sum + in + rest) / (double)k;
+    set_stop(stats, eps_deg, stop);
   }
 }
 
@@ -830,19 +853,23 @@ void launch_gwn_t(bool grad, hipStream_t st, const float* Q, int64_t m, const Gw
     const int64_t steps = cdiv(w.n_src, kSmallStep), per = cdiv(steps, w.split);
     if (grad)
       hipLaunchKernelGGL((k_gwn_small<true, SCREENED, KAHAN>), grid, dim3(kQBlock), 0, st, Q, m, w.perm_q, w.src, steps,
-                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
+                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad, w.stop,
+                       w.clock());
     else
       hipLaunchKernelGGL((k_gwn_small<false, SCREENED, KAHAN>), grid, dim3(kQBlock), 0, st, Q, m, w.perm_q, w.src, steps,
-                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
+                         nfull, per, w.tbox, kScaledScr, kappa, w.part, w.mpad, w.stop,
+                       w.clock());
     return;
   }
   const int64_t per = cdiv(w.ntiles, w.split);
   if (grad)
     hipLaunchKernelGGL((k_gwn<SCREENED, KAHAN>), grid, dim3(kBlock), 0, st, Q, m, w.perm_q, w.src, w.ntiles, nfull, per,
-                       w.tbox, kScaledScr, kappa, w.part, w.mpad);
+                       w.tbox, kScaledScr, kappa, w.part, w.mpad, w.stop,
+                       w.clock());
   else
     hipLaunchKernelGGL((k_gwn_w<SCREENED, KAHAN>), grid, dim3(kBlock), 0, st, Q, m, w.perm_q, w.src, w.ntiles, nfull,
-                       per, w.tbox, kScaledScr, kappa, w.part, w.mpad);
+                       per, w.tbox, kScaledScr, kappa, w.part, w.mpad, w.stop,
+                       w.clock());
 }
 
 }  // namespace
@@ -885,7 +912,8 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, 
   w.kk = c.take<float>((size_t)w.npad);
   w.theta = c.take<double>((size_t)std::max(n_src, n_qry));
   w.blk = c.take<double>(2 * (size_t)std::max<int64_t>(cdiv(std::max(n_src, n_qry), 256), kEpiSmall / 64));
-  w.stats = c.take<double>(4);
+  w.stats = c.take<double>(kStatsRow * kAhead);
+  w.stop = c.take<int32_t>(1);
   w.hist = c.take<uint32_t>(kSelHistLen);
   w.sel = c.take<uint64_t>(5);
   w.cand = c.take<uint64_t>(kSelSmallMax);
@@ -901,7 +929,7 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, 
 dwg_status launch_stage(const float* P, const float* N, const float* area, const float* delta,
                         int64_t n, float eps, float kappa, const GwnWork& w, hipStream_t stream) {
   hipLaunchKernelGGL(k_stage, dim3((unsigned)cdiv(w.npad, 256)), dim3(256), 0, stream, P, N, area,
-                     delta, n, w.npad, eps, kappa, w.perm_s, w.src, w.kk);
+                     delta, n, w.npad, eps, kappa, w.perm_s, w.src, w.kk, w.stop);
   DWG_TRY_LAUNCH();
   hipLaunchKernelGGL(k_tile_box, dim3((unsigned)w.ntiles), dim3(kTile), 0, stream, w.src, n, kappa, w.tbox);
   DWG_TRY_LAUNCH();
@@ -956,10 +984,12 @@ dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const
   const int nb = (int)cdiv(n, qb);
   if (qb == 64)
     hipLaunchKernelGGL((k_update<64>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
-                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist);
+                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist, w.stop,
+                       w.clock() + 1);
   else
     hipLaunchKernelGGL((k_update<256>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
-                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist);
+                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist, w.stop,
+                       w.clock() + 1);
   DWG_TRY_LAUNCH();
   *nblk = nb;
   return DWG_OK;
@@ -973,10 +1003,12 @@ static int64_t top_count(int64_t n, double top_frac) {
 }
 
 dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, const double* iso,
-                        hipStream_t stream) {
+                        double eps_deg, int32_t* stop, hipStream_t stream) {
+  double* const stats = w.stats + kStatsRow * w.slot;
   const int64_t k = top_count(n, top_frac);
   if (n <= kSelSmallMax) {
-    hipLaunchKernelGGL(k_stats_small, dim3(1), dim3(kSelBlock), 0, stream, w.theta, (int)n, k, w.blk, nblk, iso, w.stats);
+    hipLaunchKernelGGL(k_stats_small, dim3(1), dim3(kSelBlock), 0, stream, w.theta, (int)n, k, w.blk, nblk, iso, stats,
+                       eps_deg, stop);
     DWG_TRY_LAUNCH();
     return DWG_OK;
   }
@@ -988,7 +1020,7 @@ dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, 
   hipLaunchKernelGGL(k_sel_collect, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, w.cand, w.top);
   DWG_TRY_LAUNCH();
   hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kSelBlock), 0, stream, w.theta, n, k, w.blk, nblk, iso, w.sel, w.cand,
-                     w.top, hb, w.stats);
+                     w.top, hb, stats, eps_deg, stop);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

@@ -132,13 +132,16 @@ dwg_status spatial_sort(const float* P, int64_t n, const float* delta, float eps
 // Device-side state of one GWN / iteration launch sequence, carved from the workspace.
 // Sources and queries are processed in spatial order (perm_s / perm_q: sorted position ->
 // original index); outputs are written back at the original indices.
+constexpr int kStatsRow = 6;
+constexpr int kAhead = 8;  // iterations that the host launches before it reads their statistics
 struct GwnWork {
   float4* src;        // [2 * npad]: (px,py,pz,1/rho_min), (mx,my,mz,0) per sorted source
   float* part;        // [split][kNAcc][mpad] per-split partial sums (sorted queries)
   float* kk;          // [npad] a_j / (4 pi), for restaging after the update
   double* theta;      // [m] angle change in degrees (iterate)
   double* blk;        // [2 * nblk] per-block FP64 partial sums
-  double* stats;      // [4] device statistics
+  double* stats;      // [kAhead][kStatsRow] device statistics, and the clock at either end of the evaluation
+  int32_t* stop;      // [1] set when an iteration has ended
   uint32_t* hist;     // [kSelHistLen] histograms of the top-k selection
   uint64_t* sel;      // [5] its state
   uint64_t* cand;     // [kSelSmallMax] angles near the k-th largest
@@ -149,6 +152,8 @@ struct GwnWork {
   SortWork sort;
   int64_t n_src, npad, mpad, ntiles;
   int split;
+  int slot;           // row of stats that the next launches write
+  uint64_t* clock() const { return reinterpret_cast<uint64_t*>(stats + kStatsRow * slot + 4); }
 };
 
 size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, GwnWork* out);
@@ -302,11 +307,13 @@ dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bo
 dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, float* wout,
                           float* gout, double* wmean, const GwnWork& w, hipStream_t stream);
 // The update writes *nblk block partials; launch_stats reads as many. iso: where stats[0] comes from
-// instead of the partials of w (NULL: from those).
+// instead of the partials of w (NULL: from those). The statistics go to row w.slot of w.stats; with
+// `stop`, the flag is set when they end the iteration (see dwg_iterate): evaluations and updates
+// launched behind then do nothing.
 dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, int* nblk,
                          hipStream_t stream);
 dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, const double* iso,
-                        hipStream_t stream);
+                        double eps_deg, int32_t* stop, hipStream_t stream);
 dwg_status launch_random_normals(uint64_t seed, int64_t n, float* N, hipStream_t stream);
 
 dwg_status knn_run(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k, int32_t* idx,

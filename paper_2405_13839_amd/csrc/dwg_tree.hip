@@ -263,9 +263,11 @@ __device__ __forceinline__ void node_sum(const F& f, const double* __restrict__ 
   }
 }
 
-// Tile sums, a wavefront per tile.
+// Tile sums, a wavefront per tile; the first launch of an evaluation, so it notes the clock.
 template <class F>
-__global__ __launch_bounds__(256) void k_tile_sums(F f, int64_t n, int64_t tiles, double* __restrict__ tile) {
+__global__ __launch_bounds__(256) void k_tile_sums(F f, int64_t n, int64_t tiles, double* __restrict__ tile,
+                                                   uint64_t* __restrict__ begin) {
+  if ((blockIdx.x | threadIdx.x) == 0) *begin = wall_clock64();
   const int lane = threadIdx.x & 63;
   for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < tiles; t += (int64_t)gridDim.x * 4) {
     double x[F::K];
@@ -598,7 +600,8 @@ __global__ __launch_bounds__(kTreeBlock) __attribute__((amdgpu_waves_per_eu(7)))
     const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const int4* __restrict__ node,
     const double4* __restrict__ geo, const float4* __restrict__ mom, const int32_t* __restrict__ total_p, int64_t cap,
     const float4* __restrict__ src, int64_t n_src, Scr sk, float kappa, float* __restrict__ part, int64_t mpad,
-    unsigned segments) {
+    unsigned segments, const int32_t* __restrict__ stop) {
+  if (*stop) return;
   constexpr int NA = GRAD ? kNAcc : 1;
   // per wavefront: the queries of a split leaf visit by rank, and the lanes' partial sums
   __shared__ float4 lds_q[kTreeWaves][64];
@@ -884,7 +887,7 @@ void launch_eval_t(const float* Q, int64_t m, const int32_t* qperm, const GwnWor
                    float kappa, hipStream_t st) {
   hipLaunchKernelGGL((k_tree_eval<GRAD, SCREENED, KAHAN>), dim3(tree_grid(w.mpad / kTreeBlock, w.split)),
                      dim3(kTreeBlock), 0, st, Q, m, qperm, t.node, t.geo, t.mom, t.off + t.n, t.cap, w.src, t.n, kScaledScr, kappa,
-                     w.part, w.mpad, (unsigned)w.split);
+                     w.part, w.mpad, (unsigned)w.split, w.stop);
 }
 
 }  // namespace
@@ -985,7 +988,8 @@ dwg_status tree_stage_leaves(const GwnWork& w, const TreeWork& t, float kappa, h
 dwg_status tree_moments(const GwnWork& w, const TreeWork& t, hipStream_t st) {
   const MomentSum f{w.src};
   const int64_t tiles = cdiv(t.n, kSumTile);
-  hipLaunchKernelGGL(k_tile_sums<MomentSum>, dim3((unsigned)cdiv(tiles, 4)), dim3(256), 0, st, f, t.n, tiles, t.tile);
+  hipLaunchKernelGGL(k_tile_sums<MomentSum>, dim3((unsigned)cdiv(tiles, 4)), dim3(256), 0, st, f, t.n, tiles, t.tile,
+                     w.clock());
   DWG_TRY_LAUNCH();
   hipLaunchKernelGGL(k_tree_mom, dim3(node_grid(t.n)), dim3(256), 0, st, t.node, t.off + t.n, t.cap, f, t.tile, t.mom);
   DWG_TRY_LAUNCH();

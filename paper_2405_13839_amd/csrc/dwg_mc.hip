@@ -6,7 +6,7 @@
 // Grid. The octree frame (lo = bounding-box minimum, side = largest extent) cut into 2^depth
 // cells per axis; a point's cell is its level-21 octree cell shifted down to `depth`. The
 // evaluated cells are the cells holding points grown by `dilate` rings (inside the cube),
-// sorted by Morton code; their corners are deduplicated (radix sort + scan) and placed at
+// in Morton order; their corners, without repetitions, are placed at
 // lo + c * side / 2^depth (FP64, rounded once to FP32).
 // Level set: Marching Cubes (the paper's "standard Marching Cubes"). Corner index
 // x + 2y + 4z; a corner is above when w > w_bar; the case of a cube is the 8-bit mask of its
@@ -50,6 +50,27 @@ using morton::compact21;
 __device__ __forceinline__ uint64_t morton3(int x, int y, int z) { return morton::code3(x, y, z); }
 
 unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 256), 16384)); }
+
+// Code of corner k (x + 2y + 4z) of the cell.
+__device__ __forceinline__ uint64_t corner_code(uint64_t cell, int k) {
+  return morton3(compact21(cell >> 2) + (k & 1), compact21(cell >> 1) + ((k >> 1) & 1),
+                 compact21(cell) + ((k >> 2) & 1));
+}
+
+// Cell size = side / 2^depth, side = the largest extent of the bounding box (FP64).
+__device__ __forceinline__ double cell_size(const float* __restrict__ box, int depth) {
+  double side = (double)box[3] - (double)box[0];
+  const double sy = (double)box[4] - (double)box[1], sz = (double)box[5] - (double)box[2];
+  if (sy > side) side = sy;
+  if (sz > side) side = sz;
+  return side / (double)(1 << depth);
+}
+
+__device__ __forceinline__ void corner_position(uint64_t code, const double* __restrict__ frame, double h, int64_t id,
+                                                int64_t ld, float* __restrict__ pos) {
+  const int c[3] = {compact21(code >> 2), compact21(code >> 1), compact21(code)};
+  for (int d = 0; d < 3; ++d) pos[d * ld + id] = (float)__dadd_rn(frame[d], __dmul_rn((double)c[d], h));
+}
 
 // Cell code of every point at `depth` (from the level-21 octree cell).
 __global__ void k_mc_point_keys(const float* __restrict__ P, int64_t n, const double* __restrict__ frame, int depth,
@@ -98,13 +119,161 @@ __global__ void k_mc_dilate(const uint64_t* __restrict__ occ, const int32_t* __r
   }
 }
 
+// ---- Sets of codes as bitmaps: bit b of word w stands for code 64 w + b, so the set bits in order
+// are the distinct codes in ascending order, and a code's rank among them is the number of bits in
+// the words before it (an exclusive scan of the words' counts) plus those below it in its word.
+// One word is a 4 x 4 x 4 block of cells: growing by rings and the corners of the cells are shifts
+// of a block and its neighbours, word by word, with no atomics but one per point. Sorting a code per
+// candidate instead (27 per point, 8 per cell, most of them equal) took 265 and 175 us for 100K
+// points at depth 7, 42 and 43 this way (212 and 156 for the first kernels alone when they set
+// one bit at a time). Used when the words fit the arrays that the sort needs (bitmap_words): they
+// are then at most as many as the codes, and scanning them costs less than one pass of the sort; a
+// sparse set of a deep grid is sorted.
+using Word = unsigned long long;
+
+// An axis of a block: the bits of coordinate k are m0 << (k's shift); coordinate 1 is s0 bits up,
+// 2 is s1 = 8 s0.
+template <int S0>
+struct Axis {
+  static constexpr int S1 = 8 * S0;
+  static constexpr Word mask(int k) {
+    Word m = 0;
+    for (int b = 0; b < 64; ++b)
+      if (((b / S0) & 1) + 2 * ((b / S1) & 1) == k) m |= Word(1) << b;
+    return m;
+  }
+  static constexpr Word M0 = mask(0), M1 = mask(1), M2 = mask(2), M3 = mask(3);
+  // every cell moved by one along the axis, with what comes in from the block before / after
+  static __device__ __forceinline__ Word up(Word w, Word before) {
+    return ((w & (M0 | M2)) << S0) | ((w & M1) << (S1 - S0)) | ((before & M3) >> (S1 + S0));
+  }
+  static __device__ __forceinline__ Word down(Word w, Word after) {
+    return ((w & (M1 | M3)) >> S0) | ((w & M2) >> (S1 - S0)) | ((after & M0) << (S1 + S0));
+  }
+  // grown by r <= 2 cells both ways
+  static __device__ __forceinline__ Word grow(Word w, Word before, Word after, int r) {
+    Word out = w, u = w, d = w;
+    for (int k = 0; k < r; ++k) {
+      u = up(u, before);
+      before = up(before, 0);
+      d = down(d, after);
+      after = down(after, 0);
+      out |= u | d;
+    }
+    return out;
+  }
+};
+using AxisX = Axis<4>;
+using AxisY = Axis<2>;
+using AxisZ = Axis<1>;
+
+// The word of block (x, y, z) of a cube of `side` blocks per axis; empty outside.
+__device__ __forceinline__ Word block_at(const Word* __restrict__ bits, int side, int x, int y, int z) {
+  if ((unsigned)x >= (unsigned)side || (unsigned)y >= (unsigned)side || (unsigned)z >= (unsigned)side) return 0;
+  return bits[morton3(x, y, z)];
+}
+__device__ __forceinline__ int blocks_per_axis(int depth) { return depth > 2 ? 1 << (depth - 2) : 1; }
+
+// The cells holding points.
+__global__ void k_bits_occupied(const float* __restrict__ P, int64_t n, const double* __restrict__ frame, int depth,
+                                Word* __restrict__ bits) {
+  const int sh = morton::kDepth - depth;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    int c[3];
+    morton::cell21(P, n, i, frame, c);
+    const uint64_t code = morton3(c[0] >> sh, c[1] >> sh, c[2] >> sh);
+    const Word b = Word(1) << (code & 63);
+    if (!(bits[code >> 6] & b)) atomicOr(&bits[code >> 6], b);
+  }
+}
+
+// Those cells grown by r rings inside the cube, and their number per word.
+__global__ void k_bits_grow(const Word* __restrict__ occ, int64_t words, int depth, int r, Word* __restrict__ bits,
+                            int32_t* __restrict__ cnt) {
+  const int side = blocks_per_axis(depth);
+  const Word inside = depth >= 2 ? ~Word(0) : (Word(1) << (1 << 3 * depth)) - 1;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x) {
+    Word v = occ[i];
+    if (r > 0) {
+      const int x = compact21((uint64_t)i >> 2), y = compact21((uint64_t)i >> 1), z = compact21((uint64_t)i);
+      Word plane[3];
+#pragma unroll
+      for (int dz = -1; dz <= 1; ++dz) {
+        Word row[3];
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy)
+          row[dy + 1] = AxisX::grow(block_at(occ, side, x, y + dy, z + dz), block_at(occ, side, x - 1, y + dy, z + dz),
+                                    block_at(occ, side, x + 1, y + dy, z + dz), r);
+        plane[dz + 1] = AxisY::grow(row[1], row[0], row[2], r);
+      }
+      v = AxisZ::grow(plane[1], plane[0], plane[2], r) & inside;
+    }
+    bits[i] = v;
+    cnt[i] = __popcll(v);
+  }
+}
+
+// The corners of the cells (every cell and the next one along each axis), and their number per word.
+__global__ void k_bits_corners(const Word* __restrict__ cells, int depth, int64_t words, Word* __restrict__ bits,
+                               int32_t* __restrict__ cnt) {
+  const int side = blocks_per_axis(depth);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x) {
+    const int x = compact21((uint64_t)i >> 2), y = compact21((uint64_t)i >> 1), z = compact21((uint64_t)i);
+    Word v = 0;
+    if (x <= side && y <= side && z <= side) {
+      Word plane[2];
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz) {
+        Word row[2];
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          const Word w = block_at(cells, side, x, y - dy, z - dz);
+          row[dy] = w | AxisX::up(w, block_at(cells, side, x - 1, y - dy, z - dz));
+        }
+        plane[dz] = row[0] | AxisY::up(row[0], row[1]);
+      }
+      v = plane[0] | AxisZ::up(plane[0], plane[1]);
+    }
+    bits[i] = v;
+    cnt[i] = __popcll(v);
+  }
+}
+
+__device__ __forceinline__ int32_t bit_rank(const Word* __restrict__ bits, const int32_t* __restrict__ rank,
+                                            uint64_t code) {
+  return rank[code >> 6] + __popcll(bits[code >> 6] & ((Word(1) << (code & 63)) - 1));
+}
+
+// The codes in ascending order.
+__global__ void k_bits_list(const Word* __restrict__ bits, int64_t words,
+                            const int32_t* __restrict__ rank, uint64_t* __restrict__ out) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x) {
+    int32_t at = rank[i];
+    for (Word b = bits[i]; b; b &= b - 1) out[at++] = 64ull * (uint64_t)i + (uint64_t)(__ffsll(b) - 1);
+  }
+}
+
+// Corner ids of every cell (the rank of the corner's code) and the corner positions.
+__global__ void k_bits_corner_ids(const uint64_t* __restrict__ cells, int64_t C,
+                                  const Word* __restrict__ bits, int64_t words,
+                                  const int32_t* __restrict__ rank, const double* __restrict__ frame,
+                                  const float* __restrict__ box, int depth, int32_t* __restrict__ cidx,
+                                  float* __restrict__ pos, int64_t ld) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < 8 * C; t += step)
+    cidx[t] = bit_rank(bits, rank, corner_code(cells[t >> 3], (int)(t & 7)));
+  const double h = cell_size(box, depth);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += step) {
+    int32_t id = rank[i];
+    for (unsigned long long b = bits[i]; b; b &= b - 1ull, ++id)
+      corner_position(64ull * (uint64_t)i + (uint64_t)(__ffsll(b) - 1), frame, h, id, ld, pos);
+  }
+}
+
 // Corner lattice keys of every cell: key[8 cell + k] = Morton code of the corner.
 __global__ void k_mc_corner_keys(const uint64_t* __restrict__ cells, int64_t C, uint64_t* __restrict__ key) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < 8 * C; t += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t code = cells[t >> 3];
-    const int k = (int)(t & 7);
-    key[t] = morton3(compact21(code >> 2) + (k & 1), compact21(code >> 1) + ((k >> 1) & 1),
-                     compact21(code) + ((k >> 2) & 1));
+    key[t] = corner_code(cells[t >> 3], (int)(t & 7));
   }
 }
 
@@ -113,21 +282,12 @@ __global__ void k_mc_corner_ids(const uint64_t* __restrict__ key, const int32_t*
                                 const int32_t* __restrict__ off, const double* __restrict__ frame,
                                 const float* __restrict__ box, int depth, int32_t* __restrict__ cidx,
                                 float* __restrict__ pos, int64_t ld) {
-  // cell size = side / 2^depth, side = the largest extent of the bounding box (FP64)
-  double side = (double)box[3] - (double)box[0];
-  const double sy = (double)box[4] - (double)box[1], sz = (double)box[5] - (double)box[2];
-  if (sy > side) side = sy;
-  if (sz > side) side = sz;
-  const double h = side / (double)(1 << depth);
+  const double h = cell_size(box, depth);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n8; i += (int64_t)gridDim.x * blockDim.x) {
     const bool head = i == 0 || key[i] != key[i - 1];
     const int32_t id = head ? off[i] : off[i] - 1;
     cidx[val[i]] = id;
-    if (head) {
-      const uint64_t k = key[i];
-      const int c[3] = {compact21(k >> 2), compact21(k >> 1), compact21(k)};
-      for (int d = 0; d < 3; ++d) pos[d * ld + id] = (float)__dadd_rn(frame[d], __dmul_rn((double)c[d], h));
-    }
+    if (head) corner_position(key[i], frame, h, id, ld, pos);
   }
 }
 
@@ -578,9 +738,43 @@ size_t carve_mc_faces(Carver& c, int64_t n, int64_t C, const McParams& mp, McWor
   return c.used - s0;
 }
 
+namespace {
+// Words of a bitmap over the codes of 3 x bits, when `sets` of them and a count per word fit the
+// sort's arrays of `keys` keys; 0 otherwise.
+int64_t bitmap_words(int bits, int sets, int64_t keys) {
+  const int64_t words = int64_t(1) << std::max(0, 3 * bits - 6);
+  return 3 * bits <= 48 && sets * words <= keys ? words : 0;
+}
+
+Word* cell_bits(const McWork& w, int64_t words) { return reinterpret_cast<Word*>(w.key[0]) + words; }
+
+dwg_status read_count(const int32_t* count, int64_t* out, hipStream_t st) {
+  int32_t c = 0;
+  DWG_TRY_HIP(hipMemcpyAsync(&c, count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  DWG_TRY_HIP(hipStreamSynchronize(st));
+  *out = c;
+  return DWG_OK;
+}
+}  // namespace
+
 dwg_status mc_cells(const float* P, int64_t n, const McParams& mp, const McWork& w, int64_t* C_host,
                     hipStream_t st) {
   DWG_PROPAGATE_INT(morton_frame(P, n, w.bpart, w.box, w.frame, st));
+  if (const int64_t words = bitmap_words(mp.depth, 2, mc_key_cap(n, mp))) {
+    Word* const occ = reinterpret_cast<Word*>(w.key[0]);
+    Word* const bits = cell_bits(w, words);
+    hipLaunchKernelGGL(k_zero_u64, dim3(grid_of(words)), dim3(256), 0, st, occ, words);
+    DWG_TRY_LAUNCH();
+    hipLaunchKernelGGL(k_bits_occupied, dim3(grid_of(n)), dim3(256), 0, st, P, n, w.frame, mp.depth, occ);
+    DWG_TRY_LAUNCH();
+    hipLaunchKernelGGL(k_bits_grow, dim3(grid_of(words)), dim3(256), 0, st, occ, words, mp.depth, mp.dilate, bits,
+                       w.head);
+    DWG_TRY_LAUNCH();
+    DWG_PROPAGATE_INT(exclusive_scan(w.head, words, w.hdsums, st));
+    hipLaunchKernelGGL(k_bits_list, dim3(grid_of(words)), dim3(256), 0, st, bits, words, w.head, w.cells);
+    DWG_TRY_LAUNCH();
+    return read_count(w.head + words, C_host, st);
+  }
   hipLaunchKernelGGL(k_mc_point_keys, dim3(grid_of(n)), dim3(256), 0, st, P, n, w.frame, mp.depth, w.key[0]);
   DWG_TRY_LAUNCH();
   int res = 0;
@@ -602,15 +796,27 @@ dwg_status mc_cells(const float* P, int64_t n, const McParams& mp, const McWork&
   DWG_PROPAGATE_INT(exclusive_scan(w.head, nk, w.hdsums, st));
   hipLaunchKernelGGL(k_mc_compact, dim3(grid_of(nk)), dim3(256), 0, st, w.key[res], nk, limit, w.head, w.cells);
   DWG_TRY_LAUNCH();
-  int32_t C = 0;
-  DWG_TRY_HIP(hipMemcpyAsync(&C, w.head + nk, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  DWG_TRY_HIP(hipStreamSynchronize(st));
-  *C_host = C;
-  return DWG_OK;
+  return read_count(w.head + nk, C_host, st);
 }
 
 dwg_status mc_corners(const McParams& mp, McWork& w, int64_t* m_host, hipStream_t st) {
   const int64_t n8 = 8 * w.C;
+  const int64_t cell_words = bitmap_words(mp.depth, 2, mc_key_cap(w.n, mp));
+  const int64_t words = cell_words ? bitmap_words(mp.depth + 1, 1, n8) : 0;
+  if (words) {  // from the bitmap that mc_cells left
+    Word* const bits = reinterpret_cast<Word*>(w.ckey[0]);
+    hipLaunchKernelGGL(k_bits_corners, dim3(grid_of(words)), dim3(256), 0, st, cell_bits(w, cell_words), mp.depth, words,
+                       bits, w.chead);
+    DWG_TRY_LAUNCH();
+    DWG_PROPAGATE_INT(exclusive_scan(w.chead, words, w.chdsums, st));
+    DWG_PROPAGATE_INT(read_count(w.chead + words, m_host, st));
+    w.m = *m_host;
+    w.ld = w.m + (mp.iso_points ? w.n : 0);
+    hipLaunchKernelGGL(k_bits_corner_ids, dim3(grid_of(std::max(n8, words))), dim3(256), 0, st, w.cells, w.C, bits,
+                       words, w.chead, w.frame, w.box, mp.depth, w.cidx, w.pos, w.ld);
+    DWG_TRY_LAUNCH();
+    return DWG_OK;
+  }
   hipLaunchKernelGGL(k_mc_corner_keys, dim3(grid_of(n8)), dim3(256), 0, st, w.cells, w.C, w.ckey[0]);
   DWG_TRY_LAUNCH();
   int res = 0;
@@ -618,15 +824,12 @@ dwg_status mc_corners(const McParams& mp, McWork& w, int64_t* m_host, hipStream_
   hipLaunchKernelGGL(k_mc_heads, dim3(grid_of(n8)), dim3(256), 0, st, w.ckey[res], n8, ~0ull, w.chead);
   DWG_TRY_LAUNCH();
   DWG_PROPAGATE_INT(exclusive_scan(w.chead, n8, w.chdsums, st));
-  int32_t m = 0;
-  DWG_TRY_HIP(hipMemcpyAsync(&m, w.chead + n8, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  DWG_TRY_HIP(hipStreamSynchronize(st));
-  w.m = m;
-  w.ld = m + (mp.iso_points ? w.n : 0);
+  DWG_PROPAGATE_INT(read_count(w.chead + n8, m_host, st));
+  w.m = *m_host;
+  w.ld = w.m + (mp.iso_points ? w.n : 0);
   hipLaunchKernelGGL(k_mc_corner_ids, dim3(grid_of(n8)), dim3(256), 0, st, w.ckey[res], w.cval[res], n8, w.chead,
                      w.frame, w.box, mp.depth, w.cidx, w.pos, w.ld);
   DWG_TRY_LAUNCH();
-  *m_host = m;
   return DWG_OK;
 }
 
@@ -645,11 +848,7 @@ dwg_status mc_faces(const McWork& w, float* tri, int64_t tcap, int64_t* F_host, 
     hipLaunchKernelGGL(k_mc_emit, dim3(grid_of(w.C)), dim3(256), 0, st, w.C, w.cidx, w.pos, w.ld, w.wc, w.iso,
                        w.fcnt, w.fcap, w.cen, w.fcap, w.vec, tri, tcap);
   DWG_TRY_LAUNCH();
-  int32_t F = 0;
-  DWG_TRY_HIP(hipMemcpyAsync(&F, w.fcnt + w.C, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  DWG_TRY_HIP(hipStreamSynchronize(st));
-  *F_host = F;
-  return DWG_OK;
+  return read_count(w.fcnt + w.C, F_host, st);
 }
 
 dwg_status mc_scatter(const McParams& mp, const McWork& w, int64_t F, hipStream_t st) {

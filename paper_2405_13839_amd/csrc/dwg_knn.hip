@@ -96,6 +96,7 @@ constexpr int kSample = 4096;                       // points the grid is laid o
 constexpr int kSamplePer = kSample / kSetupBlock;   // of them per thread
 constexpr int kTrimBins = 1024;
 constexpr int kTrimLevels = 3;
+constexpr int kTrimEnough = 128;                    // bins: at least that many left end the trimming
 constexpr int kCoarse = 32;                         // cells per axis of the finer counting grid
 constexpr int kSetupTable = kCoarse * kCoarse * kCoarse;
 // Other reference points that a reference point is expected to share its cell with, per
@@ -111,7 +112,7 @@ constexpr float kCellShare = 0.6f;
 struct SetupLds {
   int hist[3 * kTrimBins];
   int wtot[kSetupBlock / 64];
-  int found[3][2];
+  int found[3][2], shrunk;
   int64_t below_lo[3], below[3];
   double range[6];
   float red[6][kSetupBlock / 64];
@@ -136,6 +137,12 @@ __device__ __forceinline__ int64_t sample_index(int s, int S, int64_t n) {
   return i < n ? i : n - 1;
 }
 
+// Cube root of a volume, to single precision.
+__device__ __forceinline__ double cells_edge(double v) {
+  const int e = ilogb(v) / 3;  // v = (m 2^(3e)), m a float's range whatever v
+  return ldexp((double)cbrtf((float)ldexp(v, -3 * e)), e);
+}
+
 // Grid parameters for the cell edge h (grown until the grid has at most max_cells cells).
 __device__ void grid_dims(const double* range, double h, int64_t max_cells, GridParams* gp) {
   float mn[3], mx[3];
@@ -156,7 +163,7 @@ __device__ void grid_dims(const double* range, double h, int64_t max_cells, Grid
   // slabs thinner than 1e-3 of the largest extent count as that thickness for the volume
   double vol = 1.0;
   for (int d = 0; d < 3; ++d) vol *= fmax(ext[d], 1e-3 * emax);
-  const double hmin = cbrt(vol / (double)max_cells);
+  const double hmin = cells_edge(vol / (double)max_cells);
   if (!(h >= hmin)) h = hmin;
   if (!(h <= emax)) h = emax;
   // every point of the box must fall inside the grid: grow h until the uncapped cell counts
@@ -240,9 +247,12 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
   }
   // Trimming: each level narrows an axis to the bins that hold the ranks floor(S / 1024) and
   // S - 1 - floor(S / 1024) of the sample's coordinates. A range whose ranks are not found
-  // (NaN coordinates) is kept.
+  // (NaN coordinates) is kept. Once no axis shrinks below kTrimEnough of its bins, its ends are
+  // known to 1% of it and the rest is left (outliers far away take the further levels). 25 -> 20 us.
   const int64_t rlo = S / kTrimBins, rhi = S - 1 - S / kTrimBins;
-  for (int level = 0; level < kTrimLevels && rlo > 0; ++level) {
+  bool again = rlo > 0;
+  for (int level = 0; level < kTrimLevels && again; ++level) {
+    if (t == 0) s.shrunk = 0;
     __syncthreads();
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -298,8 +308,11 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
         s.range[2 * t] = lo + blo * w;
         s.range[2 * t + 1] = bhi == kTrimBins - 1 ? hi : lo + (bhi + 1) * w;
         s.below[t] = s.below_lo[t];
+        if (bhi - blo + 1 < kTrimEnough) s.shrunk = 1;
       }
     }
+    __syncthreads();
+    again = s.shrunk != 0;
   }
   __syncthreads();
   // Pair counts of the sample on the trimmed box cut into 32 and 16 cells along its longest
@@ -337,8 +350,10 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
     // the points sharing a cell of edge e grow like e^D (D = 2 on a surface)
     const double scale = S > 1 ? (double)(n - 1) / ((double)S * (double)(S - 1)) : 1.0;
     const double fine = fmax((double)s.pairs[0], 0.5) * scale, coarse = fmax((double)s.pairs[1], 1.0) * scale;
-    const double dim = fmin(3.0, fmax(1.0, log2(coarse / fine)));
-    const double h = flat ? 1.0 : (emax / kCoarse) * pow((double)kCellShare * k / fine, 1.0 / dim);
+    // (single precision: one thread's FP64 log, power and cube root took a third of the kernel, and
+    // h sets the search's cost only)
+    const float dim = fminf(3.0f, fmaxf(1.0f, log2f((float)(coarse / fine))));
+    const double h = flat ? 1.0 : (emax / kCoarse) * exp2f(log2f((float)((double)kCellShare * k / fine)) / dim);
     grid_dims(s.range, h, max_cells, &s.gp);
   }
   __syncthreads();

@@ -102,10 +102,10 @@ constexpr int kSetupTable = kCoarse * kCoarse * kCoarse;
 // Other reference points that a reference point is expected to share its cell with, per
 // neighbour searched for. The thread-per-query pass takes the 27 cells around the query, which
 // reach 1 to 1.5 cells from it: on a surface 0.6 k points per cell put about 3 k of them there, and
-// it finishes nearly every query that is not isolated. Both passes for 0.4 / 0.5 / 0.65 / 0.8 in
-// place of 0.6 (whole calls, us): radius of 1M points by 10 of 4,096 anchors 570 / 373 / 341 / 320,
-// 10 and 15 nearest of 131,071 points with their areas 626 / 565 / 560 / 591, 10 nearest of 50,001
-// points 124 / 132 / 141 / 149. (8 cells per reference point, whatever the cloud, give 0.1 k on a
+// it finishes nearly every query that is not isolated. Whole calls for 0.45 / 0.5 / 0.6 / 0.7, us:
+// radius of 1M points by 10 of 4,096 anchors 340 / 301 / 287 / 290, their learned normals (16 anchors)
+// 462 / 427 / 400 / 424, 10 and 15 nearest of 131,071 points with their areas 418 / 405 / 398 / 409,
+// 10 nearest of 50,001 points 114 / 110 / 120 / 128. (8 cells per reference point, whatever the cloud, give 0.1 k on a
 // sampled surface of 4,096 points: rings 2 and 3, 84 rows of cells instead of 9.)
 constexpr float kCellShare = 0.6f;
 
@@ -1004,25 +1004,94 @@ __device__ __forceinline__ double lane_below(double v) {
   return __hiloint2double(hi, lo);
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// The key of the lane whose number differs in the given bits, within a row of 16 lanes.
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kXor3 = 0x1b, kXor7 = 0x141, kXor8 = 0x128, kXor15 = 0x140;
+__device__ __forceinline__ double lane_xor4(double v) { return dpp_double<kXor3>(dpp_double<kXor7>(v)); }
+
+// Of this lane's key and its partner's, the smaller where the lane is the lower of the two.
+__device__ __forceinline__ double exchange(double v, double other, bool lower) {
+  return (v < other) == lower ? v : other;
+}
+
+// Sorts the keys of a row (ascending) that first falls and then rises or the reverse.
+__device__ __forceinline__ double merge_row(double v, int lane) {
+  v = exchange(v, dpp_double<kXor8>(v), !(lane & 8));
+  v = exchange(v, lane_xor4(v), !(lane & 4));
+  v = exchange(v, dpp_double<kXor2>(v), !(lane & 2));
+  return exchange(v, dpp_double<kXor1>(v), !(lane & 1));
+}
+
+// The 16 smallest of the list `key` (ascending in each row, the same in every row) and the 64 lanes'
+// x, as such a list: the rows are sorted (a bitonic network), and two sorted rows a, b hold their 16
+// smallest in min(a_i, b_15-i). 135 instructions, as many as a dozen insertions.
+__device__ __forceinline__ double merge_keys(double key, double x) {
+  const int lane = threadIdx.x & 63;
+  x = exchange(x, dpp_double<kXor1>(x), !(lane & 1));
+  x = exchange(x, dpp_double<kXor3>(x), !(lane & 2));
+  x = exchange(x, dpp_double<kXor1>(x), !(lane & 1));
+  x = exchange(x, dpp_double<kXor7>(x), !(lane & 4));
+  x = exchange(x, dpp_double<kXor2>(x), !(lane & 2));
+  x = exchange(x, dpp_double<kXor1>(x), !(lane & 1));
+  x = exchange(x, dpp_double<kXor15>(x), !(lane & 8));
+  x = exchange(x, lane_xor4(x), !(lane & 4));
+  x = exchange(x, dpp_double<kXor2>(x), !(lane & 2));
+  x = exchange(x, dpp_double<kXor1>(x), !(lane & 1));
+  {
+    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = key_min(__hiloint2double((int)b[0], (int)a[0]), dpp_double<kXor15>(__hiloint2double((int)b[1], (int)a[1])));
+    x = merge_row(x, lane);
+  }
+  {
+    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = key_min(__hiloint2double((int)b[0], (int)a[0]), dpp_double<kXor15>(__hiloint2double((int)b[1], (int)a[1])));
+    x = merge_row(x, lane);
+  }
+  return merge_row(key_min(key, dpp_double<kXor15>(x)), lane);
+}
+
+// Inclusive sum over the lanes.
+__device__ __forceinline__ int32_t wave_scan(int32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // The items k_knn left unfinished, one wavefront per item (a grid-stride loop over the
 // wavefronts of the launch). The cube around the query grows by half (half-width 2, 3, 4, 6, 9,
 // ...), or to the half-width that the k-th best distance needs where that is less; the lanes share out
-// the rows of cells that each step adds, write the positions of the rows' points into a list in LDS
-// (kWaveList at a time) and take the list 64 points at a time: lanes that walk their own rows
-// wait for one load per point. (Four rows per lane and step, or growing straight to the k-th best
-// distance, took 1.5 times as long.) The list of the k best is spread over the lanes of a row
-// of 16, one key per lane (the same in every row): a candidate that beats the last key is broadcast
-// and inserted with one minimum and one maximum, whatever k. The work per step is bounded by
-// the grid's rows.
-constexpr int kWaveList = 512;
+// the rows of cells that each step adds, and take the rows' points 64 at a time whatever row they
+// lie in: a lane's row is the last one that starts at or before its place in the sequence. (Four rows
+// per lane and step, or growing straight to the k-th best distance, took 1.5 times as long.) The
+// list of the k best is spread over the lanes of a row of 16, one key per lane (the same in every row):
+// a candidate that beats the last key is broadcast and inserted with one minimum and one
+// maximum, whatever k; more than kMergeFrom candidates are sorted and merged at once. Instruction
+// issue bounds it: 800 per item, most of them insertions of the first 64 candidates one by one
+// and a list of positions written row by row, when 1M queries of 4,096 anchors took 112 us;
+// 66 now. The work per step is bounded by the grid's rows.
+constexpr int kMergeFrom = 12;
 
 __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams* __restrict__ gp,
                                                   const int32_t* __restrict__ start,
                                                   const float4* __restrict__ sorted,
                                                   const int32_t* __restrict__ defer, int k, KnnEmit em) {
-  __shared__ int32_t list_all[4][kWaveList];
+  __shared__ int32_t mark_all[4][64];
   const int lane = threadIdx.x & 63;
-  int32_t* const list = list_all[threadIdx.x >> 6];
+  int32_t* const mark = mark_all[threadIdx.x >> 6];
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   const int64_t nd = defer[0];
   const GridParams g = *gp;
@@ -1048,41 +1117,45 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
         int32_t b0 = 0, e0 = 0, b1 = 0, e1 = 0;  // this lane's row: up to two ranges of sorted
         if (l < rows)
           shell_row(g, start, cx, cy, cz, rp, zl + (int)(l / nyr), yl + (int)(l % nyr), xl, xh, b0, e0, b1, e1);
-        for (;;) {  // until every row's points have been listed and taken
-          const int32_t len = (e0 - b0) + (e1 - b1);
-          if (__ballot(len > 0) == 0ull) break;
-          int32_t inc = len;
-          for (int o = 1; o < 64; o <<= 1) {
-            const int32_t y = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += y;
-          }
-          const int32_t all = __shfl(inc, 63, 64);
-          int32_t at = inc - len;
-          while (at < kWaveList && b0 < e0) list[at++] = b0++;
-          while (at < kWaveList && b1 < e1) list[at++] = b1++;
+        const int32_t len0 = e0 - b0, len = len0 + (e1 - b1);
+        const int32_t upto = wave_scan(len), from = upto - len, all = __builtin_amdgcn_readlane(upto, 63);
+        int carry = 0;  // the row of the place before the next 64
+        for (int32_t base = 0; base < all; base += 64) {
+          mark[lane] = 0;
           wave_lds_fence();
-          const int32_t n = min(all, kWaveList);
-          for (int32_t c = lane; c - lane < n; c += 64) {
-            uint32_t hi = 0xffffffffu;
-            int j = 0x7fffffff;
-            if (c < n) {
-              const float4 sp = sorted[list[c]];
-              j = __float_as_int(sp.w);
-              const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
-              if (j != skip) hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
-            }
-            unsigned long long mask = __ballot(hi <= worst);
-            while (mask) {
-              const int src = __ffsll((long long)mask) - 1;
-              mask &= mask - 1ull;
-              const uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)hi, src);
-              if (ch > worst) continue;
-              const double x = __hiloint2double((int)ch, __builtin_amdgcn_readlane(j, src));
-              key = key_max(lane_below(key), key_min(key, x));
-              worst = (uint32_t)__builtin_amdgcn_readlane(__double2hiint(key), k - 1);
-            }
-          }
+          if (len > 0 && from >= base && from < base + 64) mark[from - base] = lane + 1;
           wave_lds_fence();
+          const int32_t m = mark[lane];
+          const unsigned long long first = __ballot(m != 0) & (~0ull >> (63 - lane));
+          const int started = __shfl(m, first ? 63 - __clzll((long long)first) : lane, 64);
+          const int row = first ? started - 1 : carry;
+          carry = __builtin_amdgcn_readlane(row, 63);
+          const int32_t at = base + lane - __shfl(from, row, 64), l0r = __shfl(len0, row, 64);
+          const int32_t lo = __shfl(b0, row, 64), hi1 = __shfl(b1, row, 64);
+          uint32_t hi = 0xffffffffu;
+          int j = 0x7fffffff;
+          if (base + lane < all) {
+            const float4 sp = sorted[at < l0r ? lo + at : hi1 + (at - l0r)];
+            j = __float_as_int(sp.w);
+            const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
+            if (j != skip) hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
+          }
+          unsigned long long mask = __ballot(hi <= worst);
+          if (__popcll(mask) > kMergeFrom) {
+            const bool in = hi <= worst;
+            key = merge_keys(key, __hiloint2double(in ? (int)hi : (int)kKeyInf, in ? j : 0x7fffffff));
+            worst = (uint32_t)__builtin_amdgcn_readlane(__double2hiint(key), k - 1);
+            continue;
+          }
+          while (mask) {
+            const int src = __ffsll((long long)mask) - 1;
+            mask &= mask - 1ull;
+            const uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)hi, src);
+            if (ch > worst) continue;
+            const double x = __hiloint2double((int)ch, __builtin_amdgcn_readlane(j, src));
+            key = key_max(lane_below(key), key_min(key, x));
+            worst = (uint32_t)__builtin_amdgcn_readlane(__double2hiint(key), k - 1);
+          }
         }
       }
       const float lb = outside_bound(g, f, cx, cy, cz, r);

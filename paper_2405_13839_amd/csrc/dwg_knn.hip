@@ -103,7 +103,7 @@ constexpr int kSetupTable = kCoarse * kCoarse * kCoarse;
 // neighbour searched for. The thread-per-query pass takes the 27 cells around the query, which
 // reach 1 to 1.5 cells from it: on a surface 0.6 k points per cell put about 3 k of them there, and
 // it finishes nearly every query that is not isolated. Whole calls for 0.45 / 0.5 / 0.6 / 0.7, us:
-// radius of 1M points by 10 of 4,096 anchors 340 / 301 / 287 / 290, their learned normals (16 anchors)
+// radius of 1M points by 10 of 4,096 anchors (lists of pairs) 340 / 301 / 287 / 290, their learned normals (16 anchors)
 // 462 / 427 / 400 / 424, 10 and 15 nearest of 131,071 points with their areas 418 / 405 / 398 / 409,
 // 10 nearest of 50,001 points 114 / 110 / 120 / 128. (8 cells per reference point, whatever the cloud, give 0.1 k on a
 // sampled surface of 4,096 points: rings 2 and 3, 84 rows of cells instead of 9.)
@@ -623,21 +623,49 @@ __device__ __forceinline__ double key_max(double a, double b) {
   return r;
 }
 
-// Inserts key x into the ascending list b of K keys, dropping the last: b[u] becomes
+// The K best candidates of a query, ascending. As pairs: an inserted key x makes b[u]
 // max(b[u - 1], min(b[u], x)), two FP64 instructions per slot (ranking the pairs by compares and
 // selects took eight).
 template <int K>
-__device__ __forceinline__ void insert_key(double x, double* b) {
+struct PairList {
+  static constexpr bool kIndexed = true;
+  double b[K];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int u = K - 1; u >= 1; --u) b[u] = key_max(b[u - 1], key_min(b[u], x));
-  b[0] = key_min(b[0], x);
-}
+    for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, 0x7fffffff);
+  }
+  __device__ __forceinline__ void offer(float d2, int j) {
+    const uint32_t hi = __float_as_uint(d2) + kKeyBias;
+    if (hi > key_high(b[K - 1])) return;
+    const double x = __hiloint2double((int)hi, j);
+#pragma unroll
+    for (int u = K - 1; u >= 1; --u) b[u] = key_max(b[u - 1], key_min(b[u], x));
+    b[0] = key_min(b[0], x);
+  }
+  __device__ __forceinline__ float d2(int u) const { return key_d2(b[u]); }
+  __device__ __forceinline__ int index(int u) const { return __double2loint(b[u]); }
+};
 
+// As squared distances alone, where only the radius they give is asked for: the median of
+// (b[u - 1], b[u], x), one FP32 instruction per slot (which of equally distant references is taken
+// does not matter then). 1M queries of 4,096 anchors, k = 10: 116 us, with pairs 166.
 template <int K>
-__device__ __forceinline__ void clear_keys(double* b) {
+struct DistList {
+  static constexpr bool kIndexed = false;
+  float b[K];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, 0x7fffffff);
-}
+    for (int u = 0; u < K; ++u) b[u] = INFINITY;
+  }
+  __device__ __forceinline__ void offer(float d2, int) {
+    if (!(d2 < b[K - 1])) return;
+#pragma unroll
+    for (int u = K - 1; u >= 1; --u) b[u] = __builtin_amdgcn_fmed3f(b[u - 1], b[u], d2);
+    b[0] = fminf(b[0], d2);
+  }
+  __device__ __forceinline__ float d2(int u) const { return b[u]; }
+  __device__ __forceinline__ int index(int) const { return 0; }
+};
 
 // What a finished query writes: its neighbour list, or the kernel radius that the list gives
 // (k_delta_window's and the mean distance's arithmetic, without storing the lists).
@@ -657,28 +685,28 @@ __device__ __forceinline__ float inverse_mean(float s, int k) {
   return s > 0.0f ? 1.0f / s : 0.0f;
 }
 
-template <int K>
-__device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const double* b) {
+template <int K, class List>
+__device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const List& b) {
   float d[K];
 #pragma unroll
-  for (int u = 0; u < K; ++u) d[u] = sqrtf(key_d2(b[u]));
-  if (e.mode == kEmitList) {
+  for (int u = 0; u < K; ++u) d[u] = sqrtf(b.d2(u));
+  if (List::kIndexed && e.mode == kEmitList) {
 #pragma unroll
     for (int u = 0; u < K; ++u) {
-      e.idx[q * K + u] = __double2loint(b[u]);
+      e.idx[q * K + u] = b.index(u);
       if (e.dist) e.dist[q * K + u] = d[u];
     }
-  } else if (e.mode == kEmitMean || e.mode == kEmitScaled) {
+  } else if (e.mode == kEmitMean || (List::kIndexed && e.mode == kEmitScaled)) {
     float s = 0.0f;
 #pragma unroll
     for (int u = 0; u < K; ++u) s += d[u];
-    if (e.mode == kEmitMean) {
+    if (!List::kIndexed || e.mode == kEmitMean) {
       e.delta[q] = e.scale * (s / (float)K);
       return;
     }
     e.delta[q] = inverse_mean(s, K);
 #pragma unroll
-    for (int u = 0; u < K; ++u) e.idx[q * K + u] = __double2loint(b[u]);
+    for (int u = 0; u < K; ++u) e.idx[q * K + u] = b.index(u);
   } else {
     // the mean of the distances that lie in [vmin, vmax]; when none does, the mean of all k
     // clamped to [vmin, vmax] (Sec. 5.2 "Poisson Kernels")
@@ -827,12 +855,12 @@ __device__ __forceinline__ void shell_row(const GridParams& g, const int32_t* __
 
 // Search of one query by one thread over the cubes of half-width 1, 2, .. rcap: true when it is
 // finished (b holds its list), false when it needs more rings.
-template <int K>
+template <int K, class List>
 __device__ __forceinline__ bool knn_thread(const GridParams& g, const int32_t* __restrict__ start,
-                                           const float4* __restrict__ sorted, const KnnQuery& kq, int rcap, double* b) {
+                                           const float4* __restrict__ sorted, const KnnQuery& kq, int rcap, List& b) {
   const float qx = kq.x, qy = kq.y, qz = kq.z;
   const int skip = kq.skip;
-  clear_keys<K>(b);
+  b.clear();
   int cx, cy, cz;
   cell_of(g, qx, qy, qz, cx, cy, cz);
   float f[3];
@@ -847,8 +875,7 @@ __device__ __forceinline__ bool knn_thread(const GridParams& g, const int32_t* _
       if (pp < e) next = sorted[pp];
       const int j = __float_as_int(sp.w);
       const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
-      const uint32_t hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
-      if (j != skip && hi <= key_high(b[K - 1])) insert_key<K>(__hiloint2double((int)hi, j), b);
+      if (j != skip) b.offer(fmaf(ez, ez, fmaf(ey, ey, ex * ex)), j);
     }
   };
   // The cube of half-width 1: nine rows of up to three cells, the query's own row first, their
@@ -874,7 +901,8 @@ __device__ __forceinline__ bool knn_thread(const GridParams& g, const int32_t* _
   // still holds.)
   for (int r = 1;; ++r) {
     const float lb = outside_bound(g, f, cx, cy, cz, r);
-    if (lb == INFINITY || (key_high(b[K - 1]) < kKeyInf && key_d2(b[K - 1]) <= lb * lb) || r >= rmax) return true;
+    const float kth = b.d2(K - 1);  // +inf while the list is not full
+    if (lb == INFINITY || (kth < INFINITY && kth <= lb * lb) || r >= rmax) return true;
     if (r >= rcap) return false;
     const int rr = r + 1;
     const int zl = max(cz - rr, 0), zh = min(cz + rr, g.nz - 1);
@@ -900,7 +928,7 @@ __device__ __forceinline__ bool knn_thread(const GridParams& g, const int32_t* _
 // order in which candidates are met, so it is the same whichever pass finishes it. Work items in
 // cell order let the lanes of a wavefront walk the same rows of cells: the same loads, loops of
 // nearly the same length.
-template <int K>
+template <int K, class List>
 __global__ __launch_bounds__(256) void k_knn(QuerySet qs, const GridParams* __restrict__ gp,
                                              const int32_t* __restrict__ start,
                                              const float4* __restrict__ sorted, int rcap,
@@ -909,7 +937,7 @@ __global__ __launch_bounds__(256) void k_knn(QuerySet qs, const GridParams* __re
   if (p >= qs.m) return;
   const GridParams g = *gp;
   const KnnQuery kq = knn_query_of(qs, p);
-  double b[K];
+  List b;
   if (knn_thread<K>(g, start, sorted, kq, rcap, b))
     emit_query<K>(em, kq.q, b);
   else
@@ -1512,8 +1540,11 @@ enum QueryOrder { kOwnOrder, kAnyOrder, kGivenOrder };
 
 template <int K>
 void launch_knn_k(hipStream_t st, const QuerySet& qs, const KnnWork& w, int rcap, const KnnEmit& em) {
-  hipLaunchKernelGGL((k_knn<K>), dim3((unsigned)cdiv(qs.m, 256)), dim3(256), 0, st, qs, w.gp, w.start, w.sorted, rcap,
-                     w.defer, em);
+  const dim3 grid((unsigned)cdiv(qs.m, 256));
+  if (em.mode == kEmitMean || em.mode == kEmitWindow)
+    hipLaunchKernelGGL((k_knn<K, DistList<K>>), grid, dim3(256), 0, st, qs, w.gp, w.start, w.sorted, rcap, w.defer, em);
+  else
+    hipLaunchKernelGGL((k_knn<K, PairList<K>>), grid, dim3(256), 0, st, qs, w.gp, w.start, w.sorted, rcap, w.defer, em);
 }
 
 // Grid of the nr references R for searches of k neighbours.

@@ -549,18 +549,23 @@ __global__ void k_tree_leafpos(const int4* __restrict__ node, const int32_t* __r
 // the segment that holds the ancestor). Every node is then taken by the same queries as in one
 // walk. What bounds it is the length of one walk where the queries are few (a wavefront of
 // 20,011 points walks for 260 us alone, and their 313 wavefronts leave two SIMDs in three
-// empty: 265 us a launch before, 77 with 32 segments) and the last walks to end where they are
-// many (1M points, 15,626 wavefronts: 4.95 ms a launch before, 4.4 with 9 segments). The rule
-// aims at 131,072 wavefronts (16,384: 24.8 ms for four launches and the rest of a pass at 1M,
-// 65,536: 24.2, 131,072: 23.7, 262,144: 23.9) of at least 512 sources' nodes each (20,011
-// points: 1.16 ms a pass; 256 sources 1.14, 1,024 1.24; one segment 2.0), so the partial sums
-// stay below 28 bytes for each of 2^23 + m queries.
+// empty: 265 us a launch as one segment) and the last walks to end where they are many (1M points,
+// 15,626 wavefronts: 4.95 ms a launch as one, 4.4 as 9 segments). The rule aims at 131,072
+// wavefronts (16,384: 24.8 ms for four launches and the rest of a pass at 1M, 65,536: 24.2, 131,072:
+// 23.7, 262,144: 23.9), so the partial sums stay below 28 bytes for each of 2^23 + m queries; of at
+// least 64 sources' nodes each, and at most 64 segments, whose partial sums then cost more to add
+// than they save. Evaluation / whole iteration, us:
+//   points             1,000   2,500   5,000   10,000    20,000    40,000    80,000
+//   512 sources, 32   65 / 95 72 / 103 67 / 104 72 / 112 96 / 145 149 / 210 289 / 354
+//   128 sources, 64   35 / 65 37 / 70  36 / 76  47 / 92  80 / 134 127 / 200 268 / 348
+//   128 sources, 128  35 / 65 37 / 70  36 / 76  46 / 93  81 / 141 135 / 233 271 / 369
+//   64 sources, 64    26 / 55 31 / 65  32 / 74  47 / 92  82 / 134 127 / 199 267 / 348
 constexpr int kFoldLeaves = 4;
 // Threads per block of the traversal: its wavefronts share no data and never wait for each
 // other (each has its own LDS area and no barrier).
 constexpr int kTreeBlock = 256;
 constexpr int kTreeWaves = kTreeBlock / 64;
-constexpr int64_t kSegmentWaves = 131072, kSegmentSources = 512, kMaxSegments = 32;
+constexpr int64_t kSegmentWaves = 131072, kSegmentSources = 64, kMaxSegments = 64;
 // A leaf visit is spread over the idle lanes when that saves at least this many iterations.
 constexpr int kSplitMinSaved = 2;
 

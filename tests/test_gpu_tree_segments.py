@@ -1,5 +1,5 @@
 """Octree evaluation in segments of the node list, at the edges of the rule that counts them: one
-segment of 512 sources, two and three of one source more, more segments than nodes, the most
+segment of 64 sources, two and three of one source more, more segments than nodes, the most
 there are; queries that end inside a wavefront and inside a run of blocks; nodes of one source."""
 import numpy as np
 import pytest
@@ -22,7 +22,8 @@ def _cloud(kind, n):
     return P, c.area[:n].copy()
 
 
-CASES = [("torus", 1, 1, 16), ("torus", 512, 512, 16), ("torus", 513, 65, 16), ("torus", 1025, 2049, 1),
+CASES = [("torus", 1, 1, 16), ("torus", 64, 64, 16), ("torus", 65, 63, 4), ("torus", 129, 128, 1),
+         ("torus", 4032, 65, 16), ("torus", 4097, 4097, 32), ("torus", 512, 512, 16), ("torus", 513, 65, 16), ("torus", 1025, 2049, 1),
          ("torus", 16_384, 257, 1), ("torus", 20_011, 2305, 16), ("copies", 3000, 700, 4), ("equal", 2000, 130, 16)]
 
 

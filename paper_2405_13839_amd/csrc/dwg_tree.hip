@@ -562,9 +562,12 @@ __global__ void k_tree_leafpos(const int4* __restrict__ node, const int32_t* __r
 //   64 sources, 64    26 / 55 31 / 65  32 / 74  47 / 92  82 / 134 127 / 199 267 / 348
 constexpr int kFoldLeaves = 4;
 // Threads per block of the traversal: its wavefronts share no data and never wait for each
-// other (each has its own LDS area and no barrier).
+// other (each has its own LDS area and no barrier), but a block's place on a CU is free only when
+// its last wavefront has ended. From kLoneQueries queries on a block is one wavefront (1M points:
+// 20.0 against 20.9 ms for four launches and the rest of a pass, a level-set update of 100K points,
+// 250K queries, 2.49 against 2.53); below, four (20,011 points: 0.77 against 0.79 ms a pass).
 constexpr int kTreeBlock = 256;
-constexpr int kTreeWaves = kTreeBlock / 64;
+constexpr int64_t kLoneQueries = 131072;
 constexpr int64_t kSegmentWaves = 131072, kSegmentSources = 64, kMaxSegments = 64;
 // A leaf visit is spread over the idle lanes when that saves at least this many iterations.
 constexpr int kSplitMinSaved = 2;
@@ -600,8 +603,8 @@ unsigned tree_grid(int64_t nb, int segments) { return (unsigned)(8 * cdiv(nb, 8)
 
 // Seven wavefronts per SIMD: left to itself the compiler takes 73 VGPRs (six; 25.5 ms a pass at
 // 1M against 23.1), and at eight it spills (25.9).
-template <bool GRAD, bool SCREENED, bool KAHAN>
-__global__ __launch_bounds__(kTreeBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_tree_eval(
+template <int BLOCK, bool GRAD, bool SCREENED, bool KAHAN>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(7))) void k_tree_eval(
     const float* __restrict__ Q, int64_t m, const int32_t* __restrict__ qperm, const int4* __restrict__ node,
     const double4* __restrict__ geo, const float4* __restrict__ mom, const int32_t* __restrict__ total_p, int64_t cap,
     const float4* __restrict__ src, int64_t n_src, Scr sk, float kappa, float* __restrict__ part, int64_t mpad,
@@ -609,12 +612,12 @@ __global__ __launch_bounds__(kTreeBlock) __attribute__((amdgpu_waves_per_eu(7)))
   if (*stop) return;
   constexpr int NA = GRAD ? kNAcc : 1;
   // per wavefront: the queries of a split leaf visit by rank, and the lanes' partial sums
-  __shared__ float4 lds_q[kTreeWaves][64];
-  __shared__ float lds_p[kTreeWaves][64][NA == 1 ? 1 : 8];
+  __shared__ float4 lds_q[BLOCK / 64][64];
+  __shared__ float lds_p[BLOCK / 64][64][NA == 1 ? 1 : 8];
   const int wv = (int)(threadIdx.x >> 6);
   unsigned qblock, segment;
-  if (!xcd_block(blockIdx.x, (unsigned)(mpad / kTreeBlock), segments, &qblock, &segment)) return;
-  const int64_t qi = (int64_t)qblock * kTreeBlock + threadIdx.x;
+  if (!xcd_block(blockIdx.x, (unsigned)(mpad / BLOCK), segments, &qblock, &segment)) return;
+  const int64_t qi = (int64_t)qblock * BLOCK + threadIdx.x;
   const int64_t o = qperm[qi < m ? qi : m - 1];
   const float ux = Q[o], uy = Q[m + o], uz = Q[2 * m + o];
   const double dqx = ux, dqy = uy, dqz = uz;  // the opening test runs in unscaled FP64
@@ -887,12 +890,21 @@ __global__ void k_tree_export(const int4* __restrict__ node, const int32_t* __re
   }
 }
 
+template <int BLOCK, bool GRAD, bool SCREENED, bool KAHAN>
+void launch_eval_b(const float* Q, int64_t m, const int32_t* qperm, const GwnWork& w, const TreeWork& t,
+                   float kappa, hipStream_t st) {
+  hipLaunchKernelGGL((k_tree_eval<BLOCK, GRAD, SCREENED, KAHAN>), dim3(tree_grid(w.mpad / BLOCK, w.split)), dim3(BLOCK),
+                     0, st, Q, m, qperm, t.node, t.geo, t.mom, t.off + t.n, t.cap, w.src, t.n, kScaledScr, kappa,
+                     w.part, w.mpad, (unsigned)w.split, w.stop);
+}
+
 template <bool GRAD, bool SCREENED, bool KAHAN>
 void launch_eval_t(const float* Q, int64_t m, const int32_t* qperm, const GwnWork& w, const TreeWork& t,
                    float kappa, hipStream_t st) {
-  hipLaunchKernelGGL((k_tree_eval<GRAD, SCREENED, KAHAN>), dim3(tree_grid(w.mpad / kTreeBlock, w.split)),
-                     dim3(kTreeBlock), 0, st, Q, m, qperm, t.node, t.geo, t.mom, t.off + t.n, t.cap, w.src, t.n, kScaledScr, kappa,
-                     w.part, w.mpad, (unsigned)w.split, w.stop);
+  if (m >= kLoneQueries)
+    launch_eval_b<64, GRAD, SCREENED, KAHAN>(Q, m, qperm, w, t, kappa, st);
+  else
+    launch_eval_b<kTreeBlock, GRAD, SCREENED, KAHAN>(Q, m, qperm, w, t, kappa, st);
 }
 
 }  // namespace

@@ -130,13 +130,13 @@ dwg_status eval_prepare(const float* P, const float* N, const float* area, const
   if (!es->tree) {
     carve_gwn(c, n, m, choose_split(n, m, kp.split), same, &es->wk);
     DWG_PROPAGATE(launch_order(P, n, delta, kp.eps, position_scale(kp), Q, m, same, es->wk, st));
-    return launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), es->wk, st);
+    return launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), true, es->wk, st);
   }
   carve_gwn(c, n, m, segments > 0 ? segments : tree_segments(n, m), same, &es->wk);
   carve_tree(c, n, tree_leaf(kp), kp.tree_beta, &es->tw);
   DWG_PROPAGATE(tree_build(P, area, delta, n, kp.eps, es->tw, es->wk.perm_s, st));
   if (!same) DWG_PROPAGATE(spatial_sort(Q, m, nullptr, 0.0f, es->wk.sort, es->wk.perm_q, st));
-  DWG_PROPAGATE(launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), es->wk, st));
+  DWG_PROPAGATE(launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), false, es->wk, st));
   return tree_stage_leaves(es->wk, es->tw, position_scale(kp), st);
 }
 

@@ -277,14 +277,16 @@ __global__ __launch_bounds__(kQBlock) void k_gwn_small(
 // (kappa = the position scale of the kernel, 1 when plain; positions stay unscaled, the
 // evaluation kernels scale differences).
 // A NaN delta poisons the source's m so that the result is NaN as in the definition. Clears the
-// stop flag of an iteration.
-__global__ void k_stage(const float* __restrict__ P, const float* __restrict__ N,
+// stop flag of an iteration. With tbox (the all-pairs kernels'), a block is a source tile and writes its
+// box (real sources only) and largest radius max(delta, eps), in the unscaled units of the
+// positions (the staged 1/radius carries kappa).
+__global__ __launch_bounds__(kTile) void k_stage(const float* __restrict__ P, const float* __restrict__ N,
                         const float* __restrict__ A, const float* __restrict__ D, int64_t n,
-                        int64_t npad, float eps, float kappa, const int32_t* __restrict__ perm,
-                        float4* __restrict__ src, float* __restrict__ kk, int32_t* __restrict__ stop) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                        float eps, float kappa, const int32_t* __restrict__ perm,
+                        float4* __restrict__ src, float* __restrict__ kk, int32_t* __restrict__ stop,
+                        float4* __restrict__ tbox) {
+  const int64_t j = (int64_t)blockIdx.x * kTile + threadIdx.x;  // < npad
   if (j == 0) *stop = 0;
-  if (j >= npad) return;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = make_float4(0.f, 0.f, 0.f, 0.f);
   float k = 0.0f;
   if (j < n) {
@@ -300,37 +302,33 @@ __global__ void k_stage(const float* __restrict__ P, const float* __restrict__ N
   src[2 * j] = a;
   src[2 * j + 1] = b;
   kk[j] = k;
-}
-
-// Box of each source tile (real sources only) and its largest radius max(delta, eps), in the
-// unscaled units of the positions (the staged 1/radius carries kappa).
-__global__ __launch_bounds__(kTile) void k_tile_box(const float4* __restrict__ src, int64_t n, float kappa,
-                                                    float4* __restrict__ tbox) {
-  __shared__ float lds[7][kTile];
-  const int64_t j = (int64_t)blockIdx.x * kTile + threadIdx.x;
+  if (!tbox) return;
+  __shared__ float lds[7][kTile / 64];
   float v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0f};
   if (j < n) {
-    const float4 a = src[2 * j];
     v[0] = v[3] = a.x;
     v[1] = v[4] = a.y;
     v[2] = v[5] = a.z;
     v[6] = 1.0f / (kappa * a.w);  // radius (0 when 1/radius is +inf)
     if (!(v[6] == v[6])) v[6] = INFINITY;
   }
-  for (int d = 0; d < 7; ++d) lds[d][threadIdx.x] = v[d];
-  __syncthreads();
-  for (int s = kTile / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      for (int d = 0; d < 3; ++d) lds[d][threadIdx.x] = fminf(lds[d][threadIdx.x], lds[d][threadIdx.x + s]);
-      for (int d = 3; d < 7; ++d) lds[d][threadIdx.x] = fmaxf(lds[d][threadIdx.x], lds[d][threadIdx.x + s]);
+#pragma unroll
+  for (int d = 0; d < 7; ++d) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const float x = __shfl_xor(v[d], o, 64);
+      v[d] = d < 3 ? fminf(v[d], x) : fmaxf(v[d], x);
     }
-    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[d][threadIdx.x >> 6] = v[d];
   }
-  if (threadIdx.x == 0) {
-    tbox[2 * blockIdx.x] = make_float4(lds[0][0], lds[1][0], lds[2][0], lds[6][0]);
-    tbox[2 * blockIdx.x + 1] = make_float4(lds[3][0], lds[4][0], lds[5][0], 0.0f);
-  }
+  __syncthreads();
+  if (threadIdx.x > 0) return;
+#pragma unroll
+  for (int d = 0; d < 7; ++d)
+    for (int w = 0; w < kTile / 64; ++w) v[d] = d < 3 ? fminf(v[d], lds[d][w]) : fmaxf(v[d], lds[d][w]);
+  tbox[2 * blockIdx.x] = make_float4(v[0], v[1], v[2], v[6]);
+  tbox[2 * blockIdx.x + 1] = make_float4(v[3], v[4], v[5], 0.0f);
 }
+
 
 // Sum of `split` partials of accumulator `a` for sorted query i, in split order, eight loads in
 // flight at a time.
@@ -927,11 +925,9 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, 
 }
 
 dwg_status launch_stage(const float* P, const float* N, const float* area, const float* delta,
-                        int64_t n, float eps, float kappa, const GwnWork& w, hipStream_t stream) {
-  hipLaunchKernelGGL(k_stage, dim3((unsigned)cdiv(w.npad, 256)), dim3(256), 0, stream, P, N, area,
-                     delta, n, w.npad, eps, kappa, w.perm_s, w.src, w.kk, w.stop);
-  DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_tile_box, dim3((unsigned)w.ntiles), dim3(kTile), 0, stream, w.src, n, kappa, w.tbox);
+                        int64_t n, float eps, float kappa, bool tiles, const GwnWork& w, hipStream_t stream) {
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)w.ntiles), dim3(kTile), 0, stream, P, N, area, delta, n, eps, kappa,
+                     w.perm_s, w.src, w.kk, w.stop, tiles ? w.tbox : nullptr);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

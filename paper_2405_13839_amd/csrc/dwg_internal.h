@@ -300,8 +300,9 @@ dwg_status mlp_anchor_normals(const float* params, const AnchorRows& rows, int64
 // Launchers (all enqueue on `stream`; return DWG_OK or DWG_E_DEVICE).
 dwg_status launch_order(const float* P, int64_t n, const float* delta, float eps, float kappa, const float* Q,
                         int64_t m, bool same, const GwnWork& w, hipStream_t stream);
+// tiles: also the boxes of the source tiles, which the all-pairs kernels read.
 dwg_status launch_stage(const float* P, const float* N, const float* area, const float* delta,
-                        int64_t n, float eps, float kappa, const GwnWork& w, hipStream_t stream);
+                        int64_t n, float eps, float kappa, bool tiles, const GwnWork& w, hipStream_t stream);
 dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bool grad,
                       const GwnWork& w, hipStream_t stream);
 dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, float* wout,

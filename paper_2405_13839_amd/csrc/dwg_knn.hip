@@ -521,11 +521,27 @@ __global__ __launch_bounds__(kSetupBlock) void k_grid_setup(const float* __restr
 constexpr int kSmallRefs = 8192;
 constexpr int kSmallPer = kSmallRefs / kSetupBlock;
 
+constexpr int kBuckets = 4096;  // of the cell order of queries (k_order)
+
+// Clears what a search of the grid counts in: the bucket totals and the number of deferred items.
+// The grid's own kernels do it for the first search, k_order_clear for further ones.
+__device__ __forceinline__ void clear_queries(int64_t first, int64_t step, int32_t* __restrict__ total,
+                                              int32_t* __restrict__ defer) {
+  for (int64_t i = first; i < kBuckets; i += step) total[i] = 0;
+  if (first == 0) defer[0] = 0;
+}
+
+__global__ void k_order_clear(int32_t* __restrict__ total, int32_t* __restrict__ defer) {
+  clear_queries(blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, total, defer);
+}
+
 __global__ __launch_bounds__(kSetupBlock) void k_grid_small(const float* __restrict__ R, int64_t n,
                                                             int64_t max_cells, int k,
                                                             GridParams* __restrict__ gp,
                                                             int32_t* __restrict__ start,
-                                                            float4* __restrict__ sorted) {
+                                                            float4* __restrict__ sorted, int32_t* __restrict__ total,
+                                                            int32_t* __restrict__ defer) {
+  clear_queries(threadIdx.x, kSetupBlock, total, defer);
   __shared__ SetupLds s;
   __shared__ int tab[kSetupTable];
   __shared__ int32_t lds[kSetupBlock / 64];
@@ -570,11 +586,13 @@ __global__ __launch_bounds__(kSetupBlock) void k_grid_small(const float* __restr
 // Clears the cell counts (ncells + 1 of them) and the scan state (as many words as tiles of the
 // actual grid need).
 __global__ void k_grid_zero(const GridParams* __restrict__ gp, int32_t* __restrict__ count,
-                            unsigned long long* __restrict__ state) {
+                            unsigned long long* __restrict__ state, int32_t* __restrict__ total,
+                            int32_t* __restrict__ defer) {
   const int64_t nc = gp->ncells, words = 1 + (nc + kScanTile - 1) / kScanTile;
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = t0; i <= nc; i += step) count[i] = 0;
   for (int64_t i = t0; i < words; i += step) state[i] = 0ull;
+  clear_queries(t0, step, total, defer);
 }
 
 // Cell of each reference point and its rank among the cell's points (arbitrary order).
@@ -954,7 +972,6 @@ __global__ __launch_bounds__(256) void k_knn(QuerySet qs, const GridParams* __re
 constexpr int kOrderBlock = 1024;
 constexpr int kOrderPer = 8;
 constexpr int kOrderTile = kOrderBlock * kOrderPer;
-constexpr int kBuckets = 4096;
 
 __device__ __forceinline__ uint32_t spread4(uint32_t v) {
   return (v & 1u) | (v & 2u) << 2 | (v & 4u) << 4 | (v & 8u) << 6;
@@ -970,13 +987,6 @@ __device__ __forceinline__ int bucket_of(const GridParams& g, int sh, float x, f
 __device__ __forceinline__ int bucket_shift(const GridParams& g) {
   const int top = max(g.nx, max(g.ny, g.nz)) - 1;
   return top > 15 ? 28 - __clz(top) : 0;
-}
-
-// Clears the bucket totals and the count of deferred items.
-__global__ void k_order_clear(int32_t* __restrict__ total, int32_t* __restrict__ defer) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kBuckets) total[i] = 0;
-  if (i == 0) defer[0] = 0;
 }
 
 // FILL = false: adds the block's bucket counts to total. FILL = true: total holds the buckets'
@@ -1551,14 +1561,16 @@ void launch_knn_k(hipStream_t st, const QuerySet& qs, const KnnWork& w, int rcap
 dwg_status build_grid(const float* R, int64_t nr, int k, const KnnWork& w, hipStream_t st) {
   const int64_t mc = max_cells_for(nr);
   if (nr <= kSmallRefs) {
-    hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(kSetupBlock), 0, st, R, nr, mc, k, w.gp, w.start, w.sorted);
+    hipLaunchKernelGGL(k_grid_small, dim3(1), dim3(kSetupBlock), 0, st, R, nr, mc, k, w.gp, w.start, w.sorted,
+                       w.total, w.defer);
     DWG_TRY_LAUNCH();
     return DWG_OK;
   }
   hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kSetupBlock), 0, st, R, nr, mc, k, w.gp);
   DWG_TRY_LAUNCH();
   // the launches cover the largest possible grid (the actual one has <= mc cells)
-  hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(mc + 1, 256, 1024)), dim3(256), 0, st, w.gp, w.start, w.state);
+  hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(mc + 1, 256, 1024)), dim3(256), 0, st, w.gp, w.start, w.state,
+                     w.total, w.defer);
   DWG_TRY_LAUNCH();
   hipLaunchKernelGGL(k_cell_count, dim3(grid_for(nr)), dim3(256), 0, st, R, nr, w.gp, w.key, w.rank, w.start);
   DWG_TRY_LAUNCH();
@@ -1570,16 +1582,17 @@ dwg_status build_grid(const float* R, int64_t nr, int k, const KnnWork& w, hipSt
   return DWG_OK;
 }
 
-// kOwnOrder: the queries are exactly the m references of the grid, q0 = 0, skip_mode 1.
+// kOwnOrder: the queries are exactly the m references of the grid, q0 = 0, skip_mode 1. first: no search
+// has used the grid since it was built.
 dwg_status knn_query(const float* Q, int64_t qld, int64_t q0, int64_t m, const KnnWork& w, int skip_mode,
-                     int64_t stride, int k, const KnnEmit& em, hipStream_t st, QueryOrder order) {
+                     int64_t stride, int k, const KnnEmit& em, hipStream_t st, QueryOrder order, bool first = false) {
   if (m > w.mq) {  // the deferred list holds at most w.mq items
     set_error("internal: %lld kNN queries exceed the carved capacity %lld", (long long)m, (long long)w.mq);
     return DWG_E_INVALID;
   }
   if (m <= 0) return DWG_OK;
   QuerySet qs{Q, qld, q0, m, order == kOwnOrder ? w.sorted : nullptr, skip_mode, stride};
-  if (order != kGivenOrder) {
+  if (order != kGivenOrder && !first) {
     hipLaunchKernelGGL(k_order_clear, dim3(kBuckets / 256), dim3(256), 0, st, w.total, w.defer);
     DWG_TRY_LAUNCH();
   }
@@ -1623,7 +1636,7 @@ dwg_status knn_emit(const float* R, int64_t nr, const float* Q, int64_t m, int s
   if (s != DWG_OK) return s;
   // queries that are the references themselves (same array, same count) run in cell order
   const QueryOrder order = self_skip && Q == R && m == nr ? kOwnOrder : kAnyOrder;
-  return knn_query(Q, m, 0, m, w, self_skip ? 1 : 0, 1, k, em, stream, order);
+  return knn_query(Q, m, 0, m, w, self_skip ? 1 : 0, 1, k, em, stream, order, true);
 }
 
 }  // namespace

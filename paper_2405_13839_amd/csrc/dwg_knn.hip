@@ -92,7 +92,9 @@ __global__ __launch_bounds__(256) void k_bbox_final(const float* __restrict__ pa
 
 // ---- Grid setup ----
 constexpr int kSetupBlock = 1024;
-constexpr int kSample = 4096;                       // points the grid is laid out from
+// Points the grid is laid out from (4,096: areas of 131,072 points 369 us, 354 with 2,048; 10 nearest of
+// 50,001 points 106, 101).
+constexpr int kSample = 2048;
 constexpr int kSamplePer = kSample / kSetupBlock;   // of them per thread
 constexpr int kTrimBins = 1024;
 constexpr int kTrimLevels = 3;

@@ -2,7 +2,7 @@
 // "Poisson Kernels": mean distance to the k nearest neighbours) and the k = 16 anchor
 // features of the learned initial normals.
 //
-// Grid build: the box is the range of a stratified sample of at most 4096 points (all of them
+// Grid build: the box is the range of a stratified sample of at most kSample points (all of them
 // below that), trimmed per axis to the sample's quantiles 1/1024 and 1 - 1/1024; the cell size
 // is the one at which a point is expected to share its cell with kCellShare * k others, from
 // the sample's pair counts on two coarse grids (k_grid_setup); counting sort of the reference

@@ -687,8 +687,7 @@ struct DistList {
   __device__ __forceinline__ int index(int) const { return 0; }
 };
 
-// What a finished query writes: its neighbour list, or the kernel radius that the list gives
-// (k_delta_window's and the mean distance's arithmetic, without storing the lists).
+// What a finished query writes: its neighbour list, or the kernel radius that the list gives.
 enum EmitMode { kEmitList = 0, kEmitMean = 1, kEmitWindow = 2, kEmitScaled = 3 };
 struct KnnEmit {
   int mode;

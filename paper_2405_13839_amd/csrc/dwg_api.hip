@@ -20,6 +20,31 @@ void set_error(const char* fmt, ...) {
   va_end(ap);
 }
 
+static constexpr int kDefaultLeaf = 32;
+
+static bool tree_mode(const dwg_kernel_params& kp) { return kp.tree_beta > 0.0f; }
+static int tree_leaf(const dwg_kernel_params& kp) { return kp.tree_leaf > 0 ? kp.tree_leaf : kDefaultLeaf; }
+
+// Layout of an evaluation: the sorted sources and queries, the partial sums and the octree.
+static void carve_eval(Carver& c, int64_t n, int64_t m, const dwg_kernel_params& kp, int segments, bool same,
+                       GwnWork* wk, TreeWork* tw) {
+  if (!tree_mode(kp)) {
+    carve_gwn(c, n, m, choose_split(n, m, kp.split), split_columns(n, m, kp.split), same, wk);
+    return;
+  }
+  if (segments > 0)
+    carve_gwn(c, n, m, segments, segments * padded_queries(m), same, wk);
+  else
+    carve_gwn(c, n, m, tree_segments(n, m), segment_columns(n, m), same, wk);
+  carve_tree(c, n, tree_leaf(kp), kp.tree_beta, tw);
+}
+
+size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp, int segments) {
+  Carver c(nullptr);
+  carve_eval(c, n_src, n_qry, kp, segments, false, nullptr, nullptr);
+  return c.used;
+}
+
 }  // namespace dwg
 
 using namespace dwg;
@@ -41,10 +66,6 @@ namespace {
   } while (0)
 
 const dwg_kernel_params kDefaultKp = {0.0f, 0.0f, 1, 0, 0.0f, 0, {0, 0}};
-constexpr int kDefaultLeaf = 32;
-
-bool tree_mode(const dwg_kernel_params& kp) { return kp.tree_beta > 0.0f; }
-int tree_leaf(const dwg_kernel_params& kp) { return kp.tree_leaf > 0 ? kp.tree_leaf : kDefaultLeaf; }
 
 dwg_status check_kp(const dwg_kernel_params* kp) {
   if (!kp) return DWG_OK;
@@ -102,18 +123,6 @@ struct EventPair {
   }
 };
 
-// segments: of the octree's node list (0 = the rule of tree_segments).
-size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp, int segments = 0) {
-  Carver c(nullptr);
-  if (tree_mode(kp)) {
-    carve_gwn(c, n_src, n_qry, segments > 0 ? segments : tree_segments(n_src, n_qry), false, nullptr);
-    carve_tree(c, n_src, tree_leaf(kp), kp.tree_beta, nullptr);
-  } else {
-    carve_gwn(c, n_src, n_qry, choose_split(n_src, n_qry, kp.split), false, nullptr);
-  }
-  return c.used;
-}
-
 // Carves the evaluation state, orders sources and queries and stages the sources: the
 // all-pairs tiles, or the octree with its node summaries.
 struct EvalState {
@@ -127,13 +136,11 @@ dwg_status eval_prepare(const float* P, const float* N, const float* area, const
                         hipStream_t st, EvalState* es, int segments = 0) {
   Carver c(ws);
   es->tree = tree_mode(kp);
+  carve_eval(c, n, m, kp, segments, same, &es->wk, &es->tw);
   if (!es->tree) {
-    carve_gwn(c, n, m, choose_split(n, m, kp.split), same, &es->wk);
     DWG_PROPAGATE(launch_order(P, n, delta, kp.eps, position_scale(kp), Q, m, same, es->wk, st));
     return launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), true, es->wk, st);
   }
-  carve_gwn(c, n, m, segments > 0 ? segments : tree_segments(n, m), same, &es->wk);
-  carve_tree(c, n, tree_leaf(kp), kp.tree_beta, &es->tw);
   DWG_PROPAGATE(tree_build(P, area, delta, n, kp.eps, es->tw, es->wk.perm_s, st));
   if (!same) DWG_PROPAGATE(spatial_sort(Q, m, nullptr, 0.0f, es->wk.sort, es->wk.perm_q, st));
   DWG_PROPAGATE(launch_stage(P, N, area, delta, n, kp.eps, position_scale(kp), false, es->wk, st));
@@ -216,6 +223,12 @@ dwg_status mc_prepare(const float* P, const float* N, const float* area, const f
   carve_mc_faces(c, n, C, mp, w);
   int64_t m = 0;
   DWG_PROPAGATE(mc_corners(mp, *w, &m, st));
+  // the layout is for the queries there are, within the room for as many as there could be
+  const size_t used = align256(c.used + gwn_bytes(n, w->ld, kp));
+  if (used > need) {
+    set_error("internal: %zu bytes to be laid out, %zu counted", used, need);
+    return DWG_E_WORKSPACE;
+  }
   if (mp.iso_points) DWG_PROPAGATE(mc_append_points(P, n, *w, st));
   DWG_PROPAGATE(knn_grid(P, n, mp.k, w->knn, st));
   DWG_PROPAGATE(mc_clear(*w, st));
@@ -403,7 +416,7 @@ dwg_status dwg_octree_work(const float* P, const float* area, const float* delta
   DWG_CHECK(kpp && tree_mode(*kpp), "kp->tree_beta must be > 0 (octree mode)");
   const dwg_kernel_params kp = *kpp;
   Carver need(nullptr);
-  carve_gwn(need, n, m, 1, false, nullptr);
+  carve_gwn(need, n, m, 1, padded_queries(m), false, nullptr);
   carve_tree(need, n, tree_leaf(kp), kp.tree_beta, nullptr);
   need.take<unsigned long long>(kTreeWorkCounts);
   DWG_CHECK(ws || ws_bytes == 0, "ws is NULL but ws_bytes > 0");
@@ -417,7 +430,7 @@ dwg_status dwg_octree_work(const float* P, const float* area, const float* delta
   Carver c(ws);
   GwnWork wk;
   TreeWork tw;
-  carve_gwn(c, n, m, 1, same, &wk);
+  carve_gwn(c, n, m, 1, padded_queries(m), same, &wk);
   carve_tree(c, n, tree_leaf(kp), kp.tree_beta, &tw);
   unsigned long long* cnt = c.take<unsigned long long>(kTreeWorkCounts);
   DWG_PROPAGATE(tree_build(P, area, delta, n, kp.eps, tw, wk.perm_s, st));
@@ -644,7 +657,7 @@ dwg_status dwg_octree(const float* P, int64_t n, int leaf, int32_t* perm, int32_
   dwg_kernel_params kp = kDefaultKp;
   kp.tree_beta = 2.3f;
   kp.tree_leaf = leaf;
-  const size_t need = gwn_bytes(n, n, kp);
+  const size_t need = gwn_bytes(n, n, kp, 1);
   DWG_CHECK(ws || ws_bytes == 0, "ws is NULL but ws_bytes > 0");
   if (!ws || ws_bytes < need) {
     set_error("workspace too small: %zu bytes given, %zu needed", ws_bytes, need);
@@ -655,7 +668,7 @@ dwg_status dwg_octree(const float* P, int64_t n, int leaf, int32_t* perm, int32_
   Carver c(ws);
   GwnWork wk;
   TreeWork tw;
-  carve_gwn(c, n, n, 1, true, &wk);
+  carve_gwn(c, n, n, 1, padded_queries(n), true, &wk);
   carve_tree(c, n, tree_leaf(kp), kp.tree_beta, &tw);
   DWG_PROPAGATE(tree_build(P, nullptr, nullptr, n, 0.0f, tw, perm, st));
   return tree_export(tw, nodes, cap, count, st);

@@ -911,16 +911,31 @@ int choose_split(int64_t n_src, int64_t n_qry, int requested) {
   return (int)s;
 }
 
-size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, GwnWork* out) {
+// choose_split's rules times the blocks of queries, each by a bound that never falls as sources or queries
+// grow: cdiv(B, x) x <= B - 1 + x. (`fill` takes the larger count of blocks and the finer step where the
+// launch is not a small one, since launches of fewer queries can be.)
+int64_t split_columns(int64_t n_src, int64_t n_qry, int requested) {
+  const int64_t qblocks = cdiv(n_qry, kQBlock);
+  if (requested > 0) return choose_split(n_src, n_qry, requested) * qblocks * kQBlock;
+  const int64_t ntiles = cdiv(n_src, kTile);
+  const int64_t rounds = std::min<int64_t>(32768 - 1 + qblocks, std::max<int64_t>(1, ntiles / 8) * qblocks);
+  const int64_t fill = std::min<int64_t>((small_launch(n_src, n_qry) ? kSmallBlocks : kFillBlocks) - 1 + qblocks,
+                                         cdiv(n_src, kSmallStep) * qblocks);
+  const int64_t memory = std::max<int64_t>(16 * qblocks, kAutoSplitBytes / ((int64_t)kNAcc * 4 * kQBlock));
+  const int64_t blocks = std::min<int64_t>(std::min<int64_t>(std::max<int64_t>(rounds, fill), memory), kMaxSplit * qblocks);
+  return std::max<int64_t>(blocks, qblocks) * kQBlock;
+}
+
+size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, int64_t columns, bool same, GwnWork* out) {
   GwnWork w{};
   w.n_src = n_src;
   w.ntiles = cdiv(n_src, kTile);
   w.npad = w.ntiles * kTile;
-  w.mpad = cdiv(n_qry, kQBlock) * kQBlock;
+  w.mpad = padded_queries(n_qry);
   w.split = split;
   const size_t start = c.used;
   w.src = c.take<float4>(2 * (size_t)w.npad);
-  w.part = c.take<float>((size_t)split * kNAcc * (size_t)w.mpad);
+  w.part = c.take<float>((size_t)columns * kNAcc);
   w.kk = c.take<float>((size_t)w.npad);
   w.theta = c.take<double>((size_t)std::max(n_src, n_qry));
   w.blk = c.take<double>(2 * (size_t)std::max<int64_t>(cdiv(std::max(n_src, n_qry), 256), kEpiSmall / 64));

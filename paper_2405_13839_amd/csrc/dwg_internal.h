@@ -67,6 +67,13 @@ float position_scale(const dwg_kernel_params& kp);
 // Split count for the all-pairs kernels.
 int choose_split(int64_t n_src, int64_t n_qry, int requested);
 
+// Columns of partial sums (split x padded queries) that a layout for n_src sources and n_qry queries
+// has room for. The automatic count of splits rises in steps as the queries fall, so that fewer
+// queries can take more columns; the room is a bound for every smaller count too, and never falls
+// as either number grows: a layout for some bound of the queries holds what is carved for the actual
+// ones, and a workspace for the largest call serves the smaller ones.
+int64_t split_columns(int64_t n_src, int64_t n_qry, int requested);
+
 // Uniform grid over a reference point set (dwg_knn.hip).
 struct GridParams {
   float ox, oy, oz;  // origin (minimum corner of the trimmed box)
@@ -136,7 +143,7 @@ constexpr int kStatsRow = 6;
 constexpr int kAhead = 8;  // iterations that the host launches before it reads their statistics
 struct GwnWork {
   float4* src;        // [2 * npad]: (px,py,pz,1/rho_min), (mx,my,mz,0) per sorted source
-  float* part;        // [split][kNAcc][mpad] per-split partial sums (sorted queries)
+  float* part;        // [split][kNAcc][mpad] per-split partial sums (sorted queries), in room for split_columns
   float* kk;          // [npad] a_j / (4 pi), for restaging after the update
   double* theta;      // [m] angle change in degrees (iterate)
   double* blk;        // [2 * nblk] per-block FP64 partial sums
@@ -156,7 +163,12 @@ struct GwnWork {
   uint64_t* clock() const { return reinterpret_cast<uint64_t*>(stats + kStatsRow * slot + 4); }
 };
 
-size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, bool same, GwnWork* out);
+// columns: room for partial sums, at least split x padded queries (split_columns, segment_columns).
+size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, int64_t columns, bool same, GwnWork* out);
+inline int64_t padded_queries(int64_t n_qry) { return cdiv(n_qry, kQBlock) * kQBlock; }
+// Workspace bytes of an evaluation; never falls as n_src or n_qry grows, for segments = 0. segments: of
+// the octree's node list (0 = the rule of tree_segments).
+size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp, int segments = 0);
 
 // Octree of the sources for the Sec. 5.2 traversal (dwg_tree.hip): Morton-sorted sources,
 // nodes in depth-first pre-order, node summaries; carved from the workspace.
@@ -185,6 +197,8 @@ struct TreeWork {
 int64_t tree_cap(int64_t n);
 // Segments of the node list that an evaluation walks separately (GwnWork::split of octree mode).
 int tree_segments(int64_t n_src, int64_t n_qry);
+// Their columns of partial sums (as split_columns).
+int64_t segment_columns(int64_t n_src, int64_t n_qry);
 size_t carve_tree(Carver& c, int64_t n, int leaf, double beta, TreeWork* out);
 // Sorts the sources (perm[i] = index of the i-th sorted source) and builds the nodes; with
 // area != NULL also the node centres, radii and opening radii.

@@ -917,6 +917,12 @@ int tree_segments(int64_t n_src, int64_t n_qry) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(s, kMaxSegments));
 }
 
+// cdiv(B, x) x <= B - 1 + x for the wavefronts; the columns are padded to eight of them.
+int64_t segment_columns(int64_t n_src, int64_t n_qry) {
+  const int64_t waves = padded_queries(n_qry) / 64, most = std::min<int64_t>(cdiv(n_src, kSegmentSources), kMaxSegments);
+  return 64 * std::min<int64_t>(most * waves, kSegmentWaves + waves + (kQBlock / 64) * kMaxSegments);
+}
+
 dwg_status morton_frame(const float* P, int64_t n, float* bpart, float* box, double* frame, hipStream_t st) {
   dwg_status s = launch_bbox(P, n, bpart, box, st);
   if (s != DWG_OK) return s;

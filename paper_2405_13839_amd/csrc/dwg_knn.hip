@@ -114,7 +114,7 @@ constexpr float kCellShare = 0.6f;
 struct SetupLds {
   int hist[3 * kTrimBins];
   int wtot[kSetupBlock / 64];
-  int found[3][2], shrunk;
+  int found[3][2], shrunk[kTrimLevels];  // a flag per level: none is written again while others read it
   int64_t below_lo[3], below[3];
   double range[6];
   float red[6][kSetupBlock / 64];
@@ -236,6 +236,7 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
   for (int i = t; i < 3 * kTrimBins; i += kSetupBlock) s.hist[i] = 0;
   for (int i = t; i < kSetupTable; i += kSetupBlock) tab[i] = 0;
   if (t < 2) s.pairs[t] = 0;
+  if (t < kTrimLevels) s.shrunk[t] = 0;
   __syncthreads();
   if (t < 3) {
     float lo = s.red[t][0], hi = s.red[3 + t][0];
@@ -247,6 +248,7 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
     s.range[2 * t + 1] = hi;
     s.below[t] = 0;
   }
+  __syncthreads();
   // Trimming: each level narrows an axis to the bins that hold the ranks floor(S / 1024) and
   // S - 1 - floor(S / 1024) of the sample's coordinates. A range whose ranks are not found
   // (NaN coordinates) is kept. Once no axis shrinks below kTrimEnough of its bins, its ends are
@@ -254,8 +256,6 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
   const int64_t rlo = S / kTrimBins, rhi = S - 1 - S / kTrimBins;
   bool again = rlo > 0;
   for (int level = 0; level < kTrimLevels && again; ++level) {
-    if (t == 0) s.shrunk = 0;
-    __syncthreads();
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const double lo = s.range[2 * d], hi = s.range[2 * d + 1];
@@ -310,13 +310,12 @@ __device__ void grid_setup(const float* __restrict__ R, int64_t n, int64_t max_c
         s.range[2 * t] = lo + blo * w;
         s.range[2 * t + 1] = bhi == kTrimBins - 1 ? hi : lo + (bhi + 1) * w;
         s.below[t] = s.below_lo[t];
-        if (bhi - blo + 1 < kTrimEnough) s.shrunk = 1;
+        if (bhi - blo + 1 < kTrimEnough) s.shrunk[level] = 1;
       }
     }
     __syncthreads();
-    again = s.shrunk != 0;
+    again = s.shrunk[level] != 0;
   }
-  __syncthreads();
   // Pair counts of the sample on the trimmed box cut into 32 and 16 cells along its longest
   // axis: sum over the points of the other points in their cell.
   double emax = 0.0;

@@ -621,8 +621,8 @@ __global__ void k_scatter(const float* __restrict__ R, int64_t n, const int32_t*
 
 // A candidate (d2, j) as one FP64 number: the bits of d2 (>= 0) plus 2^20 in the high word, j (>= 0)
 // in the low word. Positive FP64 numbers order like their bits, so keys order like the pairs
-// (d2, j); 2^20 keeps every key a normal number and d2 = +inf a finite one. The high word of a
-// NaN d2, as an unsigned integer, is above that of every key.
+// (d2, j); 2^20 keeps every key a normal number and d2 = +inf a finite one. A NaN d2 makes no key (its
+// bits can wrap around to a small high word): it is turned away by a comparison of the distances.
 constexpr uint32_t kKeyBias = 0x00100000u;
 constexpr uint32_t kKeyInf = 0x7f800000u + kKeyBias;
 
@@ -654,9 +654,8 @@ struct PairList {
     for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, 0x7fffffff);
   }
   __device__ __forceinline__ void offer(float d2, int j) {
-    const uint32_t hi = __float_as_uint(d2) + kKeyBias;
-    if (hi > key_high(b[K - 1])) return;
-    const double x = __hiloint2double((int)hi, j);
+    if (!(d2 <= key_d2(b[K - 1]))) return;
+    const double x = __hiloint2double((int)(__float_as_uint(d2) + kKeyBias), j);
 #pragma unroll
     for (int u = K - 1; u >= 1; --u) b[u] = key_max(b[u - 1], key_min(b[u], x));
     b[0] = key_min(b[0], x);
@@ -1183,7 +1182,8 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
             const float4 sp = sorted[at < l0r ? lo + at : hi1 + (at - l0r)];
             j = __float_as_int(sp.w);
             const float ex = sp.x - qx, ey = sp.y - qy, ez = sp.z - qz;
-            if (j != skip) hi = __float_as_uint(fmaf(ez, ez, fmaf(ey, ey, ex * ex))) + kKeyBias;
+            const float d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+            if (j != skip && d2 <= INFINITY) hi = __float_as_uint(d2) + kKeyBias;  // not a NaN
           }
           unsigned long long mask = __ballot(hi <= worst);
           if (__popcll(mask) > kMergeFrom) {

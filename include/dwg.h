@@ -287,7 +287,9 @@ dwg_status dwg_init_normals(dwg_init_kind kind, uint64_t seed, const float* P, i
  * grid (Sec. 5.1 uses kNN for the kernel radius and the normal update). async.
  *   R: reference points [3][nr]; Q: queries [3][m]; self_skip: 1 when Q is R itself (then
  *   query i never returns reference i), else 0. idx: output int32 [m][k] (ascending
- *   distance); dist: output float32 [m][k] or NULL. Distances are Euclidean in FP32.
+ *   distance); dist: output float32 [m][k] or NULL. Distances are Euclidean in FP32. A NaN
+ *   reference is never listed; entries that no reference fills (a NaN query's, or with fewer than k
+ *   references that are not NaN) are 0x7fffffff with distance +inf.
  */
 dwg_status dwg_knn(const float* R, int64_t nr, const float* Q, int64_t m, int self_skip, int k,
                    int32_t* idx, float* dist, void* ws, size_t ws_bytes, void* stream);

@@ -642,6 +642,11 @@ __device__ __forceinline__ double key_max(double a, double b) {
   return r;
 }
 
+// The index of an entry that no reference has filled: a NaN query's, or one of a set with too few
+// references that are not NaN. dwg_knn hands it out; the other users of a list never read by it.
+constexpr int32_t kNoRef = 0x7fffffff;
+__device__ __forceinline__ int32_t filled(int32_t j, int32_t other) { return j == kNoRef ? other : j; }
+
 // The K best candidates of a query, ascending. As pairs: an inserted key x makes b[u]
 // max(b[u - 1], min(b[u], x)), two FP64 instructions per slot (ranking the pairs by compares and
 // selects took eight).
@@ -651,7 +656,7 @@ struct PairList {
   double b[K];
   __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, 0x7fffffff);
+    for (int u = 0; u < K; ++u) b[u] = __hiloint2double((int)kKeyInf, kNoRef);
   }
   __device__ __forceinline__ void offer(float d2, int j) {
     if (!(d2 <= key_d2(b[K - 1]))) return;
@@ -691,7 +696,8 @@ struct KnnEmit {
   int mode;
   int32_t* idx;   // [m][k]
   float* dist;    // [m][k] or NULL
-  float* delta;   // [m]; kEmitScaled (the indices too): the inverse of the mean distance
+  float* delta;   // [m]; kEmitScaled (the indices too, 0 for those not filled, whose mean distance is
+                  // infinite): the inverse of the mean distance
   float scale;    // kEmitMean
   float vmin, vmax;  // kEmitWindow
 };
@@ -723,7 +729,7 @@ __device__ __forceinline__ void emit_query(const KnnEmit& e, int64_t q, const Li
     }
     e.delta[q] = inverse_mean(s, K);
 #pragma unroll
-    for (int u = 0; u < K; ++u) e.idx[q * K + u] = b.index(u);
+    for (int u = 0; u < K; ++u) e.idx[q * K + u] = filled(b.index(u), 0);
   } else {
     // the mean of the distances that lie in [vmin, vmax]; when none does, the mean of all k
     // clamped to [vmin, vmax] (Sec. 5.2 "Poisson Kernels")
@@ -771,7 +777,7 @@ __device__ __forceinline__ void emit_wave(const KnnEmit& e, int64_t q, int k, do
     if (lane == 0) e.delta[q] = e.scale * (s / (float)k);
   } else if (e.mode == kEmitScaled) {
     if (lane == 0) e.delta[q] = inverse_mean(s, k);
-    if (lane < k) e.idx[q * k + lane] = __double2loint(key);
+    if (lane < k) e.idx[q * k + lane] = filled(__double2loint(key), 0);
   } else {
     double r = c > 0 ? sd / c : all / k;
     if (c == 0) r = r < e.vmin ? e.vmin : (r > e.vmax ? e.vmax : r);
@@ -1144,7 +1150,7 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
     const KnnQuery kq = knn_query_of(qs, defer[1 + item]);
     const float qx = kq.x, qy = kq.y, qz = kq.z;
     const int skip = kq.skip;
-    double key = __hiloint2double((int)kKeyInf, 0x7fffffff);  // list entry lane % 16
+    double key = __hiloint2double((int)kKeyInf, kNoRef);      // list entry lane % 16
     uint32_t worst = kKeyInf;                                 // high word of entry k - 1
     int cx, cy, cz;
     cell_of(g, qx, qy, qz, cx, cy, cz);
@@ -1177,7 +1183,7 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
           const int32_t at = base + lane - __shfl(from, row, 64), l0r = __shfl(len0, row, 64);
           const int32_t lo = __shfl(b0, row, 64), hi1 = __shfl(b1, row, 64);
           uint32_t hi = 0xffffffffu;
-          int j = 0x7fffffff;
+          int j = kNoRef;
           if (base + lane < all) {
             const float4 sp = sorted[at < l0r ? lo + at : hi1 + (at - l0r)];
             j = __float_as_int(sp.w);
@@ -1188,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_knn_wave(QuerySet qs, const GridParams*
           unsigned long long mask = __ballot(hi <= worst);
           if (__popcll(mask) > kMergeFrom) {
             const bool in = hi <= worst;
-            key = merge_keys(key, __hiloint2double(in ? (int)hi : (int)kKeyInf, in ? j : 0x7fffffff));
+            key = merge_keys(key, __hiloint2double(in ? (int)hi : (int)kKeyInf, in ? j : kNoRef));
             worst = (uint32_t)__builtin_amdgcn_readlane(__double2hiint(key), k - 1);
             continue;
           }
@@ -1301,7 +1307,7 @@ __global__ void k_pca_normals(const float* __restrict__ P, int64_t n, const int3
   if (i >= n) return;
   double mx = P[i], my = P[n + i], mz = P[2 * n + i];
   for (int t = 0; t < k; ++t) {
-    const int64_t j = idx[i * k + t];
+    const int64_t j = filled(idx[i * k + t], (int32_t)i);
     mx += P[j];
     my += P[n + j];
     mz += P[2 * n + j];
@@ -1312,7 +1318,7 @@ __global__ void k_pca_normals(const float* __restrict__ P, int64_t n, const int3
   mz *= inv;
   double a[6] = {0, 0, 0, 0, 0, 0};
   for (int t = -1; t < k; ++t) {
-    const int64_t j = t < 0 ? i : (int64_t)idx[i * k + t];
+    const int64_t j = t < 0 ? i : (int64_t)filled(idx[i * k + t], (int32_t)i);
     const double x = P[j] - mx, y = P[n + j] - my, z = P[2 * n + j] - mz;
     a[0] += x * x;
     a[1] += x * y;
@@ -1366,8 +1372,8 @@ __global__ __launch_bounds__(4 * kCellPoints) void k_voronoi_area(const float* _
   const int64_t base = (int64_t)blockIdx.x * kCellPoints;
   const int np = (int)(n - base < kCellPoints ? n - base : kCellPoints);
   for (int e = tid; e < np * m; e += 4 * kCellPoints) {
-    const int64_t j = idx[base * m + e];
     const int pt = e / m, t = e - pt * m;
+    const int64_t j = filled(idx[base * m + e], (int32_t)(base + pt));
     nb[0][t][pt] = P[j];
     nb[1][t][pt] = P[n + j];
     nb[2][t][pt] = P[2 * n + j];

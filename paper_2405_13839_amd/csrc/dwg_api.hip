@@ -37,6 +37,7 @@ static void carve_eval(Carver& c, int64_t n, int64_t m, const dwg_kernel_params&
   else
     carve_gwn(c, n, m, tree_segments(n, m), segment_columns(n, m), same, wk);
   carve_tree(c, n, tree_leaf(kp), kp.tree_beta, tw);
+  if (wk) wk->walk = true;
 }
 
 size_t gwn_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params& kp, int segments) {

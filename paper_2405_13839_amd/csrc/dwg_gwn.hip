@@ -333,20 +333,28 @@ __global__ __launch_bounds__(kTile) void k_stage(const float* __restrict__ P, co
 // Sum of `split` partials of accumulator `a` for sorted query i, in split order, eight loads in
 // flight at a time; whole batches without a check of each (the update of 2,000 points 11.2 -> 9.3 us,
 // of 20,011 13.1 -> 11.0, the epilogue of 100K queries 28.6 -> 24.8; batches of 16 no faster, at 1M
-// points slower).
-__device__ __forceinline__ float combine(const float* part, int split, int64_t mpad, int na, int a, int64_t i,
-                                         bool kahan) {
+// points slower). The sum is compensated, also where the partials are not: finer splits and segments then
+// cost no precision. A Kahan step loses the low bits of the running sum where the partial is the larger of
+// the two, which is the rule in an octree walk (one segment holds the near field): TWO takes the exact error
+// of every addition instead, for two additions more. Error of octree gradients against 64 bits, over
+// 1,500 to 100,000 points, in units of one walk without segments: 1.02 with Kahan steps from 20,000 points on, 1.00
+// with exact ones (four iterations 0.77 to 0.93); without compensation 1.1 to 1.4, now 0.9 to 0.96. All-pairs,
+// not compensated, 16,000 to 50,000 points, in units of the coarser splits: 1.06 to 1.11, now 0.89 to 0.96.
+template <bool TWO>
+__device__ __forceinline__ float combine(const float* part, int split, int64_t mpad, int na, int a, int64_t i) {
   const float* p = part + (int64_t)a * mpad + i;
   const int64_t step = (int64_t)na * mpad;
   float s = 0.0f, c = 0.0f;
   auto add = [&](float x) {
-    if (kahan) {
+    if (TWO) {
+      const float t = s + x, b = t - s;
+      c -= (s - (t - b)) + (x - b);
+      s = t;
+    } else {
       const float y = x - c;
       const float t = s + y;
       c = (t - s) - y;
       s = t;
-    } else {
-      s += x;
     }
   };
   constexpr int kBatch = 8;
@@ -368,7 +376,7 @@ __device__ __forceinline__ float combine(const float* part, int split, int64_t m
       add(x[u]);
     }
   }
-  return kahan ? s - c : s;
+  return s - c;
 }
 
 // The epilogue kernels take QB queries per block: its kEpiBlock threads first sum the splits of
@@ -379,11 +387,11 @@ constexpr int kEpiBlock = 64 * kNAcc;
 constexpr int kEpiWaves = kNAcc;
 constexpr int64_t kEpiSmall = 32768;  // queries up to which QB = 64: at 256 a few blocks would do it all
 
-template <int QB>
+template <int QB, bool TWO>
 __device__ __forceinline__ void combine_block(const float* part, int split, int64_t mpad, int na, int64_t q0,
-                                              bool kahan, float (*acc)[QB]) {
+                                              float (*acc)[QB]) {
   for (int i = threadIdx.x; i < na * QB; i += kEpiBlock)
-    acc[i / QB][i % QB] = combine(part, split, mpad, na, i / QB, q0 + i % QB, kahan);
+    acc[i / QB][i % QB] = combine<TWO>(part, split, mpad, na, i / QB, q0 + i % QB);
   __syncthreads();
 }
 
@@ -413,17 +421,17 @@ Scale scale_of(const dwg_kernel_params& kp) {
 
 // Evaluation epilogue: combine splits; write w and grad at the query's original index;
 // FP64 block partial of w.
-template <int QB>
+template <int QB, bool TWO>
 __global__ __launch_bounds__(kEpiBlock) void k_combine(const float* __restrict__ part, int split,
                                                        int64_t mpad, int64_t m, bool grad, Scale sc,
-                                                       bool kahan, const int32_t* __restrict__ qperm,
+                                                       const int32_t* __restrict__ qperm,
                                                        float* __restrict__ wout,
                                                        float* __restrict__ gout,
                                                        double* __restrict__ blk) {
   __shared__ float acc[kNAcc][QB];
   __shared__ double lds[kEpiWaves];
   const int64_t q0 = (int64_t)blockIdx.x * QB;  // mpad is a multiple of QB
-  combine_block<QB>(part, split, mpad, grad ? kNAcc : 1, q0, kahan, acc);
+  combine_block<QB, TWO>(part, split, mpad, grad ? kNAcc : 1, q0, acc);
   const int t = threadIdx.x;
   const int64_t i = q0 + t;
   double wv = 0.0;
@@ -443,9 +451,9 @@ __global__ __launch_bounds__(kEpiBlock) void k_combine(const float* __restrict__
 // written in place at the point's original index; restage m for the next iteration;
 // theta_i (degrees, FP64); FP64 block partials of w and of the chord |n_new - n_old|. Clears the
 // histograms of the selection that follows. After the iteration has stopped, nothing else changes.
-template <int QB>
+template <int QB, bool TWO>
 __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ part, int split,
-                                                      int64_t mpad, int64_t n, Scale sc, bool kahan,
+                                                      int64_t mpad, int64_t n, Scale sc,
                                                       const int32_t* __restrict__ perm,
                                                       const float* __restrict__ kk,
                                                       float* __restrict__ N,
@@ -460,7 +468,7 @@ __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ 
   clear_hist(hist, n);
   if (*stop) return;
   if ((blockIdx.x | threadIdx.x) == 0) *end = wall_clock64();
-  combine_block<QB>(part, split, mpad, kNAcc, q0, kahan, acc);
+  combine_block<QB, TWO>(part, split, mpad, kNAcc, q0, acc);
   const int t = threadIdx.x;
   const int64_t i = q0 + t;
   double wv = 0.0, cv = 0.0;
@@ -985,16 +993,28 @@ dwg_status launch_gwn(const float* Q, int64_t m, const dwg_kernel_params& kp, bo
   return DWG_OK;
 }
 
+// Which sums of partials take exact errors (see combine): gradients of octree walks, and all partials that
+// are not compensated themselves. Kahan steps are enough for the others: all-pairs with compensation has 0.4 to
+// 1.0 times the error of the coarser splits, octree values 0.6 to 0.97 times that of one walk.
+static bool two_sum(const GwnWork& w, const dwg_kernel_params& kp, bool grad) {
+  return kp.compensated == 0 || (w.walk && grad);
+}
+
+template <int QB, bool TWO>
+static void combine_t(int nb, int64_t m, const dwg_kernel_params& kp, bool grad, float* wout, float* gout,
+                      const GwnWork& w, hipStream_t stream) {
+  hipLaunchKernelGGL((k_combine<QB, TWO>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
+                     scale_of(kp), w.perm_q, wout, gout, w.blk);
+}
+
 dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, float* wout,
                           float* gout, double* wmean, const GwnWork& w, hipStream_t stream) {
   const int qb = m <= kEpiSmall ? 64 : 256;
   const int nb = (int)cdiv(m, qb);
-  if (qb == 64)
-    hipLaunchKernelGGL((k_combine<64>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
-                       scale_of(kp), kp.compensated != 0, w.perm_q, wout, gout, w.blk);
-  else
-    hipLaunchKernelGGL((k_combine<256>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, m, grad,
-                       scale_of(kp), kp.compensated != 0, w.perm_q, wout, gout, w.blk);
+  const bool two = two_sum(w, kp, grad);
+  auto* const run = qb == 64 ? (two ? combine_t<64, true> : combine_t<64, false>)
+                             : (two ? combine_t<256, true> : combine_t<256, false>);
+  run(nb, m, kp, grad, wout, gout, w, stream);
   DWG_TRY_LAUNCH();
   if (wmean) {
     hipLaunchKernelGGL(k_mean, dim3(1), dim3(kRedBlock), 0, stream, w.blk, nb, m, wmean);
@@ -1003,18 +1023,20 @@ dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, flo
   return DWG_OK;
 }
 
+template <int QB, bool TWO>
+static void update_t(int nb, int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, hipStream_t stream) {
+  hipLaunchKernelGGL((k_update<QB, TWO>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
+                     w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist, w.stop, w.clock() + 1);
+}
+
 dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, int* nblk,
                          hipStream_t stream) {
   const int qb = n <= kEpiSmall ? 64 : 256;
   const int nb = (int)cdiv(n, qb);
-  if (qb == 64)
-    hipLaunchKernelGGL((k_update<64>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
-                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist, w.stop,
-                       w.clock() + 1);
-  else
-    hipLaunchKernelGGL((k_update<256>), dim3(nb), dim3(kEpiBlock), 0, stream, w.part, w.split, w.mpad, n, scale_of(kp),
-                       kp.compensated != 0, w.perm_s, w.kk, N, w.src, w.theta, w.blk, nb, w.hist, w.stop,
-                       w.clock() + 1);
+  const bool two = two_sum(w, kp, true);
+  auto* const run = qb == 64 ? (two ? update_t<64, true> : update_t<64, false>)
+                             : (two ? update_t<256, true> : update_t<256, false>);
+  run(nb, n, kp, N, w, stream);
   DWG_TRY_LAUNCH();
   *nblk = nb;
   return DWG_OK;

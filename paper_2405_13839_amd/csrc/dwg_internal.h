@@ -159,6 +159,7 @@ struct GwnWork {
   SortWork sort;
   int64_t n_src, npad, mpad, ntiles;
   int split;
+  bool walk = false;  // octree mode: the splits are segments of one walk
   int slot;           // row of stats that the next launches write
   uint64_t* clock() const { return reinterpret_cast<uint64_t*>(stats + kStatsRow * slot + 4); }
 };

@@ -521,8 +521,12 @@ __global__ __launch_bounds__(kRedBlock) void k_mean(const double* __restrict__ b
 // Above that, two histograms over all angles fix the top 28 bits of the k-th largest
 // (k_sel_hist), the few angles that share them are gathered while those above are summed
 // (k_sel_collect), and one block finishes (k_stats_final): 4 launches, against 19 for a
-// select of 8 bits per pass. No floating-point sum depends on the order of an atomic: the gathered
-// angles share an exponent, so theirs is an integer sum.
+// select of 8 bits per pass. Where more angles share the 28 bits than that block holds (near convergence the
+// changes of the FP32 normals are few distinct values), three more histograms over all angles fix the other 36
+// bits (k_sel_collect, k_sel_deep; their launches end at once otherwise). One block going through all angles
+// again took 0.8 us per 1,000 of them: 3.8 ms of an iteration of 1M tied points, 0.04 now. It still does for up
+// to kSelDeepMin angles (32 for each thread). No floating-point sum depends on the order of
+// an atomic: the angles that share the bits share an exponent, so theirs is an integer sum.
 constexpr int kSelBlock = 1024;
 constexpr int kSelPer = 16;
 constexpr int kSelRegs = kSelBlock * kSelPer;
@@ -690,7 +694,7 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restr
 }
 
 // sel[0] = first digit, sel[1] = values among the k largest with that digit, sel[2] = gathered
-// values. MID = false: histogram of the first digit. MID = true: finds the first digit and takes
+// values (the rest of sel: k_sel_collect, k_sel_deep). MID = false: histogram of the first digit. MID = true: finds the first digit and takes
 // the histogram of the second among the values that have it.
 template <bool MID>
 __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const double* __restrict__ theta, int64_t n, int64_t k,
@@ -726,20 +730,67 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const double* __restrict
     if (bins[i]) atomicAdd(&mine[i], bins[i]);
 }
 
-// Gathers the values with the selected 28 top bits (as many as fit cand) and sums, per block, the
-// values above them. sel[3] = their lowest bit pattern, sel[4] = how many are among the k largest.
+// The histograms of the other 36 bits, 12 at a time from the top: counts, and for the upper two the sums of
+// the bits below the digit.
+struct SelDeep {
+  uint32_t* cnt[3];
+  unsigned long long* sum[2];
+  __device__ __forceinline__ explicit SelDeep(uint32_t* hist) {
+    uint32_t* const p = hist + kSelHistLen;
+    for (int l = 0; l < 3; ++l) cnt[l] = p + l * kSelDeepBins;
+    for (int l = 0; l < 2; ++l) sum[l] = reinterpret_cast<unsigned long long*>(p + (3 + 2 * l) * kSelDeepBins);
+  }
+};
+static_assert(kSelHistLen % 2 == 0 && kSelDeepBins == 1 << 12, "64-bit sums behind the counts, 12-bit digits");
+
+struct DeepLds {
+  unsigned cnt[kSelDeepBins];
+  unsigned long long sum[kSelDeepBins];
+};
+
+// Histogram LEVEL of the offsets (36 bits, in their bucket) for which `take` holds.
+template <int LEVEL, class F>
+__device__ void deep_hist(const double* __restrict__ theta, int64_t n, uint64_t lo, F take, const SelDeep& d,
+                          DeepLds& h) {
+  constexpr int sh = 24 - 12 * LEVEL;
+  for (int i = threadIdx.x; i < kSelDeepBins; i += kSelBlock) {
+    h.cnt[i] = 0;
+    h.sum[i] = 0;
+  }
+  __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * kSelBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelBlock) {
+    const uint64_t b = (uint64_t)__double_as_longlong(theta[i]), o = b - lo;
+    if (b < lo || o >= (1ull << kMidShift) || !take(o)) continue;
+    const int at = (int)(o >> sh) & (kSelDeepBins - 1);
+    atomicAdd(&h.cnt[at], 1u);
+    if (LEVEL < 2) atomicAdd(&h.sum[at], (unsigned long long)(o & ((1ull << sh) - 1ull)));
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSelDeepBins; i += kSelBlock) {
+    if (!h.cnt[i]) continue;
+    atomicAdd(&d.cnt[LEVEL][i], h.cnt[i]);
+    if (LEVEL < 2) atomicAdd(&d.sum[LEVEL < 2 ? LEVEL : 0][i], h.sum[i]);
+  }
+}
+
+// Sums, per block, the values above those with the selected 28 top bits, and gathers those that have them, or,
+// where they are too many for that (and n > kSelDeepMin), counts the first 12 of their other bits. sel[3] =
+// their lowest bit pattern, sel[4] = how many are among the k largest, sel[5] = how many there are.
 __global__ __launch_bounds__(kSelBlock) void k_sel_collect(const double* __restrict__ theta, int64_t n,
-                                                           const uint32_t* __restrict__ hist,
+                                                           uint32_t* __restrict__ hist,
                                                            uint64_t* __restrict__ sel, uint64_t* __restrict__ cand,
                                                            double* __restrict__ top) {
   __shared__ SelLds s;
+  __shared__ DeepLds h;
   __shared__ double lds[kSelBlock / 64];
   const uint64_t first = sel[0], krem = sel[1];
   find_bin([&](int i) { return hist[kTopBins + i]; }, kMidBins, krem, s);
   const uint64_t lo = (first << kTopShift) | ((uint64_t)s.digit << kMidShift), next = lo + (1ull << kMidShift);
+  const bool deep = n > kSelDeepMin && s.count > kSelRegs;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     sel[3] = lo;
     sel[4] = krem - s.above;
+    sel[5] = s.count;
   }
   double v = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kSelBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelBlock) {
@@ -747,18 +798,67 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_collect(const double* __restr
     const uint64_t b = (uint64_t)__double_as_longlong(x);
     if (b >= next) {
       v += x;
-    } else if (b >= lo) {
+    } else if (b >= lo && !deep) {
       const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(&sel[2]), 1ull);
       if (at < kSelRegs) cand[at] = b;
     }
   }
   const double b = block_sum(v, lds);
   if (threadIdx.x == 0) top[blockIdx.x] = b;
+  if (deep) deep_hist<0>(theta, n, lo, [](uint64_t) { return true; }, SelDeep(hist), h);
+}
+
+// LEVEL 1, 2: finds the digit of the level before and takes the histogram of the next 12 bits among the
+// offsets that have it; nothing to do where the values were gathered. sel[4 + 2 LEVEL] = the digits found so far,
+// sel[5 + 2 LEVEL] = values among the k largest that have them.
+template <int LEVEL>
+__global__ __launch_bounds__(kSelBlock) void k_sel_deep(const double* __restrict__ theta, int64_t n,
+                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel) {
+  if (sel[5] <= kSelRegs) return;
+  __shared__ SelLds s;
+  __shared__ DeepLds h;
+  const SelDeep d(hist);
+  const uint64_t krem = LEVEL == 1 ? sel[4] : sel[7], found = LEVEL == 1 ? 0 : sel[6];
+  find_bin([&](int i) { return d.cnt[LEVEL - 1][i]; }, kSelDeepBins, krem, s);
+  const uint64_t digits = (found << 12) | (uint64_t)s.digit;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sel[4 + 2 * LEVEL] = digits;
+    sel[5 + 2 * LEVEL] = krem - s.above;
+  }
+  deep_hist<LEVEL>(theta, n, sel[3], [&](uint64_t o) { return (o >> (36 - 12 * LEVEL)) == digits; }, d, h);
+}
+
+// Count and sum (minus base each) of the offsets that are among the k largest, but for those equal to the k-th:
+// of the bins above the digit found, level by level. Adds this thread's share; *kth = the k-th
+// largest offset, *krem = how many of its copies are among the k largest. Block-wide.
+__device__ void deep_sum(const SelDeep& d, const uint64_t* __restrict__ sel, SelLds& s, uint64_t* hi, uint64_t* lo,
+                         uint64_t* cnt, uint64_t* kth, uint64_t* krem) {
+  const uint64_t left = sel[9], found = sel[8];
+  find_bin([&](int i) { return d.cnt[2][i]; }, kSelDeepBins, left, s);
+  *kth = (found << 12) | (uint64_t)s.digit;
+  *krem = left - s.above;
+#pragma unroll
+  for (int level = 0; level < 3; ++level) {
+    const int sh = 24 - 12 * level;
+    const uint64_t digits = *kth >> sh, before = digits & ~(uint64_t)(kSelDeepBins - 1);
+    for (int i = (int)(digits & (kSelDeepBins - 1)) + 1 + threadIdx.x; i < kSelDeepBins; i += kSelBlock) {
+      const uint64_t c = d.cnt[level][i], o = (before | (uint64_t)i) << sh;
+      *hi += c * (o >> 18);
+      *lo += c * (o & 0x3ffffull);
+      if (level < 2) {
+        const uint64_t x = d.sum[level < 2 ? level : 0][i];
+        *hi += x >> 18;
+        *lo += x & 0x3ffffull;
+      }
+      *cnt += c;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restrict__ theta, int64_t n, int64_t k,
                                                            const double* __restrict__ blk, int nblk,
                                                            const double* __restrict__ iso,
+                                                           uint32_t* __restrict__ hist,
                                                            const uint64_t* __restrict__ sel,
                                                            const uint64_t* __restrict__ cand,
                                                            const double* __restrict__ top, int ntop, double* stats,
@@ -771,40 +871,47 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restr
   if (t < 2) part[t] = 0;
   if (t == 2) cnt = 0;
   mean_stats(blk, nblk, n, iso, lds, stats);
-  const uint64_t m = sel[2], base = sel[3];
-  const bool held = m <= kSelRegs;  // else (tens of thousands of nearly equal angles) from all angles
-  uint64_t v[kSelPer];
-#pragma unroll
-  for (int j = 0; j < kSelPer; ++j) {
-    const uint64_t i = t + j * kSelBlock;
-    v[j] = held && i < m ? cand[i] : ~0ull;
-  }
-  const uint64_t last = base + ((1ull << kMidShift) - 1ull);
-  auto visit = [&](auto f) {
-    if (held) {
-#pragma unroll
-      for (int j = 0; j < kSelPer; ++j)
-        if (v[j] != ~0ull) f(v[j]);
-    } else {
-      for (int64_t i = t; i < n; i += kSelBlock) {
-        const uint64_t b = (uint64_t)__double_as_longlong(theta[i]);
-        if (b >= base && b <= last) f(b);
-      }
-    }
-  };
-  Range r{base, kMidShift, sel[4], sel[4] == m};
-  narrow(visit, r, s);
-  // sum of the gathered values among the k largest but for the ones equal to the k-th: they share
-  // an exponent, so value = base + (bits - base) ulp
+  const uint64_t base = sel[3];
+  // sum of the values among the k largest but for the ones equal to the k-th: they share an exponent, so
+  // value = base + (bits - base) ulp
   uint64_t hi = 0, lo = 0, c = 0;
-  visit([&](uint64_t b) {
-    if (r.whole ? b >= r.lo : b > r.lo) {
-      const uint64_t d = b - base;
-      hi += d >> 18;
-      lo += d & 0x3ffffull;
-      ++c;
+  Range r{base, 0, 0, false};
+  if (n > kSelDeepMin && sel[5] > kSelRegs) {
+    deep_sum(SelDeep(hist), sel, s, &hi, &lo, &c, &r.lo, &r.krem);
+    r.lo += base;
+  } else {
+    const uint64_t m = sel[2];
+    const bool held = m <= kSelRegs;  // else (n <= kSelDeepMin, nearly all angles nearly equal) from all angles
+    uint64_t v[kSelPer];
+#pragma unroll
+    for (int j = 0; j < kSelPer; ++j) {
+      const uint64_t i = t + j * kSelBlock;
+      v[j] = held && i < m ? cand[i] : ~0ull;
     }
-  });
+    const uint64_t last = base + ((1ull << kMidShift) - 1ull);
+    auto visit = [&](auto f) {
+      if (held) {
+#pragma unroll
+        for (int j = 0; j < kSelPer; ++j)
+          if (v[j] != ~0ull) f(v[j]);
+      } else {
+        for (int64_t i = t; i < n; i += kSelBlock) {
+          const uint64_t b = (uint64_t)__double_as_longlong(theta[i]);
+          if (b >= base && b <= last) f(b);
+        }
+      }
+    };
+    r = Range{base, kMidShift, sel[4], sel[4] == m};
+    narrow(visit, r, s);
+    visit([&](uint64_t b) {
+      if (r.whole ? b >= r.lo : b > r.lo) {
+        const uint64_t d = b - base;
+        hi += d >> 18;
+        lo += d & 0x3ffffull;
+        ++c;
+      }
+    });
+  }
   for (int o = 32; o > 0; o >>= 1) {
     hi += __shfl_xor((unsigned long long)hi, o, 64);
     lo += __shfl_xor((unsigned long long)lo, o, 64);
@@ -949,8 +1056,8 @@ size_t carve_gwn(Carver& c, int64_t n_src, int64_t n_qry, int split, int64_t col
   w.blk = c.take<double>(2 * (size_t)std::max<int64_t>(cdiv(std::max(n_src, n_qry), 256), kEpiSmall / 64));
   w.stats = c.take<double>(kStatsRow * kAhead);
   w.stop = c.take<int32_t>(1);
-  w.hist = c.take<uint32_t>(kSelHistLen);
-  w.sel = c.take<uint64_t>(5);
+  w.hist = c.take<uint32_t>(kSelHistLen + kSelDeepLen);
+  w.sel = c.take<uint64_t>(kSelState);
   w.cand = c.take<uint64_t>(kSelSmallMax);
   w.top = c.take<double>(256);
   w.tbox = c.take<float4>(2 * (size_t)w.ntiles);
@@ -1066,8 +1173,14 @@ dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, 
   DWG_TRY_LAUNCH();
   hipLaunchKernelGGL(k_sel_collect, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, w.cand, w.top);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kSelBlock), 0, stream, w.theta, n, k, w.blk, nblk, iso, w.sel, w.cand,
-                     w.top, hb, stats, eps_deg, stop);
+  if (n > kSelDeepMin) {
+    hipLaunchKernelGGL(k_sel_deep<1>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel);
+    DWG_TRY_LAUNCH();
+    hipLaunchKernelGGL(k_sel_deep<2>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel);
+    DWG_TRY_LAUNCH();
+  }
+  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kSelBlock), 0, stream, w.theta, n, k, w.blk, nblk, iso, w.hist, w.sel,
+                     w.cand, w.top, hb, stats, eps_deg, stop);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

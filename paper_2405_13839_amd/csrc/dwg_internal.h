@@ -36,12 +36,17 @@ constexpr int64_t kAutoSplitBytes = int64_t(512) << 20;  // partial sums of an a
 constexpr int kRedBlock = 256;  // threads per block for O(n) epilogue / reductions
 constexpr int64_t kSelSmallMax = 16384;  // angles up to which one block selects the largest
 constexpr int kSelHistLen = 16640;       // histogram words of the selection above that
+constexpr int64_t kSelDeepMin = 32768;   // angles from which ties are narrowed by all blocks (see k_sel_deep)
+constexpr int kSelDeepBins = 4096;
+constexpr int kSelState = 10;
+constexpr int kSelDeepLen = 3 * kSelDeepBins + 2 * 2 * kSelDeepBins;  // words of its counts and 64-bit sums
 constexpr int kMaxK = 16;       // largest k for the kNN kernels
 
 // Clears the selection's histograms where it will use them (all blocks of the launch together).
 __device__ __forceinline__ void clear_hist(uint32_t* hist, int64_t n) {
   if (n <= kSelSmallMax) return;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSelHistLen; i += gridDim.x * blockDim.x) hist[i] = 0;
+  const int len = n > kSelDeepMin ? kSelHistLen + kSelDeepLen : kSelHistLen;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) hist[i] = 0;
 }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -149,8 +154,8 @@ struct GwnWork {
   double* blk;        // [2 * nblk] per-block FP64 partial sums
   double* stats;      // [kAhead][kStatsRow] device statistics, and the clock at either end of the evaluation
   int32_t* stop;      // [1] set when an iteration has ended
-  uint32_t* hist;     // [kSelHistLen] histograms of the top-k selection
-  uint64_t* sel;      // [5] its state
+  uint32_t* hist;     // [kSelHistLen + kSelDeepLen] histograms of the top-k selection
+  uint64_t* sel;      // [kSelState] its state
   uint64_t* cand;     // [kSelSmallMax] angles near the k-th largest
   double* top;        // [256] block sums of the angles above them
   float4* tbox;       // [2 * ntiles] source tile boxes and radii

@@ -471,11 +471,13 @@ dwg_status dwg_iterate(const float* P, const float* area, const float* delta, in
   GwnWork& wk = es.wk;
   // kAhead iterations are launched before the statistics of the first are read (an iteration of
   // 2,000 points takes 30 us on the GPU, a copy and a wait as long again). The statistics
-  // kernel itself decides whether its iteration was the last: the evaluations and updates behind
+  // kernel itself decides whether its iteration was the last: the kernels behind
   // it then return at once, so N_inout holds the iterate it ended with. Four iterations of 2,000 /
   // 20,011 points (octree), with their preparation, us: 305 / 918 with a wait for each, 262 / 838 with
   // events around each evaluation, which the GPU waits 5 us for, 241 / 805 with the kernels reading
-  // the clock.
+  // the clock. A solve that ends in its first iteration pays for the launches behind it: octree
+  // solves of 2,000 / 20,011 / 1M points 266 / 476 / 6,217 us, calls of one iteration 210 / 380 / 5,835
+  // (359 / 625 / 6,528 when the moments and statistics behind the last iteration still ran).
   double all[kStatsRow * kAhead];
   int dev = 0, khz = 0;
   DWG_TRY_HIP(hipGetDevice(&dev));

@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kEpiBlock) void k_combine(const float* __restrict__
 // Iteration epilogue (Eq. 7): n_new = -grad/|grad| (kept when |grad| is 0 or not finite),
 // written in place at the point's original index; restage m for the next iteration;
 // theta_i (degrees, FP64); FP64 block partials of w and of the chord |n_new - n_old|. Clears the
-// histograms of the selection that follows. After the iteration has stopped, nothing else changes.
+// histograms of the selection that follows. After the iteration has stopped, nothing changes.
 template <int QB, bool TWO>
 __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ part, int split,
                                                       int64_t mpad, int64_t n, Scale sc,
@@ -465,8 +465,8 @@ __global__ __launch_bounds__(kEpiBlock) void k_update(const float* __restrict__ 
   __shared__ float acc[kNAcc][QB];
   __shared__ double lds[kEpiWaves];
   const int64_t q0 = (int64_t)blockIdx.x * QB;
-  clear_hist(hist, n);
   if (*stop) return;
+  clear_hist(hist, n);
   if ((blockIdx.x | threadIdx.x) == 0) *end = wall_clock64();
   combine_block<QB, TWO>(part, split, mpad, kNAcc, q0, acc);
   const int t = threadIdx.x;
@@ -641,6 +641,7 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restr
                                                            const double* __restrict__ blk, int nblk,
                                                            const double* __restrict__ iso, double* stats,
                                                            double eps_deg, int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
   __shared__ SelLds s;
   __shared__ double lds[kSelBlock / 64];
   __shared__ uint64_t ext[2][kSelBlock / 64];
@@ -698,7 +699,9 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restr
 // the histogram of the second among the values that have it.
 template <bool MID>
 __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const double* __restrict__ theta, int64_t n, int64_t k,
-                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel) {
+                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel,
+                                                        const int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
   __shared__ SelLds s;
   __shared__ unsigned bins[MID ? kMidBins : kTopBins];
   constexpr int kBins = MID ? kMidBins : kTopBins;
@@ -779,7 +782,9 @@ __device__ void deep_hist(const double* __restrict__ theta, int64_t n, uint64_t 
 __global__ __launch_bounds__(kSelBlock) void k_sel_collect(const double* __restrict__ theta, int64_t n,
                                                            uint32_t* __restrict__ hist,
                                                            uint64_t* __restrict__ sel, uint64_t* __restrict__ cand,
-                                                           double* __restrict__ top) {
+                                                           double* __restrict__ top,
+                                                           const int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
   __shared__ SelLds s;
   __shared__ DeepLds h;
   __shared__ double lds[kSelBlock / 64];
@@ -813,8 +818,9 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_collect(const double* __restr
 // sel[5 + 2 LEVEL] = values among the k largest that have them.
 template <int LEVEL>
 __global__ __launch_bounds__(kSelBlock) void k_sel_deep(const double* __restrict__ theta, int64_t n,
-                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel) {
-  if (sel[5] <= kSelRegs) return;
+                                                        uint32_t* __restrict__ hist, uint64_t* __restrict__ sel,
+                                                        const int32_t* __restrict__ stop) {
+  if ((stop && *stop) || sel[5] <= kSelRegs) return;
   __shared__ SelLds s;
   __shared__ DeepLds h;
   const SelDeep d(hist);
@@ -863,6 +869,7 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_final(const double* __restr
                                                            const uint64_t* __restrict__ cand,
                                                            const double* __restrict__ top, int ntop, double* stats,
                                                            double eps_deg, int32_t* __restrict__ stop) {
+  if (stop && *stop) return;
   __shared__ SelLds s;
   __shared__ double lds[kSelBlock / 64];
   __shared__ unsigned long long part[2];  // integer sum of the low bits, in two halves
@@ -1167,16 +1174,17 @@ dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, 
     return DWG_OK;
   }
   const int hb = (int)std::min<int64_t>(cdiv(n, kSelBlock), kSelGrid);
-  hipLaunchKernelGGL((k_sel_hist<false>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel);
+  hipLaunchKernelGGL((k_sel_hist<false>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel, stop);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL((k_sel_hist<true>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel);
+  hipLaunchKernelGGL((k_sel_hist<true>), dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, k, w.hist, w.sel, stop);
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_sel_collect, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, w.cand, w.top);
+  hipLaunchKernelGGL(k_sel_collect, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, w.cand, w.top,
+                     stop);
   DWG_TRY_LAUNCH();
   if (n > kSelDeepMin) {
-    hipLaunchKernelGGL(k_sel_deep<1>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel);
+    hipLaunchKernelGGL(k_sel_deep<1>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, stop);
     DWG_TRY_LAUNCH();
-    hipLaunchKernelGGL(k_sel_deep<2>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel);
+    hipLaunchKernelGGL(k_sel_deep<2>, dim3(hb), dim3(kSelBlock), 0, stream, w.theta, n, w.hist, w.sel, stop);
     DWG_TRY_LAUNCH();
   }
   hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(kSelBlock), 0, stream, w.theta, n, k, w.blk, nblk, iso, w.hist, w.sel,

@@ -329,8 +329,8 @@ dwg_status launch_combine(int64_t m, const dwg_kernel_params& kp, bool grad, flo
                           float* gout, double* wmean, const GwnWork& w, hipStream_t stream);
 // The update writes *nblk block partials; launch_stats reads as many. iso: where stats[0] comes from
 // instead of the partials of w (NULL: from those). The statistics go to row w.slot of w.stats; with
-// `stop`, the flag is set when they end the iteration (see dwg_iterate): evaluations and updates
-// launched behind then do nothing.
+// `stop`, the flag is set when they end the iteration (see dwg_iterate): every kernel launched behind then
+// returns at once.
 dwg_status launch_update(int64_t n, const dwg_kernel_params& kp, float* N, const GwnWork& w, int* nblk,
                          hipStream_t stream);
 dwg_status launch_stats(int64_t n, double top_frac, const GwnWork& w, int nblk, const double* iso,

@@ -266,7 +266,8 @@ __device__ __forceinline__ void node_sum(const F& f, const double* __restrict__ 
 // Tile sums, a wavefront per tile; the first launch of an evaluation, so it notes the clock.
 template <class F>
 __global__ __launch_bounds__(256) void k_tile_sums(F f, int64_t n, int64_t tiles, double* __restrict__ tile,
-                                                   uint64_t* __restrict__ begin) {
+                                                   const int32_t* __restrict__ stop, uint64_t* __restrict__ begin) {
+  if (*stop) return;
   if ((blockIdx.x | threadIdx.x) == 0) *begin = wall_clock64();
   const int lane = threadIdx.x & 63;
   for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < tiles; t += (int64_t)gridDim.x * 4) {
@@ -481,7 +482,8 @@ __global__ void k_tree_crit(const int4* __restrict__ node, const int32_t* __rest
 // Node moments for the current normals: M = sum of the staged m_j over the node (FP64).
 __global__ __launch_bounds__(256) void k_tree_mom(const int4* __restrict__ node, const int32_t* __restrict__ total_p,
                                                   int64_t cap, MomentSum f, const double* __restrict__ tile,
-                                                  float4* __restrict__ mom) {
+                                                  const int32_t* __restrict__ stop, float4* __restrict__ mom) {
+  if (*stop) return;
   const int64_t total = node_count(total_p, cap);
   const int lane = threadIdx.x & 63;
   const int64_t step = (int64_t)gridDim.x * 16;
@@ -1012,9 +1014,10 @@ dwg_status tree_moments(const GwnWork& w, const TreeWork& t, hipStream_t st) {
   const MomentSum f{w.src};
   const int64_t tiles = cdiv(t.n, kSumTile);
   hipLaunchKernelGGL(k_tile_sums<MomentSum>, dim3((unsigned)cdiv(tiles, 4)), dim3(256), 0, st, f, t.n, tiles, t.tile,
-                     w.clock());
+                     w.stop, w.clock());
   DWG_TRY_LAUNCH();
-  hipLaunchKernelGGL(k_tree_mom, dim3(node_grid(t.n)), dim3(256), 0, st, t.node, t.off + t.n, t.cap, f, t.tile, t.mom);
+  hipLaunchKernelGGL(k_tree_mom, dim3(node_grid(t.n)), dim3(256), 0, st, t.node, t.off + t.n, t.cap, f, t.tile,
+                     w.stop, t.mom);
   DWG_TRY_LAUNCH();
   return DWG_OK;
 }

@@ -376,7 +376,7 @@ __device__ __forceinline__ float combine(const float* part, int split, int64_t m
       add(x[u]);
     }
   }
-  return s - c;
+  return TWO && !(c == c) ? s : s - c;  // an infinite partial has no error to take
 }
 
 // The epilogue kernels take QB queries per block: its kEpiBlock threads first sum the splits of

@@ -334,9 +334,9 @@ __global__ __launch_bounds__(kTile) void k_stage(const float* __restrict__ P, co
 // flight at a time; whole batches without a check of each (the update of 2,000 points 11.2 -> 9.3 us,
 // of 20,011 13.1 -> 11.0, the epilogue of 100K queries 28.6 -> 24.8; batches of 16 no faster, at 1M
 // points slower). The sum is compensated, also where the partials are not: finer splits and segments then
-// cost no precision. A Kahan step loses the low bits of the running sum where the partial is the larger of
+// cost no precision. A Kahan step (Kahan 1965) loses the low bits of the running sum where the partial is the larger of
 // the two, which is the rule in an octree walk (one segment holds the near field): TWO takes the exact error
-// of every addition instead, for two additions more. Error of octree gradients against 64 bits, over
+// of every addition instead (Knuth's two-sum), for two additions more. Error of octree gradients against 64 bits, over
 // 1,500 to 100,000 points, in units of one walk without segments: 1.02 with Kahan steps from 20,000 points on, 1.00
 // with exact ones (four iterations 0.77 to 0.93); without compensation 1.1 to 1.4, now 0.9 to 0.96. All-pairs,
 // not compensated, 16,000 to 50,000 points, in units of the coarser splits: 1.06 to 1.11, now 0.89 to 0.96.

@@ -122,7 +122,7 @@ struct SetupLds {
   GridParams gp;
 };
 
-__device__ __forceinline__ uint32_t hash32(uint32_t x) {  // a 32-bit integer mixer
+__device__ __forceinline__ uint32_t hash32(uint32_t x) {  // the integer mixer lowbias32 (C. Wellons, hash-prospector, 2018)
   x ^= x >> 16;
   x *= 0x7feb352du;
   x ^= x >> 15;
@@ -418,7 +418,8 @@ __global__ __launch_bounds__(kScanOneBlock) void k_scan_one(int32_t* __restrict_
   if (threadIdx.x == 0) a[n] = carry;
 }
 
-// In-place exclusive scan in one pass over the array (chained scan with look-back): a block
+// In-place exclusive scan in one pass over the array (chained scan with look-back, after Merrill and Garland,
+// "Single-pass Parallel Prefix Scan with Decoupled Look-back", 2016): a block
 // takes the next tile from a ticket counter, publishes the tile's sum, and adds up the sums of
 // the tiles before it, a wavefront's 64 at a time, back to the nearest one whose full prefix is
 // known. A tile's state is one 64-bit word (flag << 32 | value), written and read by device
@@ -525,7 +526,8 @@ constexpr int kSmallPer = kSmallRefs / kSetupBlock;
 constexpr int kBuckets = 4096;  // of the cell order of queries (k_order)
 
 // Clears what a search of the grid counts in: the bucket totals and the number of deferred items.
-// The grid's own kernels do it for the first search, k_order_clear for further ones.
+// The grid's own kernels do it for a search that follows at once (lists and radii of a cloud's own grid);
+// k_order_clear does it before each search of an anchor grid.
 __device__ __forceinline__ void clear_queries(int64_t first, int64_t step, int32_t* __restrict__ total,
                                               int32_t* __restrict__ defer) {
   for (int64_t i = first; i < kBuckets; i += step) total[i] = 0;

@@ -19,7 +19,7 @@ namespace {
 // One launch per pass instead of five (digit counts, a three-launch scan, scatter): the digit
 // totals of every pass are counted up front in one sweep over the keys (a pass only permutes
 // them), and within a pass each block publishes its tile's digit counts and adds up those of the
-// tiles before it (chained scan with look-back, one thread per digit). A pass over few tiles is a
+// tiles before it (chained scan with look-back after Merrill and Garland, 2016, one thread per digit). A pass over few tiles is a
 // chain of device-scope round trips (ticket, counts, look-back): 24 -> 14 us for 20,011 64-bit
 // keys; 1M keys 35 -> 25 us.
 constexpr int kRsThreads = 512;

@@ -241,7 +241,7 @@ def gwn_static(P, N, area, delta, Q, params: Params | None = None, want_wmean=Fa
 def iterate(P, area, delta, N, params: Params | None = None, max_iters=50, fixed_iters=False, eps_deg=0.1,
             top_frac=0.01, ws=None):
     """Run Algorithm 1 in place on N ([3, n] float32). Returns (status, stats float64 [T, 4]):
-    per iteration wmean, top-1% mean angle change (deg), mean chord, all-pairs kernel ms."""
+    per iteration wmean, top-1% mean angle change (deg), mean chord, evaluation ms."""
     lib = load()
     params = params or Params()
     P = _pts(P, "P")

@@ -695,8 +695,8 @@ __global__ __launch_bounds__(kSelBlock) void k_stats_small(const double* __restr
 }
 
 // sel[0] = first digit, sel[1] = values among the k largest with that digit, sel[2] = gathered
-// values (the rest of sel: k_sel_collect, k_sel_deep). MID = false: histogram of the first digit. MID = true: finds the first digit and takes
-// the histogram of the second among the values that have it.
+// values (the rest of sel: k_sel_collect, k_sel_deep). MID = false: histogram of the first digit. MID = true:
+// finds the first digit and takes the histogram of the second among the values that have it.
 template <bool MID>
 __global__ __launch_bounds__(kSelBlock) void k_sel_hist(const double* __restrict__ theta, int64_t n, int64_t k,
                                                         uint32_t* __restrict__ hist, uint64_t* __restrict__ sel,

@@ -64,3 +64,23 @@ def test_public_sizes_never_fall(params):
                for c in (0, 1, 500, 2_966, 13_797, 13_853, 60_562, 10 ** 6)]
         assert row == sorted(row) and row[4] >= last, n
         last = row[4]
+
+
+def test_room_for_the_partial_sums():
+    """The room counted for partial sums holds splits x padded queries, also at the steps of the rules."""
+    lib = dwg.load()
+    fn = {}
+    for name, args in (("choose_split", "lli"), ("split_columns", "lli"), ("tree_segments", "ll"), ("segment_columns", "ll")):
+        f = lib[f"_ZN3dwg{len(name)}{name}E{args}"]
+        f.argtypes = [ctypes.c_int64 if a == "l" else ctypes.c_int for a in args]
+        f.restype = ctypes.c_int64 if name.endswith("columns") else ctypes.c_int
+        fn[name] = f
+    rng = random.Random(2)
+    sizes = [int(10 ** rng.uniform(0, 9.3)) for _ in range(4000)]
+    sizes += [64 * w + d for w in range(1, 4200, 7) for d in (-1, 0, 1)]
+    for m in sizes:
+        padded = -(-m // 512) * 512
+        for n in (1, 63, 64, 65, 4096, 30_000, 1_000_000, m, int(10 ** rng.uniform(0, 9))):
+            for split in (0, 0, 1, 5, 64):
+                assert fn["split_columns"](n, m, split) >= fn["choose_split"](n, m, split) * padded, (n, m, split)
+            assert fn["segment_columns"](n, m) >= fn["tree_segments"](n, m) * padded, (n, m)

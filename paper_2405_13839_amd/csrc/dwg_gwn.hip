@@ -90,7 +90,7 @@ __device__ __forceinline__ void tile_loop(const float4* sa, const float4* sb, co
 // q0 + k*NT + tid); grid.y = source split. Sources are staged in LDS TS at a time and read
 // back as broadcasts; TS divides the 256 sources of a tile. Per tile, each wavefront decides whether the tile is far
 // from all of its queries -- box distance above the tile's largest radius, so no pair can be
-// clamped or coincident -- and then runs the shorter far-pair loop; a far tile whose box
+// clamped, coincident or too short for 1/r^3 -- and then runs the shorter far-pair loop; a far tile whose box
 // distance is also at least the largest distance of one of its queries from the block's centre
 // takes the separated far loop (r^2 and m . (p - q) from per-source |p|^2 and m . p). (Deciding
 // by the block's box puts fewer tiles in the short loops: values at 131K queries off the surface of 50K
@@ -279,7 +279,10 @@ __global__ __launch_bounds__(kQBlock) void k_gwn_small(
 // A NaN delta poisons the source's m so that the result is NaN as in the definition. Clears the
 // stop flag of an iteration. With tbox (the all-pairs kernels'), a block is a source tile and writes its
 // box (real sources only) and largest radius max(delta, eps), in the unscaled units of the
-// positions (the staged 1/radius carries kappa).
+// positions (the staged 1/radius carries kappa), or kLeastFar where that is more: no tile is far from a query
+// of which a pair is so short that 1/r^3 overflows. (As one more term of the test in the kernel: 1M x 1M 510 -> 529 ms.)
+constexpr float kLeastFar = 0x1p-42f;  // scaled length below which the general loop's guard, r^2 2^126 for 1/r, is at work
+
 __global__ __launch_bounds__(kTile) void k_stage(const float* __restrict__ P, const float* __restrict__ N,
                         const float* __restrict__ A, const float* __restrict__ D, int64_t n,
                         float eps, float kappa, const int32_t* __restrict__ perm,
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(kTile) void k_stage(const float* __restrict__ P, co
 #pragma unroll
   for (int d = 0; d < 7; ++d)
     for (int w = 0; w < kTile / 64; ++w) v[d] = d < 3 ? fminf(v[d], lds[d][w]) : fmaxf(v[d], lds[d][w]);
-  tbox[2 * blockIdx.x] = make_float4(v[0], v[1], v[2], v[6]);
+  tbox[2 * blockIdx.x] = make_float4(v[0], v[1], v[2], fmaxf(v[6], kLeastFar / kappa));
   tbox[2 * blockIdx.x + 1] = make_float4(v[3], v[4], v[5], 0.0f);
 }
 

@@ -365,6 +365,7 @@ size_t dwg_workspace_bytes(int64_t n_src, int64_t n_qry, const dwg_kernel_params
   if (check_kp(kp) != DWG_OK) return 0;
   const dwg_kernel_params k = kp ? *kp : kDefaultKp;
   size_t a = gwn_bytes(n_src, n_qry, k);
+  if (tree_mode(k)) a += align256(kTreeWorkCounts * sizeof(unsigned long long));  // dwg_octree_work's own
   size_t b = aux_bytes(std::max(n_src, n_qry));
   size_t c = mlp_ws_bytes(std::max(n_src, n_qry));
   return align256(std::max(a, std::max(b, c)));
